@@ -488,6 +488,7 @@ static rsi_status run_rays(rsi_mesh mesh, const float *from, const float *to, in
     a.stack = stack;
     a.waves_per_cu = waves;
     a.node_width = width;
+    a.default_shape = !opts || (opts->block == 0 && opts->stack_depth == 0 && opts->waves_per_cu == 0);
     uint64_t *ws_counters = reinterpret_cast<uint64_t *>(static_cast<char *>(ws));
     a.queue_len = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + 32);
     a.queue = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + 64);
@@ -974,6 +975,7 @@ rsi_status rsi_batch_intersect(rsi_batch batch, const float *rays_from, const fl
     a.stack = stack;
     a.waves_per_cu = waves;
     a.node_width = width;
+    a.default_shape = !opts || (opts->block == 0 && opts->stack_depth == 0 && opts->waves_per_cu == 0);
     a.hit = out->hit;
     a.tri_id = out->tri_id;
     a.uvt = out->uvt;

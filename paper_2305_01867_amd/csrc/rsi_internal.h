@@ -210,6 +210,7 @@ struct TraverseArgs {
     int stack = 24;
     int waves_per_cu = 0;          // 0: library default
     int node_width = 0;            // 0: the mesh's widest tree, 2: binary nodes
+    int default_shape = 0;         // the caller left block, stack depth and resident waves to the library
     uint8_t *hit = nullptr;
     int32_t *tri_id = nullptr;
     float *uvt = nullptr;

@@ -26,324 +26,13 @@
 // of the segment and mesh.  That margin exceeds every rounding of the slab
 // arithmetic, so a point within eta/4 of a box is never culled -- in
 // particular any binary64 hit of a non-grazing segment.
-#include "rsi_internal.h"
+#include "pool.h"
 
 #include <cstdlib>
 #include <type_traits>
 
 namespace rsi {
 namespace {
-
-constexpr float kEtaRel = 0x1p-20f;
-constexpr float kBoundK = 12.0f * 0x1p-24f;  // >= 8 u32 (binary32) + 8 u64 (binary64) with slack
-constexpr float kBoundTiny = 0x1p-140f;      // absorbs underflow in the products
-constexpr int kMiss = 0, kHit = 1, kUnsure = 2;
-enum { MODE_BOOL = 0, MODE_FIRST = 1, MODE_BARY = 2, MODE_COUNT = 3 };
-// distinct t a lane keeps in registers in count mode: binary32 values (plain),
-// or intervals of two floats each (certified: 11, which keeps the kernel
-// within its 128 VGPRs with few spills; the segments with more go to the
-// second pass -- 27k of 1e7 at the paper's scale, 6.38 -> 6.28 ms against 12)
-template <bool CERT>
-constexpr int kCountSlots = CERT ? 11 : 12;
-
-struct Ray {
-    float3 o, d;   // start point, direction E - O (rounded)
-    float3 inv;    // 1 / direction (components below eta/4 raised to eta/4)
-    float3 nra;    // -(O + eta) * inv   (lower box faces)
-    float3 nrb;    // -(O - eta) * inv   (upper box faces)
-};
-
-__device__ __forceinline__ bool finite3(float3 v) {
-    return __builtin_isfinite(v.x) && __builtin_isfinite(v.y) && __builtin_isfinite(v.z);
-}
-
-__device__ __forceinline__ float widen_dir(float d, float dmin) {
-    return fabsf(d) < dmin ? copysignf(dmin, d) : d;
-}
-
-// Returns false for segments whose setup is not finite.
-__device__ __forceinline__ bool setup_ray(const float *__restrict__ from, const float *__restrict__ to,
-                                          int64_t i, float scale, Ray &r) {
-    // streamed once: non-temporal, so the segments do not push the tree out of L2
-    r.o = make_float3(__builtin_nontemporal_load(from + 3 * i), __builtin_nontemporal_load(from + 3 * i + 1),
-                      __builtin_nontemporal_load(from + 3 * i + 2));
-    const float3 e = make_float3(__builtin_nontemporal_load(to + 3 * i), __builtin_nontemporal_load(to + 3 * i + 1),
-                                 __builtin_nontemporal_load(to + 3 * i + 2));
-    r.d = make_float3(e.x - r.o.x, e.y - r.o.y, e.z - r.o.z);
-    float m = fmaxf(scale, fmaxf(fmaxf(fabsf(r.o.x), fabsf(r.o.y)), fabsf(r.o.z)));
-    m = fmaxf(m, fmaxf(fmaxf(fabsf(e.x), fabsf(e.y)), fabsf(e.z)));
-    const float eta = m * kEtaRel;
-    const float dmin = 0.25f * eta;
-    r.inv = make_float3(1.0f / widen_dir(r.d.x, dmin), 1.0f / widen_dir(r.d.y, dmin), 1.0f / widen_dir(r.d.z, dmin));
-    r.nra = make_float3(-((r.o.x + eta) * r.inv.x), -((r.o.y + eta) * r.inv.y), -((r.o.z + eta) * r.inv.z));
-    r.nrb = make_float3(-((r.o.x - eta) * r.inv.x), -((r.o.y - eta) * r.inv.y), -((r.o.z - eta) * r.inv.z));
-    return finite3(r.o) && finite3(e) && finite3(r.d) && finite3(r.inv) && finite3(r.nra) && finite3(r.nrb) &&
-           __builtin_isfinite(eta);
-}
-
-// Widened slab test of one box against t in [0, tlimit]; returns the entry t.
-__device__ __forceinline__ bool slab(float xlo, float xhi, float ylo, float yhi, float zlo, float zhi,
-                                     const Ray &r, float tlimit, float &tenter) {
-    const float tx0 = fmaf(xlo, r.inv.x, r.nra.x), tx1 = fmaf(xhi, r.inv.x, r.nrb.x);
-    const float ty0 = fmaf(ylo, r.inv.y, r.nra.y), ty1 = fmaf(yhi, r.inv.y, r.nrb.y);
-    const float tz0 = fmaf(zlo, r.inv.z, r.nra.z), tz1 = fmaf(zhi, r.inv.z, r.nrb.z);
-    const float tmin = fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), fmaxf(fminf(tz0, tz1), 0.0f));
-    const float tmax = fminf(fminf(fmaxf(tx0, tx1), fmaxf(ty0, ty1)), fminf(fmaxf(tz0, tz1), tlimit));
-    tenter = tmin;
-    return tmin <= tmax;
-}
-
-// The same test with the near and far face of each axis given (the lower
-// face is the near one for a direction component >= 0, the upper one
-// otherwise, with the matching offsets nn / nf of nra / nrb).  For a box with
-// lo <= hi the sign picks exactly the operands min / max pick in slab(), so
-// the decisions are the same bit for bit; a box that is +inf on every face
-// still misses.
-__device__ __forceinline__ bool slab_nf(float nx, float fx, float ny, float fy, float nz, float fz,
-                                        const float3 &inv, const float3 &nn, const float3 &nf, float tlimit,
-                                        float &tenter) {
-    const float tnx = fmaf(nx, inv.x, nn.x), tfx = fmaf(fx, inv.x, nf.x);
-    const float tny = fmaf(ny, inv.y, nn.y), tfy = fmaf(fy, inv.y, nf.y);
-    const float tnz = fmaf(nz, inv.z, nn.z), tfz = fmaf(fz, inv.z, nf.z);
-    const float tmin = fmaxf(fmaxf(tnx, tny), fmaxf(tnz, 0.0f));
-    const float tmax = fminf(fminf(tfx, tfy), fminf(tfz, tlimit));
-    tenter = tmin;
-    return tmin <= tmax;
-}
-
-struct MT32 {
-    float det, U, W, T;
-    float3 s;
-};
-
-// Binary32 Moller-Trumbore quantities (contraction allowed: the bound below
-// holds for any grouping into fused operations).
-__device__ __forceinline__ MT32 mt32(const Tri &tri, const Ray &r) {
-    MT32 m;
-    const float3 e1 = make_float3(tri.e1.x, tri.e1.y, tri.e1.z);
-    const float3 e2 = make_float3(tri.e2.x, tri.e2.y, tri.e2.z);
-    m.s = make_float3(r.o.x - tri.a.x, r.o.y - tri.a.y, r.o.z - tri.a.z);
-    const float px = r.d.y * e2.z - r.d.z * e2.y;
-    const float py = r.d.z * e2.x - r.d.x * e2.z;
-    const float pz = r.d.x * e2.y - r.d.y * e2.x;
-    const float qx = m.s.y * e1.z - m.s.z * e1.y;
-    const float qy = m.s.z * e1.x - m.s.x * e1.z;
-    const float qz = m.s.x * e1.y - m.s.y * e1.x;
-    m.det = e1.x * px + e1.y * py + e1.z * pz;
-    m.U = m.s.x * px + m.s.y * py + m.s.z * pz;
-    m.W = r.d.x * qx + r.d.y * qy + r.d.z * qz;
-    m.T = e2.x * qx + e2.y * qy + e2.z * qz;
-    return m;
-}
-
-// The binary32 decision, same predicates as the definition.
-__device__ __forceinline__ bool decide32(const MT32 &m) {
-    if (!(m.det != 0.0f))
-        return false;
-    const float g = m.det > 0.0f ? 1.0f : -1.0f;
-    const float a = g * m.U, b = g * m.W, tt = g * m.T, D = g * m.det;
-    return a >= 0.0f && b >= 0.0f && a + b <= D && tt >= 0.0f && tt <= D;
-}
-
-// Certified classification.  Every binary32 quantity X (det, U, W, T) is a sum
-// of six signed products of three rounded differences, formed with at most 8
-// roundings per product; so |X32 - X| <= gamma_8 M(X) with M(X) the same sum
-// over absolute values, and the binary64 evaluation obeys the same form with
-// unit roundoff 2^-53.  B(X) = 12 * 2^-24 * M(X) covers both with room for the
-// roundings of M itself.  For a hit the interval [tlo, thi] holds the exact t
-// and the binary64 t.
-struct Bounds {
-    float d, U, W, T;
-};
-
-__device__ __forceinline__ Bounds mt_bounds(const MT32 &m, const Tri &tri, const Ray &r) {
-    const float adx = fabsf(r.d.x), ady = fabsf(r.d.y), adz = fabsf(r.d.z);
-    const float asx = fabsf(m.s.x), asy = fabsf(m.s.y), asz = fabsf(m.s.z);
-    const float a1x = fabsf(tri.e1.x), a1y = fabsf(tri.e1.y), a1z = fabsf(tri.e1.z);
-    const float a2x = fabsf(tri.e2.x), a2y = fabsf(tri.e2.y), a2z = fabsf(tri.e2.z);
-    const float Pmx = ady * a2z + adz * a2y, Pmy = adz * a2x + adx * a2z, Pmz = adx * a2y + ady * a2x;
-    const float Qmx = asy * a1z + asz * a1y, Qmy = asz * a1x + asx * a1z, Qmz = asx * a1y + asy * a1x;
-    Bounds b;
-    b.d = fmaf(kBoundK, a1x * Pmx + a1y * Pmy + a1z * Pmz, kBoundTiny);
-    b.U = fmaf(kBoundK, asx * Pmx + asy * Pmy + asz * Pmz, kBoundTiny);
-    b.W = fmaf(kBoundK, adx * Qmx + ady * Qmy + adz * Qmz, kBoundTiny);
-    b.T = fmaf(kBoundK, a2x * Qmx + a2y * Qmy + a2z * Qmz, kBoundTiny);
-    return b;
-}
-
-__device__ __forceinline__ int classify(const MT32 &m, const Tri &tri, const Ray &r, float &tlo, float &thi) {
-    const Bounds bb = mt_bounds(m, tri, r);
-    const float Bd = bb.d, BU = bb.U, BW = bb.W, BT = bb.T;
-    const float aD = fabsf(m.det);
-    // a hit needs |U|, |W|, |T| <= |det| in binary64; a sure excess is a sure miss
-    const float cap = aD + Bd;
-    if (fabsf(m.U) - BU > cap || fabsf(m.W) - BW > cap || fabsf(m.T) - BT > cap)
-        return kMiss;
-    if (!(aD > Bd))
-        return kUnsure;  // sign of det (or det == 0) not certain; also NaN
-    const float g = m.det > 0.0f ? 1.0f : -1.0f;
-    const float a = g * m.U, b = g * m.W, tt = g * m.T;
-    const float w = g * ((m.det - m.U) - m.W);  // D - a - b
-    const float z = g * (m.det - m.T);          // D - tt
-    const float Bw = Bd + BU + BW + 0x1p-22f * (aD + fabsf(m.U) + fabsf(m.W));
-    const float Bz = Bd + BT + 0x1p-22f * (aD + fabsf(m.T));
-    if (a < -BU || b < -BW || w < -Bw || tt < -BT || z < -Bz)
-        return kMiss;
-    if (a > BU && b > BW && w > Bw && tt > BT && z > Bz) {
-        tlo = (tt - BT) / (aD + Bd) * (1.0f - 0x1p-21f);
-        thi = (tt + BT) / (aD - Bd) * (1.0f + 0x1p-21f);
-        return kHit;
-    }
-    return kUnsure;
-}
-
-// Binary64 test in the definition's operation order: differences, cross
-// products, dot products summed left to right, no fused operations, correctly
-// rounded division.
-struct MT64 {
-    bool hit;
-    double u, v, t;
-};
-
-__device__ __forceinline__ MT64 mt64(double ox, double oy, double oz, double ex, double ey, double ez,
-                                     const float *__restrict__ V, const int32_t *__restrict__ F, int t) {
-#pragma clang fp contract(off)
-    const int32_t i0 = F[3 * (int64_t)t], i1 = F[3 * (int64_t)t + 1], i2 = F[3 * (int64_t)t + 2];
-    const double Ax = V[3 * (int64_t)i0], Ay = V[3 * (int64_t)i0 + 1], Az = V[3 * (int64_t)i0 + 2];
-    const double Bx = V[3 * (int64_t)i1], By = V[3 * (int64_t)i1 + 1], Bz = V[3 * (int64_t)i1 + 2];
-    const double Cx = V[3 * (int64_t)i2], Cy = V[3 * (int64_t)i2 + 1], Cz = V[3 * (int64_t)i2 + 2];
-    const double dx = ex - ox, dy = ey - oy, dz = ez - oz;
-    const double e1x = Bx - Ax, e1y = By - Ay, e1z = Bz - Az;
-    const double e2x = Cx - Ax, e2y = Cy - Ay, e2z = Cz - Az;
-    const double sx = ox - Ax, sy = oy - Ay, sz = oz - Az;
-    const double px = dy * e2z - dz * e2y, py = dz * e2x - dx * e2z, pz = dx * e2y - dy * e2x;
-    const double qx = sy * e1z - sz * e1y, qy = sz * e1x - sx * e1z, qz = sx * e1y - sy * e1x;
-    const double det = (e1x * px + e1y * py) + e1z * pz;
-    const double U = (sx * px + sy * py) + sz * pz;
-    const double W = (dx * qx + dy * qy) + dz * qz;
-    const double T = (e2x * qx + e2y * qy) + e2z * qz;
-    MT64 r{false, 0.0, 0.0, 0.0};
-    if (det == 0.0)
-        return r;
-    const double g = det > 0.0 ? 1.0 : -1.0;
-    const double a = g * U, b = g * W, tt = g * T, D = g * det;
-    if (a >= 0.0 && b >= 0.0 && a + b <= D && tt >= 0.0 && tt <= D) {
-        r.hit = true;
-        r.u = U / det;
-        r.v = W / det;
-        r.t = T / det;
-    }
-    return r;
-}
-
-__device__ __forceinline__ bool valid_tri(const int32_t *__restrict__ F, int64_t nv, int t) {
-    const int32_t i0 = F[3 * (int64_t)t], i1 = F[3 * (int64_t)t + 1], i2 = F[3 * (int64_t)t + 2];
-    return i0 >= 0 && i1 >= 0 && i2 >= 0 && i0 < nv && i1 < nv && i2 < nv;
-}
-
-struct Outs {
-    uint8_t *hit;
-    int32_t *id;
-    float *uvt;
-    int32_t *count;
-};
-
-__device__ __forceinline__ void write_count(const Outs &o, int64_t i, int32_t c) {
-    if (o.hit)
-        o.hit[i] = c > 0 ? 1 : 0;
-    o.count[i] = c;
-}
-
-__device__ __forceinline__ void write_out(const Outs &o, int64_t i, int mode, int id, float u, float v, float t) {
-    if (mode == MODE_COUNT) {
-        write_count(o, i, id >= 0 ? 1 : 0);
-        return;
-    }
-    if (o.hit)
-        o.hit[i] = id >= 0 ? 1 : 0;
-    if (mode != MODE_BOOL)
-        o.id[i] = id;
-    if (mode == MODE_BARY) {
-        o.uvt[3 * i] = id >= 0 ? u : NAN;
-        o.uvt[3 * i + 1] = id >= 0 ? v : NAN;
-        o.uvt[3 * i + 2] = id >= 0 ? t : NAN;
-    }
-}
-
-struct TravParams {
-    const Node *__restrict__ nodes;
-    const Node4 *__restrict__ nodes4;  // the 4-wide tree the first pass walks, or NULL
-    const Node4 *__restrict__ top4;    // its first kTopSlots nodes, breadth-first
-    int top_lds;                       // how many of them each workgroup keeps in LDS
-    int bary_after;                    // certified barycentric, one mesh: (u, v, t) by k_bary64
-    const Tri *__restrict__ tris;
-    const float *__restrict__ V;
-    const int32_t *__restrict__ F;
-    const float *__restrict__ bounds;
-    int64_t nv;
-    int64_t nt;
-    int root;
-    const float *__restrict__ from;
-    const float *__restrict__ to;
-    int64_t n;
-    Outs out;
-    int stack_depth;
-    int waves_per_cu;
-    int32_t *queue;
-    uint32_t *queue_len;
-    uint32_t *next_ray;
-    unsigned long long *counters;
-    uint32_t *visits;
-    uint32_t *tests;
-    const uint8_t *bucket;
-    const int32_t *bucket_ref;
-    const int4 *items;
-    int n_items;
-    const int32_t *group_start;  // [n_groups + 1] first item of each group, or NULL: one queue
-    int n_groups;
-    int n_meshes;
-    const int32_t *mesh_root;
-    const int32_t *mesh_root4;  // the mesh roots as 4-wide references (first pass over 4-wide nodes)
-    // batched form, 4-wide, every top slot in LDS: each workgroup keeps the
-    // top of its XCD group's meshes (group blockIdx.x mod n_groups) instead
-    // of the combined tree's, with the mesh roots as references in it
-    const Node4 *top4g;
-    const int32_t *roots4g;
-    int top_group;
-    const int32_t *mesh_toff;
-    const int32_t *ray_off;
-    const int32_t *order;  // segment at each processing position (NULL: input order)
-    int stage_ok;          // boolean results may be staged per wave (4-byte aligned output)
-    int deep_cap;          // second pass: entries of a lane's private stack (<= kDeepStack)
-    int wave_cap;          // second pass: entries of a wave's shared stack (<= its LDS array)
-};
-
-__device__ __forceinline__ void enqueue(const TravParams &p, int64_t i, int why) {
-    const uint32_t slot = atomicAdd(p.queue_len, 1u);
-    p.queue[slot] = (int32_t)i;
-    atomicAdd(p.counters + why, 1ull);
-}
-
-
-// Pointers into LDS by address space, so reads of the LDS copy of the tree's
-// top compile to ds_read and are not merged with the global path.
-typedef const __attribute__((address_space(3))) char *LdsBytes;
-typedef float F4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 lds_f4(LdsBytes p) {
-    const F4v v = *reinterpret_cast<const __attribute__((address_space(3))) F4v *>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-
-// Compare-exchange of (entry t, child) pairs: the nearer first.
-__device__ __forceinline__ void order2(float &ka, int &ca, float &kb, int &cb) {
-    const bool sw = kb < ka;
-    const float lo = fminf(ka, kb), hi = fmaxf(ka, kb);
-    const int cl = sw ? cb : ca, ch = sw ? ca : cb;
-    ka = lo;
-    kb = hi;
-    ca = cl;
-    cb = ch;
-}
 
 // ------------------------------------------------------------------ pass 1
 // Persistent waves.  Each wave owns a contiguous range of segments; a lane
@@ -377,6 +66,11 @@ constexpr int kDone = INT32_MIN;  // nothing left for the lane's segment
 constexpr int64_t kTailDiv = 6;
 constexpr int kTailChunk = 64;
 
+// Once a wave has no new segments and at most this many in flight, its lanes
+// share them (16 to 64 measure the same within 1%, 8 less: 1e6 boolean
+// segments 351 us without, 243 at 8, 230 at 24; 1e7 1631 / 1538 / 1527).
+constexpr int kTailLanes = 24;
+
 // Boolean results of one mesh in input order are staged per wave in LDS and
 // written out a window of kStageWin segments at a time (whole lines instead
 // of single bytes as segments finish): two windows per wave, each a value
@@ -392,9 +86,12 @@ constexpr int kStageWaveWords = 2 * kStageWords + 2;  // two windows, padded to 
 // visit exactly what the plain order visits, so results do not change.
 template <int MODE, bool CERT, bool STATS, bool PROP, bool WIDE>
 __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
-    int *stk = lds_stack + threadIdx.x;
-    const int stride = blockDim.x;
     const int lane = threadIdx.x & 63;
+    // each wave's stacks are a block of LDS of their own, an entry of all 64
+    // lanes after the other
+    constexpr int stride = 64;
+    const int wave_stack = (p.stack_depth + (WIDE ? 3 : 1)) * stride;
+    int *stk = lds_stack + (threadIdx.x >> 6) * wave_stack + lane;
     const uint64_t lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
     const float scale = p.bounds[6];
     const int n_internal = (int)p.nt - 1;
@@ -402,12 +99,12 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     const int depth_lim = p.stack_depth * stride;  // stack offsets are kept in units of lanes
     // 4-wide: the top of the tree in LDS, after the stacks (read-only once filled)
     const int ref_lim = WIDE ? n_internal + kTopSlots : n_internal;
-    float4 *top_cache = reinterpret_cast<float4 *>(lds_stack + (p.stack_depth + 3) * stride);
+    float4 *top_cache = reinterpret_cast<float4 *>(lds_stack + (p.stack_depth + 3) * blockDim.x);
     const int group = p.n_groups > 0 ? (int)(blockIdx.x % p.n_groups) : 0;
     if (WIDE) {
         const Node4 *top = p.top_group ? p.top4g + (int64_t)group * kTopSlots : p.top4;
         const float4 *src = reinterpret_cast<const float4 *>(top);
-        for (int i = threadIdx.x; i < 8 * p.top_lds; i += stride)
+        for (int i = threadIdx.x; i < 8 * p.top_lds; i += blockDim.x)
             top_cache[i] = src[i];
         __syncthreads();
     }
@@ -438,7 +135,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     if (stage) {
         // after the stacks (stack_depth + 3 entries per lane with 4-wide nodes,
         // + 1 with binary ones) and the top nodes
-        stage_w = reinterpret_cast<uint32_t *>(lds_stack + (p.stack_depth + (WIDE ? 3 : 1)) * stride +
+        stage_w = reinterpret_cast<uint32_t *>(lds_stack + (p.stack_depth + (WIDE ? 3 : 1)) * blockDim.x +
                                                32 * p.top_lds) +
                   (threadIdx.x >> 6) * kStageWaveWords;
         if (lane < kStageWaveWords)
@@ -486,6 +183,10 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     int lane_root = p.root, lane_toff = 0;  // of the lane's current segment
 
     int64_t ray = -1;
+    // the last segments shared by the wave's lanes: where a pool of at least
+    // 512 node entries fits in the wave's stacks
+    constexpr bool kTail = WIDE && !STATS && MODE != MODE_COUNT;
+    const bool tail = kTail && wave_stack >= 512 + kPoolLeafCap + 64 && p.nt <= kMaxPoolTris;
     Ray r;
     // 4-wide: byte offsets in a node of the near-face rows (x lo or hi at 0 /
     // 16, y at 32 / 48, z at 64 / 80; the far row is the other of each pair)
@@ -532,6 +233,53 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     bool list_full = false;
 
     auto pop = [&]() -> int { return sp > 0 ? stk[sp -= stride] : kDone; };
+
+    // the lane's segment is decided: its result goes out
+    auto finish = [&]() {
+        if (PROP && !STATS && best_late && (found || (MODE != MODE_BOOL && best_id >= 0 && !flagged && !overflow)))
+            ++n_late;  // the proposal did not hold the answer
+        if (STATS) {
+            p.visits[ray] = n_nodes;
+            p.tests[ray] = n_tests;
+        } else if (MODE == MODE_COUNT) {
+            if (overflow)
+                enqueue(p, ray, 1);
+            else if (list_full)
+                enqueue(p, ray, 3);
+            else if (CERT && flagged)
+                enqueue(p, ray, 0);
+            else
+                write_count(p.out, ray, nk);
+        } else if (MODE == MODE_BOOL) {
+            // a queued segment counts as finished here (0); the second
+            // pass writes its result after this kernel
+            if (!found && overflow)
+                enqueue(p, ray, 1);
+            seg_redecided += n_redecided > 0 ? 1u : 0u;
+            put_hit(ray, found ? 1u : 0u);
+        } else {
+            if (CERT && n_redecided > 0 && !flagged)
+                ++seg_redecided;  // (a flagged segment is counted when queued)
+            if (overflow) {
+                enqueue(p, ray, 1);
+            } else if (CERT && flagged) {
+                enqueue(p, ray, 0);
+            } else if (CERT && MODE == MODE_BARY && best_id >= 0) {
+                if (p.bary_after) {  // (u, v, t) after both passes, a lane per segment
+                    if (p.out.hit)
+                        p.out.hit[ray] = 1;
+                    p.out.id[ray] = best_id - lane_toff;
+                } else {
+                    const float *o = p.from + 3 * ray, *e = p.to + 3 * ray;
+                    const MT64 h = mt64(o[0], o[1], o[2], e[0], e[1], e[2], p.V, p.F, best_id);
+                    write_out(p.out, ray, MODE, best_id - lane_toff, (float)h.u, (float)h.v, (float)h.t);
+                }
+            } else {
+                write_out(p.out, ray, MODE, best_id >= 0 ? best_id - lane_toff : -1, best_u, best_v, best_t);
+            }
+        }
+        ray = -1;
+    };
 
     for (;;) {
         // ---- refill idle lanes
@@ -663,6 +411,10 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                 break;
             continue;
         }
+
+        // the wave's last segments, once no new ones are left: see after the loop
+        if (kTail && tail && !items_left && cursor >= range_end && __popcll(active) <= kTailLanes)
+            break;
 
         // ---- node phase
         // Push and pop are branch-free: every lane has one spare LDS slot past
@@ -980,57 +732,70 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
         }
 
         // ---- finish lanes whose segment is decided
-        if (ray >= 0 && ref == kDone && none_held()) {
-            if (PROP && !STATS && best_late && (found || (MODE != MODE_BOOL && best_id >= 0 && !flagged && !overflow)))
-                ++n_late;  // the proposal did not hold the answer
-            if (STATS) {
-                p.visits[ray] = n_nodes;
-                p.tests[ray] = n_tests;
-            } else if (MODE == MODE_COUNT) {
-                if (overflow)
-                    enqueue(p, ray, 1);
-                else if (list_full)
-                    enqueue(p, ray, 3);
-                else if (CERT && flagged)
-                    enqueue(p, ray, 0);
-                else
-                    write_count(p.out, ray, nk);
-            } else if (MODE == MODE_BOOL) {
-                // a queued segment counts as finished here (0); the second
-                // pass writes its result after this kernel
-                if (!found && overflow)
-                    enqueue(p, ray, 1);
-                seg_redecided += n_redecided > 0 ? 1u : 0u;
-                put_hit(ray, found ? 1u : 0u);
-            } else {
-                if (CERT && n_redecided > 0 && !flagged)
-                    ++seg_redecided;  // (a flagged segment is counted when queued)
-                if (overflow) {
-                    enqueue(p, ray, 1);
-                } else if (CERT && flagged) {
-                    enqueue(p, ray, 0);
-                } else if (CERT && MODE == MODE_BARY && best_id >= 0) {
-                    if (p.bary_after) {  // (u, v, t) after both passes, a lane per segment
-                        if (p.out.hit)
-                            p.out.hit[ray] = 1;
-                        p.out.id[ray] = best_id - lane_toff;
-                    } else {
-                        const float *o = p.from + 3 * ray, *e = p.to + 3 * ray;
-                        const MT64 h = mt64(o[0], o[1], o[2], e[0], e[1], e[2], p.V, p.F, best_id);
-                        write_out(p.out, ray, MODE, best_id - lane_toff, (float)h.u, (float)h.v, (float)h.t);
-                    }
-                } else {
-                    write_out(p.out, ray, MODE, best_id >= 0 ? best_id - lane_toff : -1, best_u, best_v, best_t);
-                }
-            }
-            ray = -1;
-        }
+        if (ray >= 0 && ref == kDone && none_held())
+            finish();
         if (stage) {  // a complete older window goes out whole (then perhaps the next one)
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int64_t need = range_end - win_base < kStageWin ? range_end - win_base : kStageWin;
                 if (need > 0 && stage_w[win_old * kStageWords + 16] == (uint32_t)need)
                     stage_flush();
+            }
+        }
+    }
+    if constexpr (kTail) {
+        // The wave's last segments: all lanes share them through a pool in the
+        // wave's stack memory (pool.h).  They start again from the root,
+        // keeping the limit found so far.
+        if (__ballot(ray >= 0)) {
+            PoolSegment<MODE, CERT> s;
+            s.reset();
+            s.ray = (int)ray;
+            s.toff = 0;
+            s.o = r.o;
+            s.d = r.d;
+            s.inv = r.inv;
+            s.nn = nn;
+            s.nf = nf;
+            s.tlimit = tlimit;
+            s.best_id = best_id;
+            s.best_t = best_t;
+            s.best_u = best_u;
+            s.best_v = best_v;
+            s.best_lo = best_lo;
+            s.best_hi = best_hi;
+            s.best_exact = best_exact;
+            s.best_t64 = best_t64;
+            Pool<MODE, CERT, PROP> pool;
+            pool.init(p, reinterpret_cast<uint32_t *>(stk - lane), 64, wave_stack - kPoolLeafCap - 64);
+            pool.top_cache = top_cache;
+            pool.top_lds = p.top_lds;
+            const uint32_t tag = (uint32_t)lane << kPoolRefBits;
+            bool rest = ray >= 0;
+            wave_lds_fence();
+            if (PROP) {  // the proposed subtree first, then what is left without it
+                s.late = phase == 1;
+                s.best_late = best_late;
+                pool.push(ray >= 0 && phase == 0, skip, tag);
+                wave_lds_fence();
+                pool.run(p, s, 0, 64);
+                s.late = true;
+                s.skip = skip;
+                rest = ray >= 0 && s.tlimit >= 0.0f && lane_root != skip;
+            }
+            pool.push(rest, lane_root, tag);
+            wave_lds_fence();
+            pool.run(p, s, 0, 64);
+            if (ray >= 0) {
+                best_late = s.best_late;
+                found = MODE == MODE_BOOL && s.best_id >= 0;
+                overflow = (pool.lost >> lane) & 1ull;
+                best_id = s.best_id;
+                best_t = s.best_t;
+                best_u = s.best_u;
+                best_v = s.best_v;
+                n_redecided += s.redecided;
+                finish();
             }
         }
     }
@@ -1767,7 +1532,33 @@ TravParams make_params(const MeshDev &m, const TraverseArgs &a) {
             p.wave_cap = k;
         }
     }
+    // RSI_DEBUG_POOL_NODES=k (1..) shrinks the pool form's node stack, so
+    // tests reach its overflow into the second pass
+    p.pool_cap = INT32_MAX;
+    if (const char *env = getenv("RSI_DEBUG_POOL_NODES"))
+        if (atoi(env) >= 1)
+            p.pool_cap = atoi(env);
     return p;
+}
+
+// Does the first pass run in pool form (pool.hip)?  In count mode always: it
+// visits every candidate in any order, and the pool keeps the lanes busy
+// (1e7 segments of the paper's scale 6.30 -> 4.83 ms, 1e6 0.93 -> 0.57).  In
+// the other modes up to one and a half times the lanes that are resident at
+// once (393,216): below that the launch is its slowest segments (1e4 segments
+// 156 -> 35 us, 1e5 against 526k triangles 293 -> 114, 2.5e5 at the paper's
+// scale 175 -> 120); above it a lane's nearest-first walk with its last
+// segments shared does less work (5e5: 198 against 224 us, 1e6: 292 / 388).
+// A launch shape the caller chose is the lane form's.
+bool use_pool(const TravParams &p, const TraverseArgs &a) {
+    if (!a.default_shape || p.nodes4 == nullptr || a.bucket != nullptr || p.nt > kMaxPoolTris)
+        return false;
+    if (a.mode == MODE_COUNT)
+        return true;
+    int dev = 0, cus = 256;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    return a.n <= (int64_t)cus * kDefaultWavesPerCU * 64 * 3 / 2;
 }
 
 // Keys and a stable sort of the segment indices; p.order then lists them.
@@ -1803,7 +1594,10 @@ hipError_t launch_intersect(const MeshDev &m, const TraverseArgs &a, hipStream_t
     const hipError_t e = order_segments(a, p, s);
     if (e != hipSuccess)
         return e;
-    dispatch_pass1<false>(p, a.mode, a.certified != 0, a.block, s);
+    if (use_pool(p, a))
+        launch_pool(p, a.mode, a.certified != 0, s);
+    else
+        dispatch_pass1<false>(p, a.mode, a.certified != 0, a.block, s);
     // enough blocks for one per segment of a short queue; a long queue is
     // taken 64 segments per block (count mode: a wave per segment, with
     // small blocks that fit many per CU)
