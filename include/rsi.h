@@ -123,7 +123,13 @@ typedef struct rsi_build_opts {
                               Results of rsi_intersect do not depend on the algorithm. */
 } rsi_build_opts;
 
-/* Intersection options; pass NULL for defaults. */
+/* Intersection options; pass NULL for defaults.  With block, stack_depth and
+ * waves_per_cu all 0 the first pass over 4-wide nodes takes the form that suits
+ * the call: up to 1.5 x 64 x 16 segments per compute unit, and in the
+ * intercept-count mode always, the segments of a wave share its lanes through
+ * a pool of pending nodes and leaves; otherwise each lane has a segment of its
+ * own.  A value other than 0 in any of the three asks for the latter with that
+ * shape. */
 typedef struct rsi_intersect_opts {
     int32_t precision;    /* rsi_precision; default RSI_PRECISION_PLAIN */
     int32_t block;        /* threads per workgroup of the first pass: 64, 128, 256,
@@ -170,7 +176,7 @@ typedef struct rsi_outputs {
     uint64_t *counters; /* optional [4]: [0] segments re-decided in binary64, [1] segments
                            that outgrew the LDS stack, [2] hitting segments whose answer
                            was not in the proposed bucket (proposal misses), [3] count-mode
-                           segments with more distinct hits than a lane keeps in registers
+                           segments with more hits than the first pass lists for them
                            (11 in CERTIFIED precision, 12 in PLAIN), finished by the second
                            pass.  Zeroed by the call before it counts.  [0] and [1] depend
                            on the order in which a wave's lanes reach their leaves, and the
@@ -309,9 +315,9 @@ typedef enum rsi_export_what {
 rsi_status rsi_mesh_export(rsi_mesh mesh, int32_t what, void *dst, int64_t dst_bytes, void *stream);
 
 /*
- * rsi_traversal_stats -- per-segment work of the same traversal rsi_intersect
- * runs with these arguments (an instrumented copy of the kernel; results are
- * not written).  node_visits[i] counts internal nodes fetched (4-wide nodes
+ * rsi_traversal_stats -- per-segment work of the traversal with a lane per
+ * segment (an instrumented copy of the kernel rsi_intersect runs for large
+ * calls with these arguments; results are not written).  node_visits[i] counts internal nodes fetched (4-wide nodes
  * when the first pass walks them, see node_width), leaf_tests[i]
  * triangles tested; both uint32 [n_rays] device arrays.  Segments finished by
  * the second (deep-stack) pass report the first pass's counts.
