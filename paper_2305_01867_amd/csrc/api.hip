@@ -294,7 +294,8 @@ rsi_status rsi_build(const float *vertices, int64_t n_vertices, const int32_t *t
     // node), for the builds whose tile list it is collapsed with
     const size_t sz_nodes4 = (algorithm != 1 && nt > 1) ? round_up(128 * (size_t)(nt - 1 + rsi::kTopSlots)) : 0;
     const size_t sz_par = round_up(4 * (size_t)(2 * nt - 1)), sz_cnt = round_up(4 * (size_t)(nt > 1 ? nt - 1 : 1));
-    const size_t sz_tris = round_up(48 * (size_t)nt), sz_small = 256;
+    const size_t sz_tris = round_up(48 * (size_t)nt);
+    const size_t sz_small = 256 + round_up(24 * (size_t)rsi::kBoundsParts);
     const size_t sz_tmp = round_up(rsi::sort_tmp_bytes(nt, bits));
     const size_t total =
         sz_V + sz_F + sz_keys + sz_ids + sz_nodes + sz_nodes4 + sz_par + sz_cnt + sz_tris + sz_small + sz_tmp;
@@ -326,6 +327,7 @@ rsi_status rsi_build(const float *vertices, int64_t n_vertices, const int32_t *t
     char *small = take(sz_small);
     d.bounds = reinterpret_cast<float *>(small);
     d.flags = reinterpret_cast<int32_t *>(small + 64);
+    d.partial = reinterpret_cast<float *>(small + 256);
     d.sort_tmp = take(sz_tmp);
     d.bytes = (int64_t)total;
 
@@ -820,7 +822,7 @@ rsi_status rsi_batch_create(int32_t n_meshes, const int64_t *vertex_offsets, con
     const size_t sz_tris = round_up(48 * (size_t)nt + 48), sz_small = 256;
     const size_t sz_tmp = round_up(rsi::sort_tmp_bytes(nt, 63));
     const size_t sz_off = round_up(8 * (size_t)(M + 1)) * 2 + round_up(4 * (size_t)(M + 1)) + round_up(4 * (size_t)M) * 2;
-    const size_t sz_tm = round_up(4 * (size_t)nt + 4), sz_mb = round_up(32 * (size_t)M);
+    const size_t sz_tm = round_up(4 * (size_t)nt + 4), sz_mb = 2 * round_up(32 * (size_t)M);
     const size_t sz_items = round_up(16 * (size_t)(b.n_items + 1)) + round_up(4 * (rsi::kItemGroups + 1));
     const size_t sz_q = round_up(4 * (size_t)b.n_rays + 4) + 256;
     const size_t sz_order = round_up(rsi::ray_sort_ws_bytes(b.n_rays));
@@ -867,6 +869,7 @@ rsi_status rsi_batch_create(int32_t n_meshes, const int64_t *vertex_offsets, con
     b.roots = reinterpret_cast<int32_t *>(take(round_up(4 * (size_t)M)));
     b.tri_mesh = reinterpret_cast<int32_t *>(take(sz_tm));
     b.mesh_bounds = reinterpret_cast<float *>(take(sz_mb));
+    b.key_bounds = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(b.mesh_bounds) + sz_mb / 2);
     b.items = reinterpret_cast<int4 *>(take(round_up(16 * (size_t)(b.n_items + 1))));
     b.group_start = reinterpret_cast<int32_t *>(take(round_up(4 * (rsi::kItemGroups + 1))));
     char *q = take(sz_q);
@@ -1060,7 +1063,7 @@ static rsi_status ensure_proposal(rsi_mesh mesh, hipStream_t s, uint64_t seed, b
         // the proposal order's 4-wide tree, where the mesh has one
         const bool wide = d.node_width == 4 && d.nt > 1;
         const size_t w4 = wide ? sizeof(rsi::Node4) * (size_t)(rsi::kTopSlots + d.nt - 1) : 0;
-        const size_t wsmall = wide ? round_up(4 * 256) + round_up(4 * rsi::kTopSlots) + 2 * rk : 0;
+        const size_t wsmall = wide ? round_up(4 * 256) + round_up(4 * rsi::kTopSlots) + rk : 0;
         hipError_t e = hipMallocAsync(&pr.block, 4 * f + wb + wbt + small + rk + lbk + w4 + wsmall, s);
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -1083,8 +1086,7 @@ static rsi_status ensure_proposal(rsi_mesh mesh, hipStream_t s, uint64_t seed, b
             pr.top4 = reinterpret_cast<rsi::Node4 *>(p); p += w4;
             pr.bucket_ref4 = reinterpret_cast<int32_t *>(p); p += round_up(4 * 256);
             pr.slot_bin = reinterpret_cast<int32_t *>(p); p += round_up(4 * rsi::kTopSlots);
-            pr.wide_flag = reinterpret_cast<int32_t *>(p); p += rk;
-            pr.wide_queue = reinterpret_cast<int32_t *>(p);
+            pr.wide_flag = reinterpret_cast<int32_t *>(p);
         }
         e = rsi::proposal_frontier(d, pr, s);
         if (e == hipSuccess && wide)

@@ -25,13 +25,27 @@ __device__ __forceinline__ int mesh_of(const int64_t *__restrict__ off, int M, i
     return lo;
 }
 
-// Copy the vertices, turn per-mesh vertex indices into global ones, and note
+// Clear what the later kernels add to, copy the vertices, turn per-mesh vertex indices into global ones, and note
 // each triangle's mesh.  A triangle with an index outside its mesh gets -1 in
 // all three slots: it is never hit and widens no box.
 __global__ void k_batch_prepare(const float *__restrict__ Vin, int64_t nv, const int32_t *__restrict__ Fin,
                                 int64_t nt, const int64_t *__restrict__ v_off, const int64_t *__restrict__ t_off,
                                 int M, float *__restrict__ V, int32_t *__restrict__ F,
-                                int32_t *__restrict__ tri_mesh) {
+                                int32_t *__restrict__ tri_mesh, uint32_t *__restrict__ key_bounds,
+                                int32_t *__restrict__ roots, int32_t *__restrict__ flags) {
+    if (blockIdx.x == 0) {
+        // the per-mesh minima start at the largest key, the maxima at the smallest
+        if ((int)threadIdx.x < M) {
+            const int m = threadIdx.x;
+            roots[m] = INT32_MIN;
+            for (int a = 0; a < 3; ++a) {
+                key_bounds[8 * m + a] = 0xffffffffu;
+                key_bounds[8 * m + 3 + a] = 0u;
+            }
+        }
+        if (threadIdx.x < 4)
+            flags[threadIdx.x] = 0;
+    }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 3 * nv; i += stride)
         V[i] = Vin[i];
@@ -59,27 +73,6 @@ __global__ void k_batch_prepare(const float *__restrict__ Vin, int64_t nv, const
 // coordinates are skipped, as fminf / fmaxf skip them.
 constexpr int kBoundSlices = 16;
 constexpr int kBoundStep = 768;  // floats per workgroup step: 256 threads x 3 loads
-
-__device__ __forceinline__ uint32_t order_key(float f) {
-    const uint32_t u = __float_as_uint(f);
-    return (u >> 31) ? ~u : (u | 0x80000000u);
-}
-
-__device__ __forceinline__ float order_value(uint32_t k) {
-    return __uint_as_float((k >> 31) ? (k & 0x7fffffffu) : ~k);
-}
-
-// keys of the per-mesh minima at their identity (all ones), of the maxima at 0
-__global__ void k_batch_init(uint32_t *__restrict__ key_bounds, int32_t *__restrict__ roots, int M) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m < M) {
-        roots[m] = INT32_MIN;
-        for (int a = 0; a < 3; ++a) {
-            key_bounds[8 * m + a] = 0xffffffffu;
-            key_bounds[8 * m + 3 + a] = 0u;
-        }
-    }
-}
 
 __global__ __launch_bounds__(256) void k_batch_bounds(const float *__restrict__ V, const int64_t *__restrict__ v_off,
                                                       uint32_t *__restrict__ key_bounds) {
@@ -136,58 +129,6 @@ __global__ __launch_bounds__(256) void k_batch_bounds(const float *__restrict__ 
     }
 }
 
-// The union box and the largest coordinate magnitude of all meshes (the
-// traversal widens boxes relative to it).
-__global__ void k_batch_global(float *__restrict__ mesh_bounds, int M, float *__restrict__ bounds) {
-    if (threadIdx.x != 0)
-        return;
-    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY}, scale = 0.0f;
-    uint32_t *key_bounds = reinterpret_cast<uint32_t *>(mesh_bounds);
-    for (int m = 0; m < M; ++m) {
-        float ms = 0.0f;  // an empty mesh (lo = +inf, hi = -inf) adds no scale
-        for (int a = 0; a < 3; ++a) {
-            const float l = order_value(key_bounds[8 * m + a]), h = order_value(key_bounds[8 * m + 3 + a]);
-            mesh_bounds[8 * m + a] = l;
-            mesh_bounds[8 * m + 3 + a] = h;
-            if (l <= h)
-                ms = fmaxf(ms, fmaxf(fabsf(l), fabsf(h)));
-            lo[a] = fminf(lo[a], l);
-            hi[a] = fmaxf(hi[a], h);
-        }
-        mesh_bounds[8 * m + 6] = ms;
-        mesh_bounds[8 * m + 7] = 0.0f;
-        scale = fmaxf(scale, ms);
-    }
-    for (int a = 0; a < 3; ++a) {
-        bounds[a] = lo[a];
-        bounds[3 + a] = hi[a];
-    }
-    bounds[6] = scale;
-    bounds[7] = 0.0f;
-}
-
-// The subtree root of each mesh: the internal node whose key range is exactly
-// the mesh's keys, or the leaf of a one-triangle mesh.
-__global__ void k_mesh_roots(const Node *__restrict__ nodes, const uint64_t *__restrict__ keys, int64_t nt,
-                             int32_t *__restrict__ roots) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nt)
-        return;
-    auto mesh = [&](int64_t k) { return (int)(keys[k] >> kBatchMortonBits); };
-    int64_t lo = i, hi = i;
-    if (i < nt - 1) {
-        lo = nodes[i].refs.z;
-        hi = nodes[i].refs.w;
-        const int m = mesh(lo);
-        if (mesh(hi) == m && (lo == 0 || mesh(lo - 1) != m) && (hi == nt - 1 || mesh(hi + 1) != m))
-            roots[m] = (int32_t)i;
-    }
-    // leaf i alone
-    const int m = mesh(i);
-    if ((i == 0 || mesh(i - 1) != m) && (i == nt - 1 || mesh(i + 1) != m))
-        roots[m] = ~(int32_t)i;
-}
-
 inline int blocks(int64_t n, int t) { return (int)((n + t - 1) / t); }
 
 }  // namespace
@@ -195,20 +136,12 @@ inline int blocks(int64_t n, int t) { return (int)((n + t - 1) / t); }
 hipError_t launch_batch_build(MeshDev &m, BatchDev &b, const float *V, const int32_t *F, hipStream_t s) {
     const int64_t work = 3 * m.nv > m.nt ? 3 * m.nv : m.nt;
     const int grid = work > 0 ? (blocks(work, 256) < 4096 ? blocks(work, 256) : 4096) : 1;
-    k_batch_prepare<<<grid, 256, 0, s>>>(V, m.nv, F, m.nt, b.v_off, b.t_off, b.M, m.V, m.F, b.tri_mesh);
-    uint32_t *key_bounds = reinterpret_cast<uint32_t *>(b.mesh_bounds);
-    k_batch_init<<<1, 64, 0, s>>>(key_bounds, b.roots, b.M);
-    k_batch_bounds<<<b.M * kBoundSlices, 256, 0, s>>>(m.V, b.v_off, key_bounds);
-    k_batch_global<<<1, 64, 0, s>>>(b.mesh_bounds, b.M, m.bounds);
+    k_batch_prepare<<<grid, 256, 0, s>>>(V, m.nv, F, m.nt, b.v_off, b.t_off, b.M, m.V, m.F, b.tri_mesh, b.key_bounds,
+                                         b.roots, m.flags);
     if (m.nt == 0)
         return hipGetLastError();
-    hipError_t e = launch_morton_batch(m, b.tri_mesh, b.mesh_bounds, s);
-    if (e == hipSuccess)
-        e = build_from_keys64(m, kBatchMortonBits + 6, s);  // five 8-bit sort passes
-    if (e != hipSuccess)
-        return e;
-    k_mesh_roots<<<blocks(m.nt, 256), 256, 0, s>>>(m.nodes, static_cast<const uint64_t *>(m.keys), m.nt, b.roots);
-    e = hipGetLastError();
+    k_batch_bounds<<<b.M * kBoundSlices, 256, 0, s>>>(m.V, b.v_off, b.key_bounds);
+    const hipError_t e = launch_build_batch(m, b, s);
     return e == hipSuccess ? launch_collapse_batch(m, b, s) : e;
 }
 

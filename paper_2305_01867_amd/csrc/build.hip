@@ -4,8 +4,8 @@
 // Karras 2012; Specific changes -- Morton kernel, 64-bit codes; Case Studies
 // 1-2 -- sorted int32 triangle ids, bottom-up node filling with one atomic
 // counter per internal node, N_t - 1 internal nodes, a launch sized by N_t):
-//   1. mesh extent            one workgroup, min / max over all vertices
-//   2. Morton keys            one lane per triangle
+//   1. mesh extent            min / max over all vertices
+//   2. Morton keys            one lane per triangle, first digit counted
 //   3. LDS radix sort         stable LSD, 8-bit digits: tile histograms,
 //                             one device-wide scan, stable tile scatter
 //   4. radix tree             one lane per internal node (Karras section 3)
@@ -17,23 +17,24 @@
 namespace rsi {
 namespace {
 
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 8;
+constexpr int kSortThreads = 1024;
+constexpr int kSortItems = 2;
 constexpr int kSortTile = kSortThreads * kSortItems;  // 2048 keys per tile
+constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kRadix = 256;
 // Up to this many tiles (131,072 keys) a pass is one launch: every scatter
 // workgroup derives its own offsets from the whole (small) histogram and adds
 // its keys to the next pass's histogram as it places them.
 constexpr int kSmallSortTiles = 64;
-constexpr int kBoxTile = 1024;  // leaves per bottom-up workgroup (one per lane)
+constexpr int kBoxTile = kTileLeaves;  // leaves per bottom-up workgroup (one per lane)
 constexpr int kNoTile = INT32_MIN;  // never a child reference (leaves are ~k with k < 2^30)
 constexpr int kRestructureRounds = 2;  // treelet restructuring passes of algorithm 2
 
 // ---------------------------------------------------------------- 1. extent
 // Min / max are exact in any order, so the extent is reduced in two steps:
-// up to kBoundsParts workgroups each reduce a strided share of the vertices,
-// then one workgroup combines their partial boxes and the coordinate scale.
-constexpr int kBoundsParts = 256;
+// up to kBoundsParts workgroups each reduce a strided share of the vertices;
+// every workgroup of the Morton kernel combines their partial boxes (6 KB from
+// L2), which costs less than a launch of its own (about 4.6 us).
 
 // Block-wide min / max of six values (lo xyz, hi xyz); the result is valid in
 // thread 0.
@@ -61,13 +62,42 @@ __device__ __forceinline__ void block_minmax(float lo[3], float hi[3]) {
     }
 }
 
+// The same over the first WAVES waves, valid in every thread.
+template <int WAVES>
+__device__ __forceinline__ void block_minmax_all(float lo[3], float hi[3]) {
+    __shared__ float red[WAVES][6];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (w < WAVES) {
+        for (int off = 32; off > 0; off >>= 1)
+            for (int a = 0; a < 3; ++a) {
+                lo[a] = fminf(lo[a], __shfl_xor(lo[a], off));
+                hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], off));
+            }
+        if (lane == 0)
+            for (int a = 0; a < 3; ++a) {
+                red[w][a] = lo[a];
+                red[w][3 + a] = hi[a];
+            }
+    }
+    __syncthreads();
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = red[0][a];
+        hi[a] = red[0][3 + a];
+#pragma unroll
+        for (int k = 1; k < WAVES; ++k) {
+            lo[a] = fminf(lo[a], red[k][a]);
+            hi[a] = fmaxf(hi[a], red[k][3 + a]);
+        }
+    }
+}
+
 // (also copies the caller's vertices into the mesh's own array, and clears
 // the build flags)
 __global__ __launch_bounds__(1024) void k_mesh_bounds_part(const float *__restrict__ V, int64_t nv,
                                                            float *__restrict__ partial, float *__restrict__ V_copy,
                                                            int32_t *__restrict__ flags) {
     if (blockIdx.x == 0 && threadIdx.x < 4)
-        flags[threadIdx.x] = 0;
+        flags[threadIdx.x] = 0;  // (flags[2]: the number of tiles the radix-tree kernel lists)
     float lo[3] = {INFINITY, INFINITY, INFINITY};
     float hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += (int64_t)gridDim.x * blockDim.x)
@@ -83,29 +113,6 @@ __global__ __launch_bounds__(1024) void k_mesh_bounds_part(const float *__restri
             partial[6 * blockIdx.x + a] = lo[a];
             partial[6 * blockIdx.x + 3 + a] = hi[a];
         }
-}
-
-__global__ __launch_bounds__(kBoundsParts) void k_mesh_bounds_final(const float *__restrict__ partial, int parts,
-                                                                    float *__restrict__ bounds) {
-    float lo[3] = {INFINITY, INFINITY, INFINITY};
-    float hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    if ((int)threadIdx.x < parts)
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = partial[6 * threadIdx.x + a];
-            hi[a] = partial[6 * threadIdx.x + 3 + a];
-        }
-    block_minmax(lo, hi);
-    if (threadIdx.x == 0) {
-        float scale = 0.0f;
-        for (int a = 0; a < 3; ++a) {
-            bounds[a] = lo[a];
-            bounds[3 + a] = hi[a];
-            if (lo[a] <= hi[a])  // no vertices: no scale
-                scale = fmaxf(scale, fmaxf(fabsf(lo[a]), fabsf(hi[a])));
-        }
-        bounds[6] = scale;
-        bounds[7] = 0.0f;
-    }
 }
 
 // ---------------------------------------------------------- 2. Morton keys
@@ -138,67 +145,154 @@ __device__ __forceinline__ uint32_t quantise(float c, float lo, float ext, float
     return x > 0.0f ? (uint32_t)floorf(fminf(x, top)) : 0u;
 }
 
-// (also copies the caller's triangles into the mesh's own array)
+// The digit counts of one sort tile in LDS: a lane per digit clears h before
+// and writes it after (a workgroup of kSortThreads lanes).
+__device__ __forceinline__ void put_hist(const uint32_t *h, int tile, int ntiles, uint32_t *__restrict__ hist,
+                                         uint32_t *__restrict__ clear) {
+    if (threadIdx.x < kRadix) {
+        hist[(int64_t)threadIdx.x * ntiles + tile] = h[threadIdx.x];
+        if (clear)  // one-launch passes: the histogram the first pass adds to
+            clear[(int64_t)threadIdx.x * ntiles + tile] = 0u;
+    }
+}
+
+// One workgroup per sort tile: the mesh extent from its partial boxes, the
+// keys, and the counts of their lowest digit for the sort's first pass.
+// (Also copies the caller's triangles into the mesh's own array.)
 template <typename K>
-__global__ __launch_bounds__(256) void k_morton(const float *__restrict__ V, int64_t nv,
-                                                const int32_t *__restrict__ F, int64_t nt,
-                                                const float *__restrict__ bounds, K *__restrict__ keys,
-                                                int32_t *__restrict__ ids, int32_t *__restrict__ flags,
-                                                int32_t *__restrict__ F_copy) {
+__global__ __launch_bounds__(kSortThreads) void k_morton(const float *__restrict__ V, int64_t nv,
+                                                         const int32_t *__restrict__ F, int64_t nt,
+                                                         const float *__restrict__ partial, int parts,
+                                                         float *__restrict__ bounds, K *__restrict__ keys,
+                                                         int32_t *__restrict__ ids, int32_t *__restrict__ flags,
+                                                         int32_t *__restrict__ F_copy, int ntiles,
+                                                         uint32_t *__restrict__ hist, uint32_t *__restrict__ clear) {
 #pragma clang fp contract(off)
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nt)
-        return;
+    __shared__ uint32_t h[kRadix];
+    const int tid = threadIdx.x;
+    if (tid < kRadix)
+        h[tid] = 0;
+    float lo[3] = {INFINITY, INFINITY, INFINITY};
+    float hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    if (tid < parts)
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = partial[6 * tid + a];
+            hi[a] = partial[6 * tid + 3 + a];
+        }
+    block_minmax_all<kBoundsParts / 64>(lo, hi);  // (also orders the clearing of h)
+    if (blockIdx.x == 0 && tid == 0) {
+        float scale = 0.0f;
+        for (int a = 0; a < 3; ++a) {
+            bounds[a] = lo[a];
+            bounds[3 + a] = hi[a];
+            if (lo[a] <= hi[a])  // no vertices: no scale
+                scale = fmaxf(scale, fmaxf(fabsf(lo[a]), fabsf(hi[a])));
+        }
+        bounds[6] = scale;
+        bounds[7] = 0.0f;
+    }
     constexpr int b = sizeof(K) == 4 ? 10 : 21;
-    const int32_t i0 = F[3 * t], i1 = F[3 * t + 1], i2 = F[3 * t + 2];
-    F_copy[3 * t] = i0;
-    F_copy[3 * t + 1] = i1;
-    F_copy[3 * t + 2] = i2;
-    ids[t] = (int32_t)t;
-    if (i0 < 0 || i1 < 0 || i2 < 0 || i0 >= nv || i1 >= nv || i2 >= nv) {
-        atomicOr(flags, 1);
-        keys[t] = (K)0;
-        return;
-    }
-    float c[3];
-    for (int a = 0; a < 3; ++a)
-        c[a] = ((V[3 * (int64_t)i0 + a] + V[3 * (int64_t)i1 + a]) + V[3 * (int64_t)i2 + a]) / 3.0f;
     const float two_b = (float)(1u << b), top = (float)((1u << b) - 1u);
-    K key = 0;
-    for (int a = 2; a >= 0; --a) {  // z, then y, then x: z lands on the top bit of each triple
-        const float lo = bounds[a], ext = bounds[3 + a] - bounds[a];
-        key = (K)(key << 1) | spread3((K)quantise(c[a], lo, ext, two_b, top));
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+        const int64_t t = (int64_t)blockIdx.x * kSortTile + r * kSortThreads + tid;
+        if (t >= nt)
+            break;
+        const int32_t i0 = F[3 * t], i1 = F[3 * t + 1], i2 = F[3 * t + 2];
+        F_copy[3 * t] = i0;
+        F_copy[3 * t + 1] = i1;
+        F_copy[3 * t + 2] = i2;
+        ids[t] = (int32_t)t;
+        K key = 0;
+        if (i0 < 0 || i1 < 0 || i2 < 0 || i0 >= nv || i1 >= nv || i2 >= nv) {
+            atomicOr(flags, 1);
+        } else {
+            float c[3];
+            for (int a = 0; a < 3; ++a)
+                c[a] = ((V[3 * (int64_t)i0 + a] + V[3 * (int64_t)i1 + a]) + V[3 * (int64_t)i2 + a]) / 3.0f;
+            for (int a = 2; a >= 0; --a)  // z, then y, then x: z lands on the top bit of each triple
+                key = (K)(key << 1) | spread3((K)quantise(c[a], lo[a], hi[a] - lo[a], two_b, top));
+        }
+        keys[t] = key;
+        atomicAdd(&h[(uint32_t)key & 0xffu], 1u);
     }
-    keys[t] = key;
+    __syncthreads();
+    put_hist(h, blockIdx.x, ntiles, hist, clear);
 }
 
 // Batched form: the key of a triangle of mesh m is m (6 bits) above a 30-bit
 // Morton code (10 bits per axis) of its centroid normalised to mesh m's box,
 // so each mesh's triangles are contiguous after the sort and form one subtree.
-__global__ __launch_bounds__(256) void k_morton_batch(const float *__restrict__ V, const int32_t *__restrict__ F,
-                                                      const int32_t *__restrict__ tri_mesh, int64_t nt,
-                                                      const float *__restrict__ mesh_bounds,
-                                                      uint64_t *__restrict__ keys, int32_t *__restrict__ ids) {
+// One workgroup per sort tile, as k_morton.  The meshes' extents come as
+// order-preserving integers; the first workgroup also writes them as floats,
+// with their union and the largest coordinate magnitude (the traversal widens
+// boxes relative to it).
+__global__ __launch_bounds__(kSortThreads) void k_morton_batch(
+    const float *__restrict__ V, const int32_t *__restrict__ F, const int32_t *__restrict__ tri_mesh, int64_t nt,
+    const uint32_t *__restrict__ key_bounds, int M, float *__restrict__ mesh_bounds, float *__restrict__ bounds,
+    uint64_t *__restrict__ keys, int32_t *__restrict__ ids, int ntiles, uint32_t *__restrict__ hist,
+    uint32_t *__restrict__ clear) {
 #pragma clang fp contract(off)
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nt)
-        return;
-    ids[t] = (int32_t)t;
-    const int m = tri_mesh[t];
-    const int32_t i0 = F[3 * t], i1 = F[3 * t + 1], i2 = F[3 * t + 2];
-    if (i0 < 0 || i1 < 0 || i2 < 0) {  // marked invalid while copying
-        keys[t] = (uint64_t)m << kBatchMortonBits;
-        return;
+    __shared__ uint32_t h[kRadix];
+    __shared__ float bb[64][6];
+    const int tid = threadIdx.x;
+    if (tid < kRadix)
+        h[tid] = 0;
+    for (int k = tid; k < 6 * M; k += kSortThreads)
+        bb[k / 6][k % 6] = order_value(key_bounds[8 * (k / 6) + k % 6]);
+    __syncthreads();
+    if (blockIdx.x == 0 && tid < 64) {
+        float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY}, scale = 0.0f;
+        if (tid < M) {
+            for (int a = 0; a < 3; ++a) {
+                lo[a] = bb[tid][a];
+                hi[a] = bb[tid][3 + a];
+                mesh_bounds[8 * tid + a] = lo[a];
+                mesh_bounds[8 * tid + 3 + a] = hi[a];
+                if (lo[a] <= hi[a])  // an empty mesh (lo = +inf, hi = -inf) adds no scale
+                    scale = fmaxf(scale, fmaxf(fabsf(lo[a]), fabsf(hi[a])));
+            }
+            mesh_bounds[8 * tid + 6] = scale;
+            mesh_bounds[8 * tid + 7] = 0.0f;
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            for (int a = 0; a < 3; ++a) {
+                lo[a] = fminf(lo[a], __shfl_xor(lo[a], off));
+                hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], off));
+            }
+            scale = fmaxf(scale, __shfl_xor(scale, off));
+        }
+        if (tid == 0) {
+            for (int a = 0; a < 3; ++a) {
+                bounds[a] = lo[a];
+                bounds[3 + a] = hi[a];
+            }
+            bounds[6] = scale;
+            bounds[7] = 0.0f;
+        }
     }
-    const float *bb = mesh_bounds + 8 * m;
     // 10 bits per axis of the mesh's own box, as the single-mesh 30-bit codes
     const float two_b = (float)(1u << 10), top = (float)((1u << 10) - 1u);
-    uint64_t key = 0;
-    for (int a = 2; a >= 0; --a) {
-        const float c = ((V[3 * (int64_t)i0 + a] + V[3 * (int64_t)i1 + a]) + V[3 * (int64_t)i2 + a]) / 3.0f;
-        key = (key << 1) | spread3((uint64_t)quantise(c, bb[a], bb[3 + a] - bb[a], two_b, top));
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+        const int64_t t = (int64_t)blockIdx.x * kSortTile + r * kSortThreads + tid;
+        if (t >= nt)
+            break;
+        ids[t] = (int32_t)t;
+        const int m = tri_mesh[t];
+        const int32_t i0 = F[3 * t], i1 = F[3 * t + 1], i2 = F[3 * t + 2];
+        uint64_t key = 0;
+        if (i0 >= 0 && i1 >= 0 && i2 >= 0)  // (-1: marked invalid while copying)
+            for (int a = 2; a >= 0; --a) {
+                const float c =
+                    ((V[3 * (int64_t)i0 + a] + V[3 * (int64_t)i1 + a]) + V[3 * (int64_t)i2 + a]) / 3.0f;
+                key = (key << 1) | spread3((uint64_t)quantise(c, bb[m][a], bb[m][3 + a] - bb[m][a], two_b, top));
+            }
+        keys[t] = ((uint64_t)m << kBatchMortonBits) | key;
+        atomicAdd(&h[(uint32_t)key & 0xffu], 1u);
     }
-    keys[t] = ((uint64_t)m << kBatchMortonBits) | key;
+    __syncthreads();
+    put_hist(h, blockIdx.x, ntiles, hist, clear);
 }
 
 // ---------------------------------------------------------- 3. radix sort
@@ -208,9 +302,8 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const K *__restrict_
                                                             uint32_t *__restrict__ clear) {
     __shared__ uint32_t h[kRadix];
     const int tid = threadIdx.x, tile = blockIdx.x;
-    h[tid] = 0;
-    if (clear)  // one-launch passes: the histogram the first pass adds to
-        clear[(int64_t)tid * ntiles + tile] = 0u;
+    if (tid < kRadix)
+        h[tid] = 0;
     __syncthreads();
     const int64_t base = (int64_t)tile * kSortTile;
 #pragma unroll
@@ -220,7 +313,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const K *__restrict_
             atomicAdd(&h[(uint32_t)(keys[idx] >> shift) & 0xffu], 1u);
     }
     __syncthreads();
-    hist[(int64_t)tid * ntiles + tile] = h[tid];
+    put_hist(h, tile, ntiles, hist, clear);
 }
 
 // Exclusive scan of hist[0..len) in place, one workgroup of 1024 lanes.
@@ -338,33 +431,41 @@ void scan_hist(uint32_t *hist, int64_t len, uint32_t *partial, hipStream_t s) {
     k_scan_apply<<<g, 1024, 0, s>>>(hist, len, seg, partial);
 }
 
-// Stable scatter of one tile.  Its keys are loaded at once (eight per
-// lane), then ranked in rounds of 256 consecutive keys: inside a wave by
-// matching the 8 digit bits with ballots, across the four waves and earlier
-// rounds through per-digit LDS counts.  base[d] is where the tile's keys of
-// digit d start; run and wcnt start at zero.  With hist_next, each placed
-// key's next digit is counted at the tile its new position falls in.
+// Stable scatter of one tile of 2048 keys by a workgroup of 16 waves, two
+// keys a lane.  A key's rank inside its wave's 64 consecutive keys comes from
+// matching the 8 digit bits with ballots; the counts of all 32 groups of 64
+// are scanned per digit in one step (four lanes a digit), so the tile takes
+// three barriers.  (Eight keys a lane of four waves, ranked in eight rounds of
+// three barriers each, took 11.5 us a pass at 32,258 keys and 22 us at 11,000
+// 64-bit ones, against 8.1 and 7.9.)  base[d] is where the tile's keys of
+// digit d start.  With hist_next, each placed key's next digit is counted at
+// the tile its new position falls in.
 template <typename K>
 __device__ __forceinline__ void scatter_tile(const K *__restrict__ kin, const int32_t *__restrict__ iin,
                                              K *__restrict__ kout, int32_t *__restrict__ iout, int64_t n,
-                                             int shift, int tile, uint32_t *run, const uint32_t *base,
-                                             uint32_t (*wcnt)[kRadix], uint32_t *__restrict__ hist_next,
+                                             int shift, int tile, const uint32_t *base,
+                                             uint32_t (*cnt)[kRadix], uint32_t *__restrict__ hist_next,
                                              int ntiles) {
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int tid = threadIdx.x, wave = tid >> 6;
     const int64_t t0 = (int64_t)tile * kSortTile;
     K key[kSortItems];
     int32_t id[kSortItems];
+    uint32_t rank[kSortItems];
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
         const int64_t idx = t0 + r * kSortThreads + tid;
         key[r] = idx < n ? kin[idx] : K(0);
         id[r] = idx < n ? iin[idx] : 0;
     }
+    uint32_t *flat = &cnt[0][0];
+#pragma unroll
+    for (int k = 0; k < kSortItems * kSortWaves * kRadix / kSortThreads; ++k)
+        flat[k * kSortThreads + tid] = 0u;
+    __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
         const bool valid = t0 + r * kSortThreads + tid < n;
-        const uint32_t digit = valid ? (uint32_t)(key[r] >> shift) & 0xffu : 0u;
+        const uint32_t digit = (uint32_t)(key[r] >> shift) & 0xffu;
         uint64_t peers = __ballot(valid);
 #pragma unroll
         for (int bit = 0; bit < 8; ++bit) {
@@ -372,30 +473,72 @@ __device__ __forceinline__ void scatter_tile(const K *__restrict__ kin, const in
             const uint64_t m = __ballot(set);
             peers &= set ? m : ~m;
         }
-        const uint32_t rank = __popcll(peers & lt_mask);
-        if (valid && rank == 0)
-            wcnt[wave][digit] = __popcll(peers);
-        __syncthreads();
-        if (valid) {
-            uint32_t pos = base[digit] + run[digit] + rank;
-            for (int w = 0; w < wave; ++w)
-                pos += wcnt[w][digit];
-            kout[pos] = key[r];
-            iout[pos] = id[r];
-            if (hist_next)
-                atomicAdd(hist_next + (int64_t)((uint32_t)(key[r] >> (shift + 8)) & 0xffu) * ntiles + pos / kSortTile,
-                          1u);
+        rank[r] = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+        if (valid && rank[r] == 0)
+            cnt[r * kSortWaves + wave][digit] = __popcll(peers);
+    }
+    __syncthreads();
+    {
+        // four lanes a digit, eight groups of 64 each: where each group's keys
+        // of the digit start
+        constexpr int kGroups = kSortItems * kSortWaves / 4;
+        const int d = tid >> 2, q = tid & 3;
+        uint32_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < kGroups; ++k)
+            sum += cnt[q * kGroups + k][d];
+        uint32_t before = 0;  // the sums of the lower lanes of the four
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+            const uint32_t o = __shfl(sum, (threadIdx.x & 63 & ~3) | ((q - k) & 3));
+            before += q >= k ? o : 0u;
         }
-        __syncthreads();
-        uint32_t add = 0;
-        for (int w = 0; w < kSortThreads / 64; ++w) {
-            add += wcnt[w][tid];
-            wcnt[w][tid] = 0;
+        before += base[d];
+#pragma unroll
+        for (int k = 0; k < kGroups; ++k) {
+            const uint32_t c = cnt[q * kGroups + k][d];
+            cnt[q * kGroups + k][d] = before;
+            before += c;
         }
-        run[tid] += add;
-        __syncthreads();
+    }
+    __syncthreads();
+    uint32_t pos[kSortItems];
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+        const uint32_t digit = (uint32_t)(key[r] >> shift) & 0xffu;
+        pos[r] = cnt[r * kSortWaves + wave][digit] + rank[r];
+        if (t0 + r * kSortThreads + tid < n) {
+            kout[pos[r]] = key[r];
+            iout[pos[r]] = id[r];
+        }
+    }
+    if (!hist_next)
+        return;
+    // the tile's next digits by destination tile, counted in the LDS that held
+    // the groups' counts (two 16-bit counts a word), then added to the next
+    // pass's histogram: a global atomic per key took most of a pass where few
+    // digits occur (22 us for 11,000 keys)
+    const int words = kRadix * ntiles / 2;
+    __syncthreads();
+    for (int k = tid; k < words; k += kSortThreads)
+        flat[k] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r)
+        if (t0 + r * kSortThreads + tid < n) {
+            const uint32_t at = ((uint32_t)(key[r] >> (shift + 8)) & 0xffu) * ntiles + pos[r] / kSortTile;
+            atomicAdd(flat + (at >> 1), 1u << (16 * (at & 1)));
+        }
+    __syncthreads();
+    for (int k = tid; k < words; k += kSortThreads) {
+        const uint32_t c = flat[k];
+        if (c & 0xffffu)
+            atomicAdd(hist_next + 2 * k, c & 0xffffu);
+        if (c >> 16)
+            atomicAdd(hist_next + 2 * k + 1, c >> 16);
     }
 }
+static_assert(kRadix * kSmallSortTiles / 2 <= kSortItems * kSortWaves * kRadix, "the counts fit");
 
 // One scatter pass over tile histograms scanned per digit (offs: digit-major,
 // exclusive within each digit's row; totals: each digit's count).
@@ -406,27 +549,23 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const K *__restri
                                                                int64_t n, int shift, int ntiles,
                                                                const uint32_t *__restrict__ offs,
                                                                const uint32_t *__restrict__ totals) {
-    __shared__ uint32_t run[kRadix];
     __shared__ uint32_t base[kRadix];
-    __shared__ uint32_t wcnt[kSortThreads / 64][kRadix];
-    __shared__ uint32_t wsum[kSortThreads / 64];
+    __shared__ uint32_t cnt[kSortItems * kSortWaves][kRadix];
+    __shared__ uint32_t wsum[kSortWaves];
     const int tid = threadIdx.x, tile = blockIdx.x;
     uint32_t all;
-    const uint32_t below = block_excl_scan(totals[tid], wsum, all);  // keys of the digits below
-    run[tid] = 0;
-    base[tid] = below + offs[(int64_t)tid * ntiles + tile];
-    for (int w = 0; w < kSortThreads / 64; ++w)
-        wcnt[w][tid] = 0;
-    __syncthreads();
-    scatter_tile<K>(kin, iin, kout, iout, n, shift, tile, run, base, wcnt, nullptr, ntiles);
+    const uint32_t below = block_excl_scan(tid < kRadix ? totals[tid] : 0u, wsum, all);  // keys of the digits below
+    if (tid < kRadix)
+        base[tid] = below + offs[(int64_t)tid * ntiles + tile];
+    scatter_tile<K>(kin, iin, kout, iout, n, shift, tile, base, cnt, nullptr, ntiles);
 }
 
 // One pass of a small sort in one launch.  hist holds this pass's per-tile
 // digit counts (digit-major); each workgroup sums them into its own offsets
-// (digits below, then earlier tiles of its digit) and scatters its tile,
-// counting the next digit into hist_next (null after the last pass).
-// hist_clear (the histogram two passes on) is zeroed here: nothing reads or
-// adds to it during this pass.
+// (digits below, then earlier tiles of its digit; four lanes a digit) and
+// scatters its tile, counting the next digit into hist_next (null after the
+// last pass).  hist_clear (the histogram two passes on) is zeroed here: nothing
+// reads or adds to it during this pass.
 template <typename K>
 __global__ __launch_bounds__(kSortThreads) void k_sort_pass_small(const K *__restrict__ kin,
                                                                   const int32_t *__restrict__ iin,
@@ -435,26 +574,35 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass_small(const K *__res
                                                                   const uint32_t *__restrict__ hist,
                                                                   uint32_t *__restrict__ hist_next,
                                                                   uint32_t *__restrict__ hist_clear) {
-    __shared__ uint32_t run[kRadix];
     __shared__ uint32_t base[kRadix];
-    __shared__ uint32_t wcnt[kSortThreads / 64][kRadix];
-    __shared__ uint32_t wsum[kSortThreads / 64];
+    __shared__ uint32_t total[kRadix];
+    __shared__ uint32_t cnt[kSortItems * kSortWaves][kRadix];
+    __shared__ uint32_t wsum[kSortWaves];
     const int tid = threadIdx.x, tile = blockIdx.x;
-    uint32_t earlier = 0, total = 0;
-    const uint32_t *h = hist + (int64_t)tid * ntiles;
-    for (int t = 0; t < ntiles; ++t) {
+    uint32_t earlier = 0, sum = 0;
+    const uint32_t *h = hist + (int64_t)(tid >> 2) * ntiles;
+    for (int t = tid & 3; t < ntiles; t += 4) {
         const uint32_t v = h[t];
         earlier += t < tile ? v : 0u;
-        total += v;
+        sum += v;
     }
-    uint32_t all;
-    base[tid] = block_excl_scan(total, wsum, all) + earlier;
-    hist_clear[(int64_t)tid * ntiles + tile] = 0u;
-    run[tid] = 0;
-    for (int w = 0; w < kSortThreads / 64; ++w)
-        wcnt[w][tid] = 0;
+#pragma unroll
+    for (int off = 1; off < 4; off <<= 1) {
+        earlier += __shfl_xor(earlier, off);
+        sum += __shfl_xor(sum, off);
+    }
+    if ((tid & 3) == 0) {
+        base[tid >> 2] = earlier;
+        total[tid >> 2] = sum;
+    }
     __syncthreads();
-    scatter_tile<K>(kin, iin, kout, iout, n, shift, tile, run, base, wcnt, hist_next, ntiles);
+    uint32_t all;
+    const uint32_t below = block_excl_scan(tid < kRadix ? total[tid] : 0u, wsum, all);
+    if (tid < kRadix) {
+        base[tid] += below;
+        hist_clear[(int64_t)tid * ntiles + tile] = 0u;
+    }
+    scatter_tile<K>(kin, iin, kout, iout, n, shift, tile, base, cnt, hist_next, ntiles);
 }
 
 // ---------------------------------------------------------- 4. radix tree
@@ -475,17 +623,28 @@ __device__ __forceinline__ int prefix(const K *__restrict__ k, int n, int i, K k
 
 // Also lists the bottom-up tiles: the largest subtrees with at most kBoxTile
 // leaves (children of larger nodes, or the root itself), wave-aggregated into
-// tiles[0 .. *n_tiles); and flags each internal node of at most kBoxTile
-// leaves with kTileRootFlag (the 4-wide collapse above the tiles stops at the
-// first flagged nodes from the root, which are the tiles).
+// tiles[0 .. *n_tiles).  In the batched form (roots not NULL) it also finds
+// each mesh's subtree root and flags it for the 4-wide collapse.
 template <typename K>
 __global__ __launch_bounds__(256) void k_radix_tree(const K *__restrict__ keys, int n, Node *__restrict__ nodes,
                                                     int32_t *__restrict__ parent, int32_t *__restrict__ counters,
                                                     int32_t *__restrict__ tiles, int32_t *__restrict__ n_tiles,
-                                                    int32_t *__restrict__ tile_flag) {
+                                                    int32_t *__restrict__ flag, int32_t *__restrict__ roots) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n - 1)
         return;
+    // the root of a mesh of one triangle is its leaf
+    auto mesh = [&](int k) { return (int)((uint64_t)keys[k] >> kBatchMortonBits); };
+    auto leaf_root = [&](int k) {
+        const int m = mesh(k);
+        if ((k == 0 || mesh(k - 1) != m) && (k == n - 1 || mesh(k + 1) != m))
+            roots[m] = ~k;
+    };
+    if (roots) {
+        leaf_root(i);
+        if (i == n - 2)
+            leaf_root(n - 1);
+    }
     const K ki = keys[i];
     const int d = prefix(keys, n, i, ki, i + 1) > prefix(keys, n, i, ki, i - 1) ? 1 : -1;
     const int below = prefix(keys, n, i, ki, i - d);
@@ -514,7 +673,14 @@ __global__ __launch_bounds__(256) void k_radix_tree(const K *__restrict__ keys, 
     parent[left >= 0 ? left : (n - 1) + ~left] = i;
     parent[right >= 0 ? right : (n - 1) + ~right] = i;
     counters[i] = 0;
-    tile_flag[i] = hi - lo + 1 <= kBoxTile ? kTileRootFlag : 0;
+    // the internal node whose key range is exactly a mesh's keys is its root
+    if (roots) {
+        const int m = mesh(lo);
+        const bool is_root = mesh(hi) == m && (lo == 0 || mesh(lo - 1) != m) && (hi == n - 1 || mesh(hi + 1) != m);
+        if (is_root)
+            roots[m] = i;
+        flag[i] = is_root ? kMeshRootFlag : 0;
+    }
     if (i == 0)
         parent[0] = -1;
 
@@ -545,9 +711,13 @@ __global__ __launch_bounds__(256) void k_radix_tree(const K *__restrict__ keys, 
     }
 }
 
-__global__ void k_single_tile(int32_t *tiles, int32_t *n_tiles) {
-    tiles[0] = ~0;  // one triangle: the leaf is the whole tree
+// one triangle: the leaf is the whole tree (batched form: of its mesh)
+template <typename K>
+__global__ void k_single_tile(int32_t *tiles, int32_t *n_tiles, const K *keys, int32_t *roots) {
+    tiles[0] = ~0;
     *n_tiles = 1;
+    if (roots)
+        roots[(uint64_t)keys[0] >> kBatchMortonBits] = ~0;
 }
 
 // ------------------------------------------------- 5. leaves and bottom-up
@@ -557,8 +727,8 @@ __global__ void k_single_tile(int32_t *tiles, int32_t *n_tiles) {
 // most kBoxTile leaves (listed by k_radix_tree), and nodes above them:
 //   k_leaves_subtree  one workgroup per tile: counters and child boxes in LDS,
 //                     no cross-workgroup synchronisation at all;
-//   k_boxes_top       one workgroup climbs the nodes above the tiles (about
-//                     log2(N_t / kBoxTile) levels) with workgroup-scope atomics.
+//   k_boxes_top       one workgroup climbs the nodes above the tiles with
+//                     workgroup-scope atomics.
 // Cross-XCD agent-scope atomics, which cost an L2 write-back each on gfx950,
 // are not needed.  Every child box lands in its parent node in HBM; a
 // finished internal node's counter reads 2.
@@ -597,21 +767,23 @@ __device__ __forceinline__ void make_leaf(const float *__restrict__ V, int64_t n
     tris[k] = tri;
 }
 
-__device__ __forceinline__ void store_child_box(Node *node, bool is_left, const float *lo, const float *hi) {
-    if (is_left) {
-        node->xy_left = make_float4(lo[0], hi[0], lo[1], hi[1]);
-        *reinterpret_cast<float2 *>(&node->z_both.x) = make_float2(lo[2], hi[2]);
-    } else {
-        node->xy_right = make_float4(lo[0], hi[0], lo[1], hi[1]);
-        *reinterpret_cast<float2 *>(&node->z_both.z) = make_float2(lo[2], hi[2]);
-    }
-}
+// A tile in LDS: its internal nodes at their index minus the first leaf's.
+// Child references: a local node, or kLeafBit and a local leaf; parents: a
+// local node, kOutside for the tile root's.
+constexpr int kLeafBit = 0x8000, kOutside = 0xffff;
+struct BoxTile {
+    float box[kBoxTile][2][6];  // both children's boxes: lo xyz, hi xyz
+    int arrived[kBoxTile];
+    uint16_t left[kBoxTile], parent[kBoxTile];
+};
 
-// Phase 1: one workgroup per listed tile (a subtree of at most kBoxTile
-// leaves, sorted positions [a, b]).  Lane j takes leaf a + j, writes its
-// triangle and climbs; every internal node of the tile lies in [a, b], so
-// arrival counters and child boxes live in LDS at p - a.  The lane completing
-// the tile root hands its box to the root's parent.
+// One workgroup per listed tile (a subtree of at most kBoxTile leaves, sorted
+// positions [a, b]).  Every internal node of the tile lies in [a, b], so the
+// whole tile is in LDS: its references are loaded in one step, lane j then
+// takes leaf a + j, writes its triangle and climbs with arrival counters and
+// child boxes in LDS; the lane completing the tile root hands its box to the
+// root's parent.  (Parents and references read from L2 at every level of the
+// climb: 19.7 us at 32,258 triangles, against 16.6.)
 __global__ __launch_bounds__(kBoxTile) void k_leaves_subtree(const float *__restrict__ V, int64_t nv,
                                                             const int32_t *__restrict__ F,
                                                             const int32_t *__restrict__ ids, int n,
@@ -619,8 +791,8 @@ __global__ __launch_bounds__(kBoxTile) void k_leaves_subtree(const float *__rest
                                                             const int32_t *__restrict__ parent, int32_t *counters,
                                                             const int32_t *__restrict__ tiles,
                                                             const int32_t *__restrict__ n_tiles) {
-    __shared__ int arrived[kBoxTile];
-    __shared__ float box[kBoxTile][2][6];
+    __shared__ BoxTile T;
+    const int tid = threadIdx.x;
     const int total = *n_tiles;
     for (int e = blockIdx.x; e < total; e += gridDim.x) {
         const int c = tiles[e];
@@ -632,79 +804,72 @@ __global__ __launch_bounds__(kBoxTile) void k_leaves_subtree(const float *__rest
             a = r.z;
             b = r.w;
         }
-        arrived[threadIdx.x] = 0;
-        __syncthreads();
-        const int k = a + (int)threadIdx.x;
-        if (a >= 0 && k <= b && b < n && b - a < kBoxTile) {
-            float lo[3], hi[3];
+        const bool ok = a >= 0 && b < n && b - a < kBoxTile;  // always, for a tile the radix-tree kernel listed
+        // a subtree over [a, b] rooted at a holds the internal nodes [a, b - 1],
+        // rooted at b those of [a + 1, b]
+        const int base = c == a ? a : a + 1, g = a + tid;
+        T.arrived[tid] = 0;
+        if (ok && c >= 0 && g >= base && g < base + b - a) {
+            const int l = nodes[g].refs.x;
+            T.left[tid] = (uint16_t)(l >= 0 ? l - a : kLeafBit | (~l - a));
+            T.parent[tid] = (uint16_t)(g == c ? kOutside : parent[g] - a);
+        }
+        const int k = a + tid;
+        const bool mine = ok && k <= b;
+        float lo[3], hi[3];
+        if (mine)
             make_leaf(V, nv, F, ids, n, k, tris, lo, hi);
-            int self = ~k;
-            int p = n >= 2 ? parent[(n - 1) + k] : -1;
-            if (self == c) {
-                // a one-leaf tile: its box goes straight to the parent
-                if (p >= 0 && p < n - 1)
-                    store_child_box(nodes + p, nodes[p].refs.x == self, lo, hi);
-            } else {
-                // a radix tree is at most 97 levels deep; the bound only guards the loop
-                for (int level = 0; p >= a && p <= b && p < n - 1 && level < kDeepStack; ++level) {
-                    Node *node = nodes + p;
-                    const bool is_left = node->refs.x == self;
-                    store_child_box(node, is_left, lo, hi);
-                    float *mine = box[p - a][is_left ? 0 : 1];
-                    for (int d = 0; d < 3; ++d) {
-                        mine[d] = lo[d];
-                        mine[3 + d] = hi[d];
-                    }
-                    __threadfence_block();
-                    if (atomicAdd(&arrived[p - a], 1) == 0)
-                        break;  // the sibling subtree is not finished; its last lane continues
-                    __threadfence_block();
-                    const float *other = box[p - a][is_left ? 1 : 0];
-                    for (int d = 0; d < 3; ++d) {
-                        lo[d] = fminf(lo[d], other[d]);
-                        hi[d] = fmaxf(hi[d], other[3 + d]);
-                    }
-                    counters[p] = 2;
-                    if (p == c) {
-                        const int q = parent[p];
-                        if (q >= 0 && q < n - 1)
-                            store_child_box(nodes + q, nodes[q].refs.x == p, lo, hi);
-                        break;
-                    }
-                    self = p;
-                    p = parent[p];
+        int p = mine && n >= 2 ? parent[(n - 1) + k] : -1;
+        __syncthreads();
+        if (mine && c < 0) {
+            // a one-leaf tile: its box goes straight to the parent
+            if (p >= 0 && p < n - 1)
+                store_child_box(nodes + p, nodes[p].refs.x == ~k, lo, hi);
+        } else if (mine) {
+            int self = kLeafBit | tid, j = p - a;
+            // a radix tree is at most 97 levels deep; the bound only guards the loop
+            for (int level = 0; j >= 0 && j < kBoxTile && level < kDeepStack; ++level) {
+                const int side = T.left[j] == self ? 0 : 1;
+                store_child_box(nodes + a + j, side == 0, lo, hi);
+                float *own = T.box[j][side];
+                for (int d = 0; d < 3; ++d) {
+                    own[d] = lo[d];
+                    own[3 + d] = hi[d];
                 }
+                __threadfence_block();
+                if (atomicAdd(&T.arrived[j], 1) == 0)
+                    break;  // the sibling subtree is not finished; its last lane continues
+                __threadfence_block();
+                const float *other = T.box[j][side ^ 1];
+                for (int d = 0; d < 3; ++d) {
+                    lo[d] = fminf(lo[d], other[d]);
+                    hi[d] = fmaxf(hi[d], other[3 + d]);
+                }
+                counters[a + j] = 2;
+                const int up = T.parent[j];
+                if (up == kOutside) {
+                    const int q = parent[c];
+                    if (q >= 0 && q < n - 1)
+                        store_child_box(nodes + q, nodes[q].refs.x == c, lo, hi);
+                    break;
+                }
+                self = j;
+                j = up;
             }
         }
         __syncthreads();  // LDS is reused by the next tile
     }
 }
 
-// Phase 2: one workgroup finishes the nodes above the tiles (every node with
-// more than kBoxTile leaves).  Each listed tile is an arrival at its parent;
-// the second arrival merges the two child boxes (written by phase 1, or by
-// this workgroup before its release) and climbs on.
+// One workgroup finishes the nodes above the tiles (every node with more than
+// kBoxTile leaves).  Each listed tile is an arrival at its parent; the second
+// arrival merges the two child boxes (written by the tile's workgroup, or by
+// this one before its release) and climbs on: about log2(N_t / kBoxTile) levels.
+// (A build that restructures its tiles has a workgroup of that launch do it.)
 __global__ __launch_bounds__(1024) void k_boxes_top(Node *nodes, const int32_t *__restrict__ parent,
                                                     int32_t *counters, const int32_t *__restrict__ tiles,
                                                     const int32_t *__restrict__ n_tiles, int n) {
-    const int total = *n_tiles;
-    for (int e = threadIdx.x; e < total; e += blockDim.x) {
-        const int c = tiles[e];
-        int p = c < 0 ? parent[(n - 1) + ~c] : parent[c];
-        for (int level = 0; p >= 0 && p < n - 1 && level < kDeepStack; ++level) {
-            if (__hip_atomic_fetch_add(counters + p, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
-                break;
-            const Node *node = nodes + p;
-            const float4 L = node->xy_left, R = node->xy_right, Z = node->z_both;
-            const float lo[3] = {fminf(L.x, R.x), fminf(L.z, R.z), fminf(Z.x, Z.z)};
-            const float hi[3] = {fmaxf(L.y, R.y), fmaxf(L.w, R.w), fmaxf(Z.y, Z.w)};
-            const int q = parent[p];
-            if (q < 0 || q >= n - 1)
-                break;  // p is the root
-            store_child_box(nodes + q, nodes[q].refs.x == p, lo, hi);
-            p = q;
-        }
-    }
+    boxes_above_tiles(nodes, parent, counters, tiles, *n_tiles, n);
 }
 
 // ------------------------------------------ 5'. agglomerative single pass
@@ -786,60 +951,54 @@ __global__ void k_zero_i32(int32_t *p, int n) {
 
 inline int blocks_for(int64_t n, int threads) { return (int)((n + threads - 1) / threads); }
 
-// After an odd number of sort passes the sorted pairs sit in the scratch
-// buffers: copy them back.
+// Where a sort of n pairs keeps what (in its scratch).
 template <typename K>
-__global__ void k_copy_pairs(const K *__restrict__ k_in, const int32_t *__restrict__ i_in, K *__restrict__ k_out,
-                             int32_t *__restrict__ i_out, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        k_out[i] = k_in[i];
-        i_out[i] = i_in[i];
-    }
-}
+struct SortArea {
+    K *keys;        // ping-pong copies
+    int32_t *ids;
+    int ntiles;
+    uint32_t *hist;     // digit-major, three histograms in turn for one-launch passes
+    uint32_t *partial;  // digit totals of a large sort
+    SortArea(void *tmp, int64_t n)
+        : keys(static_cast<K *>(tmp)), ids(reinterpret_cast<int32_t *>(keys + n)), ntiles(blocks_for(n, kSortTile)),
+          hist(reinterpret_cast<uint32_t *>(ids + n)), partial(hist + (int64_t)kRadix * ntiles) {}
+    bool small() const { return ntiles <= kSmallSortTiles; }
+    uint32_t *clear() const { return small() ? hist + (int64_t)kRadix * ntiles : nullptr; }
+};
 
-// Stable LSD passes over (keys, ids) with 8-bit digits; tmp holds the
-// ping-pong copies, the tile histograms and the scan partials.  Up to
-// kSmallSortTiles tiles a pass is one launch; above that, a histogram, a scan
-// of each digit's row and a scatter.  An even number of passes (key_bits 30 or 63 rounded up to
-// 32 or 64) leaves the result in (keys, ids); an odd one (the batched form's
-// 36-bit keys) ends with a copy back.
+// Stable LSD passes over the pairs, with 8-bit digits.  An even number of
+// passes sorts (keys, ids) in place; with an odd one (the batched form's 36-bit
+// keys) the pairs start in the scratch copies.  The first pass's tile counts
+// are in the scratch already (put_hist).  Up to kSmallSortTiles tiles a pass is
+// one launch; above that, a histogram, a scan of each digit's row and a
+// scatter.
 template <typename K>
 void sort_passes(K *keys, int32_t *ids, void *tmp, int64_t n, int key_bits, hipStream_t s) {
-    K *keys_tmp = static_cast<K *>(tmp);
-    int32_t *ids_tmp = reinterpret_cast<int32_t *>(keys_tmp + n);
-    const int ntiles = blocks_for(n, kSortTile);
-    uint32_t *hist = reinterpret_cast<uint32_t *>(ids_tmp + n);
-    uint32_t *partial = hist + (int64_t)kRadix * ntiles;
-    K *src_k = keys, *dst_k = keys_tmp;
-    int32_t *src_i = ids, *dst_i = ids_tmp;
     if (n <= 1)
         return;  // nothing to order
-    if (ntiles <= kSmallSortTiles) {
-        // three histograms in turn: read by this pass, added to for the next,
-        // cleared for the one after
-        const int64_t hl = (int64_t)kRadix * ntiles;
-        uint32_t *H[3] = {hist, hist + hl, hist + 2 * hl};
-        k_sort_hist<K><<<ntiles, kSortThreads, 0, s>>>(src_k, n, 0, ntiles, H[0], H[1]);
-        for (int shift = 0, pass = 0; shift < key_bits; shift += 8, ++pass) {
-            k_sort_pass_small<K><<<ntiles, kSortThreads, 0, s>>>(src_k, src_i, dst_k, dst_i, n, shift, ntiles,
-                                                                  H[pass % 3], shift + 8 < key_bits ? H[(pass + 1) % 3] : nullptr,
-                                                                  H[(pass + 2) % 3]);
-            K *tk = src_k; src_k = dst_k; dst_k = tk;
-            int32_t *ti = src_i; src_i = dst_i; dst_i = ti;
+    const SortArea<K> A(tmp, n);
+    const bool odd = ((key_bits + 7) / 8) & 1;
+    K *src_k = odd ? A.keys : keys, *dst_k = odd ? keys : A.keys;
+    int32_t *src_i = odd ? A.ids : ids, *dst_i = odd ? ids : A.ids;
+    const int64_t hl = (int64_t)kRadix * A.ntiles;
+    // three histograms in turn: read by this pass, added to for the next,
+    // cleared for the one after
+    uint32_t *H[3] = {A.hist, A.hist + hl, A.hist + 2 * hl};
+    for (int shift = 0, pass = 0; shift < key_bits; shift += 8, ++pass) {
+        if (A.small()) {
+            k_sort_pass_small<K><<<A.ntiles, kSortThreads, 0, s>>>(
+                src_k, src_i, dst_k, dst_i, n, shift, A.ntiles, H[pass % 3],
+                shift + 8 < key_bits ? H[(pass + 1) % 3] : nullptr, H[(pass + 2) % 3]);
+        } else {
+            if (pass > 0)
+                k_sort_hist<K><<<A.ntiles, kSortThreads, 0, s>>>(src_k, n, shift, A.ntiles, A.hist, nullptr);
+            k_scan_rows<<<kRadix, 1024, 0, s>>>(A.hist, A.ntiles, A.partial);
+            k_sort_scatter<K><<<A.ntiles, kSortThreads, 0, s>>>(src_k, src_i, dst_k, dst_i, n, shift, A.ntiles, A.hist,
+                                                                 A.partial);
         }
-    } else {
-        for (int shift = 0; shift < key_bits; shift += 8) {
-            k_sort_hist<K><<<ntiles, kSortThreads, 0, s>>>(src_k, n, shift, ntiles, hist, nullptr);
-            k_scan_rows<<<kRadix, 1024, 0, s>>>(hist, ntiles, partial);
-            k_sort_scatter<K><<<ntiles, kSortThreads, 0, s>>>(src_k, src_i, dst_k, dst_i, n, shift, ntiles, hist,
-                                                               partial);
-            K *tk = src_k; src_k = dst_k; dst_k = tk;
-            int32_t *ti = src_i; src_i = dst_i; dst_i = ti;
-        }
+        K *tk = src_k; src_k = dst_k; dst_k = tk;
+        int32_t *ti = src_i; src_i = dst_i; dst_i = ti;
     }
-    if (src_k != keys && n > 0)
-        k_copy_pairs<K><<<blocks_for(n, 256), 256, 0, s>>>(src_k, src_i, keys, ids, n);
 }
 
 size_t pass_tmp_bytes(int64_t n, size_t key_bytes) {
@@ -849,9 +1008,10 @@ size_t pass_tmp_bytes(int64_t n, size_t key_bytes) {
 }
 
 // Sort (key, id), build the radix tree and fill the boxes bottom-up, for keys
-// already in m.keys and ids in m.ids.
+// and ids where sort_passes takes them and their first digit counted.  roots
+// (NULL for one mesh) receives each mesh's subtree root.
 template <typename K>
-hipError_t build_from_keys(MeshDev &m, int key_bits, hipStream_t s) {
+hipError_t build_from_keys(MeshDev &m, int key_bits, int32_t *roots, hipStream_t s) {
     const int64_t nt = m.nt;
     K *keys = static_cast<K *>(m.keys);
     sort_passes<K>(keys, m.ids, m.sort_tmp, nt, key_bits, s);  // sorted pairs back in (keys, ids)
@@ -867,51 +1027,54 @@ hipError_t build_from_keys(MeshDev &m, int key_bits, hipStream_t s) {
         return hipGetLastError();
     }
     // the sort's scratch is free again: the list of bottom-up tiles
-    const BuildLists L = build_lists(m.sort_tmp, nt);
+    const BuildLists L = build_lists(m);
     int32_t *n_tiles = L.n_tiles;
     int32_t *tiles = L.tiles;
-    if (nt >= 2) {
-        k_zero_i32<<<1, 64, 0, s>>>(n_tiles, 1);
+    if (nt >= 2)
         k_radix_tree<K><<<blocks_for(nt - 1, 256), 256, 0, s>>>(keys, (int)nt, m.nodes, m.parent, m.counters, tiles,
-                                                                n_tiles, L.tile_flag);
-    } else {
-        k_single_tile<<<1, 1, 0, s>>>(tiles, n_tiles);
-    }
+                                                                n_tiles, L.flag, roots);
+    else
+        k_single_tile<K><<<1, 1, 0, s>>>(tiles, n_tiles, keys, roots);
     int dev = 0, cus = 256;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const int64_t grid = nt < 2 * (int64_t)cus ? nt : 2 * (int64_t)cus;  // tiles are taken in a loop
     k_leaves_subtree<<<(int)grid, kBoxTile, 0, s>>>(m.V, m.nv, m.F, m.ids, (int)nt, m.tris, m.nodes, m.parent,
                                                     m.counters, tiles, n_tiles);
-    if (nt > kBoxTile)
+    if (nt > kBoxTile && m.algorithm != 2)
         k_boxes_top<<<1, 1024, 0, s>>>(m.nodes, m.parent, m.counters, tiles, n_tiles, (int)nt);
     return hipGetLastError();
 }
 
 template <typename K>
-hipError_t build_typed(MeshDev &m, const int32_t *F_in, hipStream_t s) {
+hipError_t build_typed(MeshDev &m, const int32_t *F_in, int parts, hipStream_t s) {
     const int64_t nt = m.nt;
-    k_morton<K><<<blocks_for(nt, 256), 256, 0, s>>>(m.V, m.nv, F_in, nt, m.bounds, static_cast<K *>(m.keys), m.ids,
-                                                    m.flags, m.F);
-    return build_from_keys<K>(m, m.morton_bits, s);
+    const SortArea<K> A(m.sort_tmp, nt);
+    k_morton<K><<<A.ntiles, kSortThreads, 0, s>>>(m.V, m.nv, F_in, nt, m.partial, parts, m.bounds,
+                                                  static_cast<K *>(m.keys), m.ids, m.flags, m.F, A.ntiles, A.hist,
+                                                  A.clear());
+    return build_from_keys<K>(m, m.morton_bits, nullptr, s);
 }
 
 }  // namespace
 
-hipError_t launch_morton_batch(MeshDev &m, const int32_t *tri_mesh, const float *mesh_bounds, hipStream_t s) {
-    if (m.nt > 0)
-        k_morton_batch<<<blocks_for(m.nt, 256), 256, 0, s>>>(m.V, m.F, tri_mesh, m.nt, mesh_bounds,
-                                                            static_cast<uint64_t *>(m.keys), m.ids);
-    return hipGetLastError();
+hipError_t launch_build_batch(MeshDev &m, const BatchDev &b, hipStream_t s) {
+    // five 8-bit passes: the pairs start in the sort's scratch (a single pair
+    // is not sorted and starts in place)
+    constexpr int key_bits = kBatchMortonBits + 6;
+    const SortArea<uint64_t> A(m.sort_tmp, m.nt);
+    uint64_t *keys = m.nt > 1 ? A.keys : static_cast<uint64_t *>(m.keys);
+    int32_t *ids = m.nt > 1 ? A.ids : m.ids;
+    k_morton_batch<<<A.ntiles, kSortThreads, 0, s>>>(m.V, m.F, b.tri_mesh, m.nt, b.key_bounds, b.M, b.mesh_bounds,
+                                                     m.bounds, keys, ids, A.ntiles, A.hist, A.clear());
+    return build_from_keys<uint64_t>(m, key_bits, b.roots, s);
 }
 
 size_t sort_tmp_bytes(int64_t nt, int morton_bits) {
     const size_t kb = morton_bits > 32 ? 8 : 4;
     const size_t sort = pass_tmp_bytes(nt, kb);
     const size_t lists = build_lists_bytes(nt);  // lists kept after the sort
-    const size_t parts = 6 * sizeof(float) * kBoundsParts;  // extent partials before the sort
-    const size_t most = sort > lists ? sort : lists;
-    return most > parts ? most : parts;
+    return sort > lists ? sort : lists;
 }
 
 size_t sort_u32_tmp_bytes(int64_t n) { return pass_tmp_bytes(n, 4); }
@@ -923,23 +1086,22 @@ hipError_t scan_u32_exclusive(uint32_t *a, int64_t len, uint32_t *partial, hipSt
 }
 
 hipError_t sort_u32_pairs(uint32_t *keys, int32_t *ids, void *tmp, int64_t n, hipStream_t s) {
-    if (n > 1)
+    if (n > 1) {
+        const SortArea<uint32_t> A(tmp, n);
+        k_sort_hist<uint32_t><<<A.ntiles, kSortThreads, 0, s>>>(keys, n, 0, A.ntiles, A.hist, A.clear());
         sort_passes<uint32_t>(keys, ids, tmp, n, 32, s);  // four passes
+    }
     return hipGetLastError();
 }
 
-hipError_t build_from_keys64(MeshDev &m, int key_bits, hipStream_t s) { return build_from_keys<uint64_t>(m, key_bits, s); }
-
 hipError_t launch_build(MeshDev &m, const float *V_in, const int32_t *F_in, hipStream_t s, size_t) {
-    // the sort scratch is free until the keys are sorted; the first kernels
-    // also copy the caller's vertices and triangles into the mesh
+    // the first kernels also copy the caller's vertices and triangles into the mesh
     const int64_t want = (m.nv + 1023) / 1024;
     const int parts = (int)(want < 1 ? 1 : (want < kBoundsParts ? want : kBoundsParts));
-    float *partial = static_cast<float *>(m.sort_tmp);
-    k_mesh_bounds_part<<<parts, 1024, 0, s>>>(V_in, m.nv, partial, m.V, m.flags);
-    k_mesh_bounds_final<<<1, kBoundsParts, 0, s>>>(partial, parts, m.bounds);
-    hipError_t e = m.morton_bits > 32 ? build_typed<uint64_t>(m, F_in, s) : build_typed<uint32_t>(m, F_in, s);
-    if (e == hipSuccess && m.algorithm == 2)
+    k_mesh_bounds_part<<<parts, 1024, 0, s>>>(V_in, m.nv, m.partial, m.V, m.flags);
+    hipError_t e = m.morton_bits > 32 ? build_typed<uint64_t>(m, F_in, parts, s)
+                                      : build_typed<uint32_t>(m, F_in, parts, s);
+    if (e == hipSuccess && m.algorithm == 2 && m.nt >= kRestructureMin)
         e = launch_restructure(m, kRestructureRounds, s);
     if (e == hipSuccess && m.algorithm != 1 && m.nodes4)
         e = launch_collapse(m, s);

@@ -31,31 +31,38 @@
 namespace rsi {
 namespace {
 
-constexpr int kTile = 1024;            // leaves per tile
+constexpr int kTile = kTileLeaves;     // leaves per tile
 constexpr int kThreads = 512;          // lanes per workgroup (256 VGPRs per lane, no spills)
-constexpr int kTreelet = 4;            // leaves per treelet (the optimisation runs in one lane's registers)
+constexpr int kTreelet = kRestructureMin;  // leaves per treelet (the optimisation runs in one lane's registers)
 constexpr float kCostNode = 1.2f;      // SAH weight of a node visit (one 64-B node, two box tests)
 constexpr float kCostTri = 1.0f;       // SAH weight of a triangle test
 
 // LDS image of one (sub)tree, nodes and leaves in one index space: a local
 // reference c below kTile is internal node c (local ids are offsets from the
 // tile's first internal node), c >= kTile is leaf c - kTile.  Every per-node
-// quantity is then one LDS read, whichever kind the reference is.
+// quantity is then one LDS read, whichever kind the reference is.  16-bit ids
+// and 78 KB in all, so a CU holds two tiles (124 KB and one tile: 383 us at
+// 522,242 triangles, whose 850 tiles took four turns of 256; 257 with two).
 struct TileLds {
-    int child[2][kTile];         // local references of internal node j's children
-    int slot[kTile];             // global internal node index of internal node j
-    int lf_ref[kTile];           // global reference of leaf k (a leaf ~g)
     float box[6][2 * kTile];     // own box of reference c: lo xyz, hi xyz
     float cost[2 * kTile];       // SAH cost of the subtree
-    int count[2 * kTile];        // leaves below
-    int lo[2 * kTile], hi[2 * kTile];  // smallest / largest sorted leaf below
-    int parent[2 * kTile];       // local parent (internal), -1 at the root
-    int arrive[kTile + 2];       // arrivals of the height climb, then per-height counters
-    int height[kTile];           // 1 + the larger child height (a leaf is 0)
-    int order[kTile];            // internal nodes by rising height
-    int h_start[kTile + 2];      // order[h_start[h] .. h_start[h + 1]) have height h
+    uint16_t child[2][kTile];    // local references of internal node j's children
+    uint16_t count_[kTile];      // leaves below internal node j
+    uint16_t lo[2 * kTile], hi[2 * kTile];  // smallest / largest leaf below, from the tile's first
+    uint16_t parent[2 * kTile];  // local parent (internal), kNone at the root
+    uint16_t order[kTile];       // internal nodes by rising height
+    uint16_t h_start[kTile + 2]; // order[h_start[h] .. h_start[h + 1]) have height h
     int n_in, n_lf, max_height;
+    int base, first;             // first internal node and leaf of the tile
+    // While a pass orders the nodes by height, their costs and counts are not
+    // in use (the pass sets them anew from the leaves up): arrivals of the
+    // height climb, then per-height counters; 1 + the larger child height.
+    __device__ __forceinline__ int *arrive() { return reinterpret_cast<int *>(cost); }
+    __device__ __forceinline__ uint16_t *height() { return count_; }
+    __device__ __forceinline__ int count(int c) const { return c < kTile ? count_[c] : 1; }
+    __device__ __forceinline__ int global_ref(int c) const { return c < kTile ? base + c : ~(first + c - kTile); }
 };
+constexpr int kNone = 0xffff;
 
 __device__ __forceinline__ float half_area(float x0, float y0, float z0, float x1, float y1, float z1) {
     const float dx = x1 - x0, dy = y1 - y0, dz = z1 - z0;
@@ -70,9 +77,9 @@ __device__ __forceinline__ float box_area(const TileLds &T, int c) {
 __device__ __forceinline__ void refresh_node(TileLds &T, int j) {
     const int c0 = T.child[0][j], c1 = T.child[1][j];
     T.cost[j] = kCostNode * box_area(T, j) + T.cost[c0] + T.cost[c1];
-    T.count[j] = T.count[c0] + T.count[c1];
-    T.lo[j] = min(T.lo[c0], T.lo[c1]);
-    T.hi[j] = max(T.hi[c0], T.hi[c1]);
+    T.count_[j] = (uint16_t)(T.count(c0) + T.count(c1));
+    T.lo[j] = (uint16_t)min((int)T.lo[c0], (int)T.lo[c1]);
+    T.hi[j] = (uint16_t)max((int)T.hi[c0], (int)T.hi[c1]);
 }
 
 // Splits of the subsets of four treelet leaves: {subset, part holding the
@@ -155,7 +162,7 @@ __device__ __forceinline__ void optimize_treelet(TileLds &T, int p) {
 #pragma unroll
             for (int a = 0; a < 6; ++a)
                 sb[S][a] = T.box[a][r];
-            sn[S] = T.count[r];
+            sn[S] = T.count(r);
             slo[S] = T.lo[r];
             shi[S] = T.hi[r];
             cost[S] = T.cost[r];
@@ -236,17 +243,17 @@ __device__ __forceinline__ void optimize_treelet(TileLds &T, int p) {
             }
         }
         const int j = node[S];
-        T.child[0][j] = child0;
-        T.child[1][j] = child1;
-        T.parent[child0] = j;
-        T.parent[child1] = j;
+        T.child[0][j] = (uint16_t)child0;
+        T.child[1][j] = (uint16_t)child1;
+        T.parent[child0] = (uint16_t)j;
+        T.parent[child1] = (uint16_t)j;
 #pragma unroll
         for (int a = 0; a < 6; ++a)
             T.box[a][j] = sb[S][a];
         T.cost[j] = cost[S];
-        T.count[j] = sn[S];
-        T.lo[j] = slo[S];
-        T.hi[j] = shi[S];
+        T.count_[j] = (uint16_t)sn[S];
+        T.lo[j] = (uint16_t)slo[S];
+        T.hi[j] = (uint16_t)shi[S];
     }
 }
 
@@ -265,12 +272,12 @@ constexpr int kGroup = 16;
 __device__ __forceinline__ void treelet_group(TileLds &T, int p, int g, int base) {
     const int c0 = T.child[0][p], c1 = T.child[1][p];
     const float now = kCostNode * box_area(T, p) + T.cost[c0] + T.cost[c1];
-    const int cnt = T.count[c0] + T.count[c1];
+    const int cnt = T.count(c0) + T.count(c1);
     if (g == 0) {  // refresh p
         T.cost[p] = now;
-        T.count[p] = cnt;
-        T.lo[p] = min(T.lo[c0], T.lo[c1]);
-        T.hi[p] = max(T.hi[c0], T.hi[c1]);
+        T.count_[p] = (uint16_t)cnt;
+        T.lo[p] = (uint16_t)min((int)T.lo[c0], (int)T.lo[c1]);
+        T.hi[p] = (uint16_t)max((int)T.hi[c0], (int)T.hi[c1]);
     }
     if (cnt < kTreelet)
         return;
@@ -294,9 +301,9 @@ __device__ __forceinline__ void treelet_group(TileLds &T, int p, int g, int base
                 b[a] = fminf(b[a], T.box[a][r]);
                 b[3 + a] = fmaxf(b[3 + a], T.box[3 + a][r]);
             }
-            n += T.count[r];
-            lo = min(lo, T.lo[r]);
-            hi = max(hi, T.hi[r]);
+            n += T.count(r);
+            lo = min(lo, (int)T.lo[r]);
+            hi = max(hi, (int)T.hi[r]);
         }
     }
     const float area = half_area(b[0], b[1], b[2], b[3], b[4], b[5]);
@@ -398,17 +405,17 @@ __device__ __forceinline__ void treelet_group(TileLds &T, int p, int g, int base
     if ((used >> S) & 1) {
         const int j = ref_of(S);
         const int child0 = ref_of(split), child1 = ref_of(S ^ split);
-        T.child[0][j] = child0;
-        T.child[1][j] = child1;
-        T.parent[child0] = j;
-        T.parent[child1] = j;
+        T.child[0][j] = (uint16_t)child0;
+        T.child[1][j] = (uint16_t)child1;
+        T.parent[child0] = (uint16_t)j;
+        T.parent[child1] = (uint16_t)j;
 #pragma unroll
         for (int k = 0; k < 6; ++k)
             T.box[k][j] = b[k];
         T.cost[j] = c;
-        T.count[j] = n;
-        T.lo[j] = lo;
-        T.hi[j] = hi;
+        T.count_[j] = (uint16_t)n;
+        T.lo[j] = (uint16_t)lo;
+        T.hi[j] = (uint16_t)hi;
     }
 }
 
@@ -416,22 +423,24 @@ __device__ __forceinline__ void treelet_group(TileLds &T, int p, int g, int base
 // leaf: the second lane to reach a node finds both child heights final.
 // Integer work only, so the divergence of the climb costs little.
 __device__ __forceinline__ void local_heights(TileLds &T) {
+    int *arrive = T.arrive();
+    uint16_t *height = T.height();
     for (int j = threadIdx.x; j < T.n_in; j += blockDim.x) {
-        T.arrive[j] = 0;
-        T.height[j] = 0;
+        arrive[j] = 0;
+        height[j] = 0;
     }
     if (threadIdx.x == 0)
         T.max_height = 0;
     __syncthreads();
     for (int k = threadIdx.x; k < T.n_lf; k += blockDim.x) {
         int j = T.parent[kTile + k];
-        for (int step = 0; j >= 0 && step < T.n_in; ++step) {  // a climb is at most n_in nodes long
-            if (__hip_atomic_fetch_add(&T.arrive[j], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
+        for (int step = 0; j != kNone && step < T.n_in; ++step) {  // a climb is at most n_in nodes long
+            if (__hip_atomic_fetch_add(&arrive[j], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
                 break;  // the other subtree is still on its way
             const int c0 = T.child[0][j], c1 = T.child[1][j];
-            const int h = 1 + max(c0 < kTile ? T.height[c0] : 0, c1 < kTile ? T.height[c1] : 0);
-            T.height[j] = h;
-            if (T.parent[j] < 0)
+            const int h = 1 + max(c0 < kTile ? (int)height[c0] : 0, c1 < kTile ? (int)height[c1] : 0);
+            height[j] = (uint16_t)h;
+            if (T.parent[j] == kNone)
                 T.max_height = h;  // the local root is the highest node
             j = T.parent[j];
         }
@@ -444,13 +453,15 @@ __device__ __forceinline__ void local_heights(TileLds &T) {
 // does not matter, its nodes are independent).
 __device__ __forceinline__ void order_by_height(TileLds &T) {
     const int H = T.max_height;
+    int *arrive = T.arrive();
+    const uint16_t *height = T.height();
     for (int h = threadIdx.x; h <= H; h += blockDim.x)
-        T.arrive[h] = 0;
+        arrive[h] = 0;
     __syncthreads();
     for (int j = threadIdx.x; j < T.n_in; j += blockDim.x) {
-        const int h = T.height[j];
+        const int h = height[j];
         if (h >= 1 && h <= H)  // always, in a tree the climb reached whole
-            atomicAdd(&T.arrive[h], 1);
+            atomicAdd(&arrive[h], 1);
     }
     __syncthreads();
     if (threadIdx.x < 64) {  // exclusive scan of the counts by the first wave
@@ -458,7 +469,7 @@ __device__ __forceinline__ void order_by_height(TileLds &T) {
         int carry = 0;
         for (int base = 0; base <= H + 1; base += 64) {
             const int h = base + lane;
-            const int v = h <= H ? T.arrive[h] : 0;
+            const int v = h <= H ? arrive[h] : 0;
             int incl = v;
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
@@ -466,18 +477,18 @@ __device__ __forceinline__ void order_by_height(TileLds &T) {
                 incl += lane >= d ? u : 0;
             }
             if (h <= H + 1)
-                T.h_start[h] = carry + incl - v;
+                T.h_start[h] = (uint16_t)(carry + incl - v);
             carry += __shfl(incl, 63, 64);
         }
     }
     __syncthreads();
     for (int h = threadIdx.x; h <= H; h += blockDim.x)
-        T.arrive[h] = 0;
+        arrive[h] = 0;
     __syncthreads();
     for (int j = threadIdx.x; j < T.n_in; j += blockDim.x) {
-        const int h = T.height[j];
+        const int h = height[j];
         if (h >= 1 && h <= H)
-            T.order[T.h_start[h] + atomicAdd(&T.arrive[h], 1)] = j;
+            T.order[T.h_start[h] + atomicAdd(&arrive[h], 1)] = (uint16_t)j;
     }
     __syncthreads();
 }
@@ -508,7 +519,7 @@ __device__ __forceinline__ void restructure_local(TileLds &T, int rounds) {
                 for (int i = b + threadIdx.x; i < e; i += blockDim.x) {
                     const int j = T.order[i];
                     refresh_node(T, j);
-                    if (T.count[j] >= kTreelet)
+                    if (T.count(j) >= kTreelet)
                         optimize_treelet(T, j);
                 }
             }
@@ -532,25 +543,22 @@ __device__ void load_tile(TileLds &T, const Node *__restrict__ nodes, int c) {
         const float4 L = nd->xy_left, R = nd->xy_right, Z = nd->z_both;
         const int4 refs = nd->refs;
         const float cb[2][6] = {{L.x, L.z, Z.x, L.y, L.w, Z.y}, {R.x, R.z, Z.z, R.y, R.w, Z.w}};
-        T.slot[j] = base + j;
         const int child[2] = {refs.x, refs.y};
         for (int side = 0; side < 2; ++side) {
             const int g = child[side];
             const int id = g >= 0 ? g - base : kTile + (~g - a);
-            T.parent[id] = j;
+            T.parent[id] = (uint16_t)j;
             for (int e = 0; e < 6; ++e)
                 T.box[e][id] = cb[side][e];
             if (g < 0) {
-                T.lf_ref[id - kTile] = g;
                 T.cost[id] = kCostTri * half_area(cb[side][0], cb[side][1], cb[side][2], cb[side][3], cb[side][4],
                                                   cb[side][5]);
-                T.count[id] = 1;
-                T.lo[id] = T.hi[id] = ~g;
+                T.lo[id] = T.hi[id] = (uint16_t)(~g - a);
             }
-            T.child[side][j] = id;
+            T.child[side][j] = (uint16_t)id;
         }
         if (base + j == c) {
-            T.parent[j] = -1;
+            T.parent[j] = (uint16_t)kNone;
             for (int e = 0; e < 3; ++e) {
                 T.box[e][j] = fminf(cb[0][e], cb[1][e]);
                 T.box[3 + e][j] = fmaxf(cb[0][3 + e], cb[1][3 + e]);
@@ -560,18 +568,20 @@ __device__ void load_tile(TileLds &T, const Node *__restrict__ nodes, int c) {
     if (threadIdx.x == 0) {
         T.n_in = n_in;
         T.n_lf = n_in ? n_in + 1 : 0;
+        T.base = base;
+        T.first = a;
     }
     __syncthreads();
 }
 
 __device__ void store_tree(const TileLds &T, Node *nodes, int32_t *parent, int n) {
     for (int j = threadIdx.x; j < T.n_in; j += blockDim.x) {
-        const int g = T.slot[j];
+        const int g = T.base + j;
         int gref[2];
         float b[2][6];
         for (int side = 0; side < 2; ++side) {
             const int c = T.child[side][j];
-            gref[side] = c < kTile ? T.slot[c] : T.lf_ref[c - kTile];
+            gref[side] = T.global_ref(c);
             for (int a = 0; a < 6; ++a)
                 b[side][a] = T.box[a][c];
             const int pslot = gref[side] >= 0 ? gref[side] : (n - 1) + ~gref[side];
@@ -581,18 +591,25 @@ __device__ void store_tree(const TileLds &T, Node *nodes, int32_t *parent, int n
         nd->xy_left = make_float4(b[0][0], b[0][3], b[0][1], b[0][4]);
         nd->xy_right = make_float4(b[1][0], b[1][3], b[1][1], b[1][4]);
         nd->z_both = make_float4(b[0][2], b[0][5], b[1][2], b[1][5]);
-        nd->refs = make_int4(gref[0], gref[1], T.lo[j], T.hi[j]);
+        nd->refs = make_int4(gref[0], gref[1], T.first + T.lo[j], T.first + T.hi[j]);
     }
 }
 
-// One workgroup per tile of the radix-tree kernel's list.
+// One workgroup per tile of the radix-tree kernel's list; the last one
+// meanwhile finishes the boxes above the tiles (a tile keeps its root, leaves
+// and box).
 __global__ __launch_bounds__(kThreads) void k_restructure_tiles(Node *nodes, int32_t *parent, int n,
                                                              const int32_t *__restrict__ tiles,
-                                                             const int32_t *__restrict__ n_tiles, int rounds) {
+                                                             const int32_t *__restrict__ n_tiles, int rounds,
+                                                             int32_t *counters) {
     extern __shared__ char lds[];
     TileLds &T = *reinterpret_cast<TileLds *>(lds);
     const int total = *n_tiles;
-    for (int e = blockIdx.x; e < total; e += gridDim.x) {
+    if (blockIdx.x == gridDim.x - 1) {
+        boxes_above_tiles(nodes, parent, counters, tiles, total, n);
+        return;
+    }
+    for (int e = blockIdx.x; e < total; e += gridDim.x - 1) {
         const int c = tiles[e];
         if (c < 0)
             continue;  // a one-leaf tile
@@ -605,12 +622,9 @@ __global__ __launch_bounds__(kThreads) void k_restructure_tiles(Node *nodes, int
 
 }  // namespace
 
-size_t restructure_lds_bytes() { return sizeof(TileLds); }
-
+static_assert(2 * sizeof(TileLds) <= 160 * 1024, "two tiles per CU");
 hipError_t launch_restructure(MeshDev &m, int rounds, hipStream_t s) {
-    if (m.nt < kTreelet)
-        return hipSuccess;
-    const BuildLists L = build_lists(m.sort_tmp, m.nt);  // the radix-tree kernel's tile list
+    const BuildLists L = build_lists(m);  // the radix-tree kernel's tile list
     int32_t *n_tiles = L.n_tiles;
     int32_t *tiles = L.tiles;
     const size_t lds = sizeof(TileLds);
@@ -623,9 +637,17 @@ hipError_t launch_restructure(MeshDev &m, int rounds, hipStream_t s) {
     int dev = 0, cus = 256;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    const int64_t want = (m.nt + kTile - 1) / kTile * 2;  // tiles hold up to kTile leaves, usually fewer
-    const int grid = (int)(want < cus ? want : cus);
-    k_restructure_tiles<<<grid, kThreads, lds, s>>>(m.nodes, m.parent, (int)m.nt, tiles, n_tiles, rounds);
+    // Tiles hold up to kTile leaves, about 600 on average.  With more of them
+    // than CUs, two workgroups of 256 lanes share a CU: one wave a SIMD each,
+    // which the 155 VGPRs allow (at 384 lanes the second did not fit beside the
+    // first: 437 against 284 us at 522,242 triangles).  With fewer, one tile's
+    // latency is all there is, and 512 lanes take its wide lower levels in fewer
+    // turns.
+    const bool shared = m.nt > 600 * (int64_t)cus;
+    const int64_t want = (m.nt + kTile - 1) / kTile * 2;
+    const int64_t most = shared ? 2 * (int64_t)cus : cus;
+    k_restructure_tiles<<<(int)(want < most ? want : most) + 1, shared ? 256 : kThreads, lds, s>>>(
+        m.nodes, m.parent, (int)m.nt, tiles, n_tiles, rounds, m.counters);
     return hipGetLastError();
 }
 

@@ -89,7 +89,6 @@ struct Proposal {
     int32_t *bucket_ref4 = nullptr;   // [256] frontier node reference per bucket in that tree
     int32_t *slot_bin = nullptr;      // [kTopSlots] binary index of each top slot
     int32_t *wide_flag = nullptr;     // [nt] collapse flags
-    int32_t *wide_queue = nullptr;    // [nt] collapse queue
     void *block = nullptr;
 };
 
@@ -112,7 +111,8 @@ struct MeshDev {
     int32_t *counters = nullptr; // [nt-1]
     Tri *tris = nullptr;       // [nt]
     float *bounds = nullptr;   // [8]
-    int32_t *flags = nullptr;  // [4]: [0] bad-index flag, [1] root of the agglomerative build
+    int32_t *flags = nullptr;  // [4]: [0] bad-index flag, [1] root of the agglomerative build, [2] number of tiles
+    float *partial = nullptr;  // [kBoundsParts][6] partial extents (one mesh)
     void *sort_tmp = nullptr;  // key/id ping-pong + histograms
     int64_t bytes = 0;
     Proposal prop;
@@ -142,6 +142,7 @@ struct BatchDev {
     int32_t *roots4g = nullptr;                  // device [kItemGroups][64] mesh roots as references in it
     int32_t *tri_mesh = nullptr;                 // device [nt]
     float *mesh_bounds = nullptr;                // device [M][8]
+    uint32_t *key_bounds = nullptr;              // device [M][8] the extents as ordered integers
     int4 *items = nullptr;                       // device [n_items] (mesh, first, end, 0), grouped
     int n_items = 0;
     int32_t *group_start = nullptr;              // device [kItemGroups + 1] first item of each group
@@ -152,39 +153,82 @@ struct BatchDev {
     int64_t n_rays = 0;
 };
 hipError_t launch_batch_build(MeshDev &m, BatchDev &b, const float *V, const int32_t *F, hipStream_t s);
-hipError_t launch_collapse_batch(MeshDev &m, BatchDev &b, hipStream_t s);  // wide.hip
 
 // Build steps (build.hip).  All asynchronous on `s`.
 hipError_t launch_build(MeshDev &m, const float *V, const int32_t *F, hipStream_t s, size_t sort_tmp_bytes);
 size_t sort_tmp_bytes(int64_t nt, int morton_bits);
-hipError_t build_from_keys64(MeshDev &m, int key_bits, hipStream_t s);
+// Batched form, after the vertices, triangles and the meshes' extents: keys,
+// sort, radix tree (with the mesh roots) and boxes.
+hipError_t launch_build_batch(MeshDev &m, const BatchDev &b, hipStream_t s);
 // Treelet restructuring of a built radix tree (restructure.hip); needs the
 // tile list the radix-tree kernel left in m.sort_tmp.
+constexpr int kRestructureMin = 4;  // triangles below which there is nothing to restructure
 hipError_t launch_restructure(MeshDev &m, int rounds, hipStream_t s);
 hipError_t launch_collapse(MeshDev &m, hipStream_t s);  // wide.hip: the 4-wide tree
+hipError_t launch_collapse_batch(MeshDev &m, BatchDev &b, hipStream_t s);
 hipError_t launch_collapse_proposal(const MeshDev &m, Proposal &pr, hipStream_t s);  // ... of the proposal order
 
-// Lists kept in a mesh's sort scratch once the sort is done: the tile count
-// and tile list of the radix-tree kernel (subtrees of at most 1024 leaves), a
-// node queue and a flag per internal node (4-wide collapse).
+__device__ __forceinline__ void store_child_box(Node *node, bool is_left, const float *lo, const float *hi) {
+    if (is_left) {
+        node->xy_left = make_float4(lo[0], hi[0], lo[1], hi[1]);
+        *reinterpret_cast<float2 *>(&node->z_both.x) = make_float2(lo[2], hi[2]);
+    } else {
+        node->xy_right = make_float4(lo[0], hi[0], lo[1], hi[1]);
+        *reinterpret_cast<float2 *>(&node->z_both.z) = make_float2(lo[2], hi[2]);
+    }
+}
+
+
+// The boxes of the nodes above the tiles, by one workgroup (build.hip).
+__device__ __forceinline__ void boxes_above_tiles(Node *nodes, const int32_t *__restrict__ parent, int32_t *counters,
+                                                  const int32_t *__restrict__ tiles, int total, int n) {
+    for (int e = threadIdx.x; e < total; e += blockDim.x) {
+        const int c = tiles[e];
+        int p = c < 0 ? parent[(n - 1) + ~c] : parent[c];
+        for (int level = 0; p >= 0 && p < n - 1 && level < kDeepStack; ++level) {
+            if (__hip_atomic_fetch_add(counters + p, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
+                break;
+            const Node *node = nodes + p;
+            const float4 L = node->xy_left, R = node->xy_right, Z = node->z_both;
+            const float lo[3] = {fminf(L.x, R.x), fminf(L.z, R.z), fminf(Z.x, Z.z)};
+            const float hi[3] = {fmaxf(L.y, R.y), fmaxf(L.w, R.w), fmaxf(Z.y, Z.w)};
+            const int q = parent[p];
+            if (q < 0 || q >= n - 1)
+                break;  // p is the root
+            store_child_box(nodes + q, nodes[q].refs.x == p, lo, hi);
+            p = q;
+        }
+    }
+}
+
+// Lists kept in a mesh's sort scratch once the sort is done: the tiles (the
+// largest subtrees of at most kTileLeaves leaves) that the radix-tree kernel
+// lists, their number in flags[2], and in the batched form a flag per internal
+// node (kMeshRootFlag: a mesh's root).
 struct BuildLists {
-    int32_t *n_tiles, *tiles;
-    int32_t *queue, *tile_flag;
+    int32_t *n_tiles, *tiles, *flag;
 };
-// tile_flag bit of the internal nodes with at most 1024 leaves (set by the
-// radix-tree kernel; the tiles are the topmost of them)
-constexpr int32_t kTileRootFlag = 1;
+constexpr int kTileLeaves = 1024;
+constexpr int32_t kMeshRootFlag = 1;
+// Workgroups that reduce a mesh's extent at most.
+constexpr int kBoundsParts = 256;
+// An order-preserving integer form of a float, for atomic min / max.
+__device__ __forceinline__ uint32_t order_key(float f) {
+    const uint32_t u = __float_as_uint(f);
+    return (u >> 31) ? ~u : (u | 0x80000000u);
+}
+__device__ __forceinline__ float order_value(uint32_t k) {
+    return __uint_as_float((k >> 31) ? (k & 0x7fffffffu) : ~k);
+}
 inline int64_t round64(int64_t n) { return (n + 63) & ~int64_t(63); }
-inline BuildLists build_lists(void *sort_tmp, int64_t nt) {
+inline BuildLists build_lists(const MeshDev &m) {
     BuildLists L;
-    L.n_tiles = static_cast<int32_t *>(sort_tmp);
-    L.tiles = L.n_tiles + 64;
-    L.queue = L.tiles + round64(nt);
-    L.tile_flag = L.queue + round64(nt);
+    L.n_tiles = m.flags + 2;
+    L.tiles = static_cast<int32_t *>(m.sort_tmp);
+    L.flag = L.tiles + round64(m.nt);
     return L;
 }
-inline size_t build_lists_bytes(int64_t nt) { return 4 * (64 + 3 * (size_t)round64(nt)); }
-size_t restructure_lds_bytes();
+inline size_t build_lists_bytes(int64_t nt) { return 4 * 2 * (size_t)round64(nt); }
 // Stable sort of (32-bit key, id) pairs in place; tmp holds sort_u32_tmp_bytes(n).
 size_t sort_u32_tmp_bytes(int64_t n);
 hipError_t sort_u32_pairs(uint32_t *keys, int32_t *ids, void *tmp, int64_t n, hipStream_t s);
@@ -198,7 +242,6 @@ size_t compact_ws_bytes(int64_t n);
 hipError_t launch_compact(const float *from, const float *to, int64_t n, const int32_t *tri_id, const float *uvt,
                           int64_t *hit_index, float *dist, int32_t *hit_tri, float *point, int64_t *n_hits,
                           void *ws, hipStream_t s);
-hipError_t launch_morton_batch(MeshDev &m, const int32_t *tri_mesh, const float *mesh_bounds, hipStream_t s);
 
 // Intersection (traverse.hip).
 struct TraverseArgs {
