@@ -186,6 +186,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     // the last segments shared by the wave's lanes: where a pool of at least
     // 512 node entries fits in the wave's stacks
     constexpr bool kTail = WIDE && !STATS && MODE != MODE_COUNT;
+    int later = -1, later_root = 0, later_toff = 0, n_later = 0;  // segments put off to the wave's end
     const bool tail = kTail && wave_stack >= 512 + kPoolLeafCap + 64 && p.nt <= kMaxPoolTris;
     Ray r;
     // 4-wide: byte offsets in a node of the near-face rows (x lo or hi at 0 /
@@ -731,7 +732,29 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
             ref = lane_root == skip ? kDone : lane_root;
         }
 
-        // ---- finish lanes whose segment is decided
+        // ---- finish lanes whose segment is decided; one whose path outgrew the
+        // stack waits for the wave's end (lane k keeps the k-th of them)
+        if constexpr (kTail) {
+            const bool out = tail && ray >= 0 && ref == kDone && none_held() && overflow && !found;
+            for (uint64_t m = __ballot(out); m && n_later < 64; m &= m - 1) {
+                const int l = __builtin_ctzll(m);
+                const int who = __builtin_amdgcn_readlane((int)ray, l);
+                const int root = __builtin_amdgcn_readlane(lane_root, l);
+                const int toff = __builtin_amdgcn_readlane(lane_toff, l);
+                if (lane == n_later) {
+                    later = who;
+                    later_root = root;
+                    later_toff = toff;
+                }
+                ++n_later;
+                if (lane == l) {
+                    if (MODE == MODE_BOOL)
+                        put_hit(ray, 0u);  // written again then
+                    atomicAdd(p.counters + 1, 1ull);
+                    ray = -1;
+                }
+            }
+        }
         if (ray >= 0 && ref == kDone && none_held())
             finish();
         if (stage) {  // a complete older window goes out whole (then perhaps the next one)
@@ -746,36 +769,57 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     if constexpr (kTail) {
         // The wave's last segments: all lanes share them through a pool in the
         // wave's stack memory (pool.h).  They start again from the root,
-        // keeping the limit found so far.
-        if (__ballot(ray >= 0)) {
-            PoolSegment<MODE, CERT> s;
-            s.reset();
-            s.ray = (int)ray;
-            s.toff = 0;
-            s.o = r.o;
-            s.d = r.d;
-            s.inv = r.inv;
-            s.nn = nn;
-            s.nf = nf;
-            s.tlimit = tlimit;
-            s.best_id = best_id;
-            s.best_t = best_t;
-            s.best_u = best_u;
-            s.best_v = best_v;
-            s.best_lo = best_lo;
-            s.best_hi = best_hi;
-            s.best_exact = best_exact;
-            s.best_t64 = best_t64;
-            Pool<MODE, CERT, PROP> pool;
-            pool.init(p, reinterpret_cast<uint32_t *>(stk - lane), 64, wave_stack - kPoolLeafCap - 64);
-            pool.top_cache = top_cache;
-            pool.top_lds = p.top_lds;
+        // keeping the limit found so far.  Then those that outgrew their stack,
+        // from the beginning (the second pass takes 12 to 20 us for a queue of
+        // one segment).
+        Pool<MODE, CERT, PROP> pool;
+        pool.init(p, reinterpret_cast<uint32_t *>(stk - lane), 64, wave_stack - kPoolLeafCap - 64);
+        pool.top_cache = top_cache;
+        pool.top_lds = p.top_lds;
+        PoolSegment<MODE, CERT> s;
+        s.reset();
+        s.ray = (int)ray;
+        s.toff = 0;
+        s.o = r.o;
+        s.d = r.d;
+        s.inv = r.inv;
+        s.nn = nn;
+        s.nf = nf;
+        s.tlimit = tlimit;
+        s.best_id = best_id;
+        s.best_t = best_t;
+        s.best_u = best_u;
+        s.best_v = best_v;
+        s.best_lo = best_lo;
+        s.best_hi = best_hi;
+        s.best_exact = best_exact;
+        s.best_t64 = best_t64;
+        s.best_late = best_late;
+#pragma unroll 1
+        for (int turn = 0; turn < (n_later ? 2 : 1); ++turn) {
+            if (turn == 1) {
+                ray = lane < n_later ? later : -1;
+                s.reset();
+                s.ray = (int)ray;
+                n_redecided = 0;
+                if (ray >= 0) {
+                    lane_root = later_root;
+                    lane_toff = later_toff;
+                    (void)setup_ray(p.from, p.to, ray, scale, r);  // (finite: it was in flight before)
+                    s.set(r);
+                    if (PROP) {
+                        skip = p.bucket_ref[p.bucket[ray]];
+                        phase = 0;
+                    }
+                }
+            }
+            if (!__ballot(ray >= 0))
+                continue;
             const uint32_t tag = (uint32_t)lane << kPoolRefBits;
             bool rest = ray >= 0;
             wave_lds_fence();
             if (PROP) {  // the proposed subtree first, then what is left without it
                 s.late = phase == 1;
-                s.best_late = best_late;
                 pool.push(ray >= 0 && phase == 0, skip, tag);
                 wave_lds_fence();
                 pool.run(p, s, 0, 64);
@@ -789,6 +833,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
             if (ray >= 0) {
                 best_late = s.best_late;
                 found = MODE == MODE_BOOL && s.best_id >= 0;
+                flagged = false;
                 overflow = (pool.lost >> lane) & 1ull;
                 best_id = s.best_id;
                 best_t = s.best_t;
@@ -797,6 +842,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                 n_redecided += s.redecided;
                 finish();
             }
+            pool.lost = 0;
         }
     }
     if (stage) {  // every segment is finished: whatever is left in the windows
