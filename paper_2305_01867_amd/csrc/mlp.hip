@@ -93,112 +93,6 @@ __global__ __launch_bounds__(256) void k_features(const float *__restrict__ from
     coord_features(x, c, row);
 }
 
-// ------------------------------------------------- weight gradients
-// dW_l[n][k] = sum_r dZ_l[r][n] H_l[r][k] for the four layers in one launch:
-// workgroup z covers layer z / chunks over rows [c k_chunk, (c + 1) k_chunk)
-// of chunk c = z % chunks and a 128 x 128 tile of (n, k); four waves of
-// 64 x 64.  Both operands are the training pass's column-major arrays,
-// contiguous along r, staged through LDS kDStage rows at a time (the next
-// stage loads into registers while the current one multiplies); the sum over
-// r runs in r order.  A split writes raw partial sums [chunk][256][K_l],
-// added in chunk order by k_grad_finish; one chunk writes the gradient.
-constexpr int kSplitMax = 16;    // row chunks of the weight gradients at most
-constexpr int kSplitRows = 256;  // rows per chunk (a multiple of kDStage)
-constexpr int kDT = 128, kDStage = 128, kDPitch = kDStage + 8;
-constexpr size_t kDwLds = 2 * (size_t)kDT * kDPitch * sizeof(__bf16);
-
-struct DwArgs {
-    const __bf16 *A[4];  // dZ_l, [256][ld]
-    const __bf16 *B[4];  // the layer's input, [K_l][ld]
-    float *out[4];       // [chunks][256][K_l] partial sums, or the gradient (one chunk)
-    int64_t ld;
-    int k_chunk, chunks;
-};
-
-// rows [m0, m0 + 128) x r [r0, r0 + kDStage) of a [rows][ld] operand, 8 16-byte loads per lane
-__device__ __forceinline__ void dw_load(const __bf16 *__restrict__ P, int rows, int64_t ld, int m0, int r0, int rend,
-                                        int tid, bf16x8 (&v)[8]) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int idx = tid + 256 * q, m = idx >> 4, c = 8 * (idx & 15);
-        if (m0 + m < rows && r0 + c < rend)
-            v[q] = *reinterpret_cast<const bf16x8 *>(P + (int64_t)(m0 + m) * ld + r0 + c);
-        else
-            v[q] = bf16x8{};
-    }
-}
-
-__device__ __forceinline__ void dw_store(__bf16 *S, int tid, const bf16x8 (&v)[8]) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int idx = tid + 256 * q;
-        *reinterpret_cast<bf16x8 *>(S + (idx >> 4) * kDPitch + 8 * (idx & 15)) = v[q];
-    }
-}
-
-__global__ __launch_bounds__(256) void k_dw(DwArgs d) {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    __bf16 *As = reinterpret_cast<__bf16 *>(lds_raw);  // [kDT][kDPitch]: n x r
-    __bf16 *Bs = As + kDT * kDPitch;                    // [kDT][kDPitch]: k x r
-    const int layer = blockIdx.z / d.chunks, chunk = blockIdx.z % d.chunks;
-    const int N = kMlpOut, K = layer == 0 ? kMlpIn : kMlpHidden;
-    const int n0 = blockIdx.y * kDT, k0 = blockIdx.x * kDT;
-    if (k0 >= K)
-        return;  // layer 1 has fewer inputs; uniform per workgroup
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wn = (wave >> 1) * 64, wk = (wave & 1) * 64;
-    const int rb = chunk * d.k_chunk;
-    const int re = min((int)d.ld, rb + d.k_chunk);
-    const __bf16 *A = d.A[layer], *B = d.B[layer];
-    f32x4 acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    bf16x8 va[8], vb[8];
-    dw_load(A, N, d.ld, n0, rb, re, tid, va);
-    dw_load(B, K, d.ld, k0, rb, re, tid, vb);
-    const int kq = 8 * (lane >> 4);
-    for (int r0 = rb; r0 < re; r0 += kDStage) {
-        __syncthreads();  // the previous stage's reads are done
-        dw_store(As, tid, va);
-        dw_store(Bs, tid, vb);
-        __syncthreads();
-        if (r0 + kDStage < re) {
-            dw_load(A, N, d.ld, n0, r0 + kDStage, re, tid, va);
-            dw_load(B, K, d.ld, k0, r0 + kDStage, re, tid, vb);
-        }
-        const int steps = min(kDStage, re - r0) / 32;
-        for (int j = 0; j < steps; ++j) {
-            bf16x8 fa[4], fb[4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-                fa[a] = *reinterpret_cast<const bf16x8 *>(As + (wn + 16 * a + (lane & 15)) * kDPitch + 32 * j + kq);
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                fb[b] = *reinterpret_cast<const bf16x8 *>(Bs + (wk + 16 * b + (lane & 15)) * kDPitch + 32 * j + kq);
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    acc[a][b] = mfma16(fa[a], fb[b], acc[a][b]);
-        }
-    }
-    float *out = d.out[layer] + (int64_t)chunk * N * K;
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int n = n0 + wn + 16 * a + 4 * (lane >> 4) + i;
-                const int k = k0 + wk + 16 * b + (lane & 15);
-                if (n < N && k < K)
-                    out[(int64_t)n * K + k] = acc[a][b][i];
-            }
-}
-
 // Uniform(-a, a) initial weights from a counter-based hash (seed, index).
 __device__ __forceinline__ uint32_t mix32(uint64_t x) {
     x ^= x >> 33;
@@ -276,14 +170,14 @@ constexpr int kPThreads = 64 * kPWaves;
 constexpr int kPColTiles = kMlpHidden / 16 / kPWaves;  // 16-column tiles per wave
 constexpr int kPAhead = 2;                          // k steps the weight loads run ahead (1: 8.0 ms, 2: 7.6, 3: 7.6, 4: 7.7)
 
-template <int RT>
-__device__ __forceinline__ void tile_step(const __bf16 *__restrict__ xrow, int k0, const bf16x8 (&fb)[kPColTiles],
-                                          f32x4 (&acc)[RT][kPColTiles]) {
+template <int RT, int CT>
+__device__ __forceinline__ void tile_step(const __bf16 *__restrict__ xrow, int k0, const bf16x8 (&fb)[CT],
+                                          f32x4 (&acc)[RT][CT]) {
 #pragma unroll
     for (int a = 0; a < RT; ++a) {
         const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(xrow + 16 * a * kPPitch + k0);
 #pragma unroll
-        for (int b = 0; b < kPColTiles; ++b)
+        for (int b = 0; b < CT; ++b)
             acc[a][b] = mfma16(fa, fb[b], acc[a][b]);
     }
 }
@@ -320,7 +214,7 @@ __device__ __forceinline__ void layer_tile(const __bf16 *__restrict__ Xin, const
 #pragma unroll
             for (int b = 0; b < kPColTiles; ++b)
                 f[st + AHEAD][b] = *reinterpret_cast<const bf16x8 *>(wfrag + (int64_t)(b * kSteps + st + AHEAD) * 512);
-        tile_step<RT>(xrow, 32 * st, f[st], acc);
+        tile_step(xrow, 32 * st, f[st], acc);
         __builtin_amdgcn_sched_barrier(0);  // keep each step's loads in its step: no hoisting past the register budget
     }
 }
@@ -330,52 +224,52 @@ __device__ __forceinline__ void layer_tile(const __bf16 *__restrict__ Xin, const
 // (from Wn, with KN inputs; none when Wn is NULL) into pf, so a layer starts
 // without waiting on memory and the epilogue between two layers hides the
 // loads' latency.
-template <int KN, int AHEAD>
+template <int KN, int CT, int AHEAD>
 __device__ __forceinline__ void prefetch_layer(const __bf16 *__restrict__ Wn, int wave, int lane,
-                                               bf16x8 (&pf)[AHEAD][kPColTiles]) {
+                                               bf16x8 (&pf)[AHEAD][CT]) {
     constexpr int kStepsN = KN / 32;
-    const __bf16 *nfrag = Wn + (int64_t)kPColTiles * wave * kStepsN * 512 + 8 * lane;
+    const __bf16 *nfrag = Wn + (int64_t)CT * wave * kStepsN * 512 + 8 * lane;
 #pragma unroll
     for (int st = 0; st < AHEAD; ++st)
 #pragma unroll
-        for (int b = 0; b < kPColTiles; ++b)
+        for (int b = 0; b < CT; ++b)
             pf[st][b] = *reinterpret_cast<const bf16x8 *>(nfrag + (int64_t)(b * kStepsN + st) * 512);
 }
 
-template <int K, int KN, int RT, int AHEAD>
+template <int K, int KN, int RT, int CT, int AHEAD>
 __device__ __forceinline__ void layer_chain(const __bf16 *__restrict__ Xin, const __bf16 *__restrict__ Wt,
                                             const __bf16 *__restrict__ Wn, int wave, int lane,
-                                            f32x4 (&acc)[RT][kPColTiles], bf16x8 (&pf)[AHEAD][kPColTiles]) {
+                                            f32x4 (&acc)[RT][CT], bf16x8 (&pf)[AHEAD][CT]) {
     constexpr int kSteps = K / 32, kStepsN = KN / 32;
     static_assert(K % 32 == 0 && KN % 32 == 0 && AHEAD <= kSteps && AHEAD <= kStepsN, "whole k steps");
 #pragma unroll
     for (int a = 0; a < RT; ++a)
 #pragma unroll
-        for (int b = 0; b < kPColTiles; ++b)
+        for (int b = 0; b < CT; ++b)
             acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     const int kq = 8 * (lane >> 4);
-    const __bf16 *wfrag = Wt + (int64_t)kPColTiles * wave * kSteps * 512 + 8 * lane;
-    const __bf16 *nfrag = Wn ? Wn + (int64_t)kPColTiles * wave * kStepsN * 512 + 8 * lane : nullptr;
+    const __bf16 *wfrag = Wt + (int64_t)CT * wave * kSteps * 512 + 8 * lane;
+    const __bf16 *nfrag = Wn ? Wn + (int64_t)CT * wave * kStepsN * 512 + 8 * lane : nullptr;
     const __bf16 *xrow = Xin + (lane & 15) * kPPitch + kq;
-    bf16x8 f[kSteps][kPColTiles];
+    bf16x8 f[kSteps][CT];
 #pragma unroll
     for (int st = 0; st < AHEAD; ++st)
 #pragma unroll
-        for (int b = 0; b < kPColTiles; ++b)
+        for (int b = 0; b < CT; ++b)
             f[st][b] = pf[st][b];
 #pragma unroll
     for (int st = 0; st < kSteps; ++st) {
         if (st + AHEAD < kSteps) {
 #pragma unroll
-            for (int b = 0; b < kPColTiles; ++b)
+            for (int b = 0; b < CT; ++b)
                 f[st + AHEAD][b] = *reinterpret_cast<const bf16x8 *>(wfrag + (int64_t)(b * kSteps + st + AHEAD) * 512);
         } else if (nfrag) {
 #pragma unroll
-            for (int b = 0; b < kPColTiles; ++b)
+            for (int b = 0; b < CT; ++b)
                 pf[st + AHEAD - kSteps][b] =
                     *reinterpret_cast<const bf16x8 *>(nfrag + (int64_t)(b * kStepsN + st + AHEAD - kSteps) * 512);
         }
-        tile_step<RT>(xrow, 32 * st, f[st], acc);
+        tile_step(xrow, 32 * st, f[st], acc);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -500,17 +394,45 @@ constexpr size_t kProposeLds = (size_t)kPRows * kPPitch * sizeof(__bf16) + 2 * k
 // One workgroup per kTRows rows of a batch: the features, the four layers
 // forward, softmax cross-entropy and the chain of input gradients back to
 // the first layer, with the activations and gradients of the tile in LDS and
-// written out (bf16, column-major) for the weight gradients.  The layer
-// products run through layer_tile, the inference kernel's, so the logits
-// equal those of k_mlp_propose bit for bit.  A workgroup
-// also writes the column sums of each layer's gradient over its rows (the
-// bias gradients, added over the tiles in order by k_grad_finish) and the sum
-// of its rows' losses.  The backward products read the transposed copy of
-// the hidden weights, so both directions load 16 contiguous bytes per lane.
+// written out in bf16 for the weight gradients.  The layer
+// products accumulate over k as k_mlp_propose's do, so the logits equal its
+// logits bit for bit.  A workgroup also writes the column sums of each
+// layer's gradient over its rows (the bias gradients, added over the tiles in
+// order by k_wgrad) and the sum of its rows' losses.  The backward products
+// read the transposed copy of the hidden weights, so both directions load 16
+// contiguous bytes per lane.
+// A batch has fewer tiles than the chip has CUs, so a tile's chain of seven
+// dependent products is what counts; its floor is the stream of 0.9 MB of
+// weights through one CU's L2 port (64 B a clock: 6 us).  Eight waves of 32
+// columns each leave two waves per SIMD to hide each other's latencies, and
+// their loads run kTAhead k steps (and over the epilogues) ahead; hidden
+// activations and gradients go out from the registers that hold them instead
+// of being gathered from LDS; the ReLU masks stay in the lanes that need them
+// again; the layers are written out one after the other, because a branch on
+// the layer inside the epilogue made each wait for every load in flight (27 us).
+// At 3,168 rows (99 tiles) 23.6 us; with four waves of 64 columns, LDS gathers
+// and masks in LDS it took 33.9.  Of its 46,000 clocks the features take 6,000
+// (two dependent gathers), the seven products 1,300 to 2,000 each, their
+// epilogues about 2,000 each and the softmax 5,000 (both VALU issue).
 constexpr int kTRows = 32;
 constexpr int kTRowTiles = kTRows / 16;
-constexpr int kTAhead = 4;
-static_assert(kTRows % 16 == 0 && kTRows <= 64, "whole row tiles; the loss sum reads one row per lane");
+constexpr int kTWaves = 8;
+constexpr int kTThreads = 64 * kTWaves;
+constexpr int kTColTiles = kMlpHidden / 16 / kTWaves;
+constexpr int kTAhead = 4;  // 6 or 7: the same
+static_assert(kTRows == 32 && kTThreads == 2 * kMlpOut, "two lanes per column and one wave per four rows of the softmax");
+static_assert(3 * kTRowTiles * kTColTiles * 4 <= 64, "the ReLU masks of a lane fit one word");
+
+// The arrays that the weight gradients read have one 1 KB block per 16 columns
+// and tile of 32 rows, laid out as MFMA operands take it (lane l: column
+// l % 16, rows 8 (l / 16) .. + 7), so a wave loads a whole block with one
+// contiguous 16 bytes per lane.  (Column-major arrays, a 64-byte piece of 16
+// columns per load, made the gradient kernel 18.5 us at
+// 3,168 rows; these make it 9.7.)
+// Offset of rows 8 g .. 8 g + 7 of column col in tile `tile` of `tiles`:
+__device__ __forceinline__ int64_t tile_block(int col, int g, int tile, int tiles) {
+    return (((int64_t)(col >> 4) * tiles + tile) * 64 + (col & 15) + 16 * g) * 8;
+}
 
 struct TrainArgs {
     const float *from, *to;
@@ -522,10 +444,10 @@ struct TrainArgs {
     const __bf16 *Wb;    // [out][in] per layer
     const __bf16 *WbT;   // layers 2..4 transposed, [in][out]
     const float *bias;   // [4][256]
-    int64_t ld;          // rows rounded up to whole tiles: the row stride of the arrays below
-    __bf16 *X0;          // [224][ld]: the features, column-major
-    __bf16 *H;           // [3][256][ld]: the hidden activations, column-major
-    __bf16 *dZ;          // [4][256][ld]: gradients of the pre-activations, column-major
+    int tiles;           // ceil(rows / kTRows)
+    __bf16 *X0;          // 224 columns of features, in the blocks of tile_block
+    __bf16 *H;           // 3 x 256 columns: the hidden activations
+    __bf16 *dZ;          // 4 x 256 columns: gradients of the pre-activations
     float *logits;       // [rows][256], or NULL
     float *bias_part;    // [tiles][4][256]
     float *loss_part;    // [tiles]
@@ -533,32 +455,15 @@ struct TrainArgs {
 };
 
 // LDS: the activations (the logits later take their place and more), the
-// gradients, the ReLU masks as wave ballots in the MFMA output layout, and
-// the per-wave column sums and row losses of the softmax.
-constexpr int kTMaskWords = kTRowTiles * kPColTiles * 4 * 4;  // (row tile, col tile, i, wave) per layer
+// gradients and the row losses of the softmax.
 constexpr size_t kTActBytes = (size_t)kTRows * kPPitch * sizeof(__bf16);
 constexpr int kLPitch = kMlpOut + 16;  // logits row pitch (floats): four rows on disjoint LDS banks
 constexpr size_t kTLogitBytes = (size_t)kTRows * kLPitch * sizeof(float);
 static_assert(kTLogitBytes >= kTActBytes, "the logits take the activations' place");
-constexpr size_t kTrainLds = kTLogitBytes + kTActBytes + 3 * (size_t)kTMaskWords * sizeof(uint64_t) +
-                             4 * (size_t)kMlpOut * sizeof(float) + (size_t)kTRows * sizeof(float);
+constexpr size_t kTrainLds = kTLogitBytes + kTActBytes + (size_t)kTRows * sizeof(float);
 
-// The tile's rows of an LDS array (pitch kPPitch, `cols` columns) into a
-// column-major global array T[col][ld] at rows t0 .. t0 + kTRows (padding
-// rows go out too: zero features, zero gradients), 16 bytes per lane, four
-// lanes per column: the weight-gradient product then reads both operands
-// contiguous along the rows.
-__device__ __forceinline__ void copy_cols(const __bf16 *S, __bf16 *T, int64_t ld, int t0, int cols, int tid) {
-    constexpr int kG = kTRows / 8;
-    for (int i = tid; i < cols * kG; i += 256) {
-        const int col = i / kG, g = i % kG;
-        bf16x8 v;
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            v[j] = S[(8 * g + j) * kPPitch + col];
-        *reinterpret_cast<bf16x8 *>(T + (int64_t)col * ld + t0 + 8 * g) = v;
-    }
-}
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Max / sum over the 16 lanes of a DPP row, every lane ending with the same
 // value: rotations by 8, 4, 2 and 1 within the row, each step adding two
@@ -584,40 +489,61 @@ __device__ __forceinline__ float row16_sum(float v) {
     return v + dpp_ror(v, 1);
 }
 
-__global__ __launch_bounds__(256) void k_train_tile(TrainArgs a) {
+__global__ __launch_bounds__(kTThreads) void k_train_tile(TrainArgs a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __bf16 *X = reinterpret_cast<__bf16 *>(lds_raw);                  // activations [kTRows][kPPitch]
     float *L = reinterpret_cast<float *>(lds_raw);                     // logits [kTRows][256], over X
     __bf16 *D = reinterpret_cast<__bf16 *>(lds_raw + kTLogitBytes);    // gradients [kTRows][kPPitch]
-    uint64_t *Msk = reinterpret_cast<uint64_t *>(lds_raw + kTLogitBytes + kTActBytes);  // [3][kTMaskWords]
-    float *csum = reinterpret_cast<float *>(Msk + 3 * kTMaskWords);   // [4 waves][256]
-    float *rl = csum + 4 * kMlpOut;                                    // [kTRows] row losses
+    float *rl = reinterpret_cast<float *>(lds_raw + kTLogitBytes + kTActBytes);  // [kTRows] row losses
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g4 = lane >> 4, l16 = lane & 15;
     const int tile = blockIdx.x, t0 = tile * kTRows;
     const int nrows = min(kTRows, a.rows - t0);
-    // features; rows past the batch are zero
-    for (int q = tid; q < kTRows * 7; q += 256) {
-        const int r = q / 7, part = q % 7;
-        __bf16 *row = X + r * kPPitch;
-        if (part == 6) {
-            for (int j = kMlpFeat; j < kMlpIn; ++j)
+    // features: lane q of the first 384 has row q % 32, coordinate and half of
+    // the bands q / 32; the others write the padding.  Rows past the batch are
+    // zero.  Loads return in order: the segment's come first.
+    const int fr = tid & (kTRows - 1), fpart = tid / kTRows, fc = fpart >> 1;
+    float fp = 0.0f, flo = 0.0f, fhi = 0.0f;
+    if (fpart < 12 && fr < nrows) {
+        const int64_t br = a.r0 + t0 + fr;
+        const int64_t seg = a.seg ? a.seg[br] : br;
+        fp = seg_coord(a.from, a.to, seg, fc);
+        flo = a.bounds[fc % 3];
+        fhi = a.bounds[3 + fc % 3];
+    }
+    bf16x8 pf[kTAhead][kTColTiles];  // the next layer's first k steps, loaded ahead
+    prefetch_layer<kMlpIn, kTColTiles, kTAhead>(a.Wb, wave, lane, pf);
+    {
+        __bf16 *row = X + fr * kPPitch;
+        if (fpart >= 12) {
+            for (int j = kMlpFeat + fpart - 12; j < kMlpIn; j += kTThreads / kTRows - 12)
                 row[j] = (__bf16)0.0f;
-        } else if (r < nrows) {
-            const int64_t br = a.r0 + t0 + r;
-            const int64_t seg = a.seg ? a.seg[br] : br;
-            const float x = norm_coord(seg_coord(a.from, a.to, seg, part), a.bounds[part % 3], a.bounds[3 + part % 3]);
-            coord_features(x, part, row);
         } else {
-            row[part] = (__bf16)0.0f;
-            for (int k = 0; k < 2 * kMlpBands; ++k)
-                row[6 + part * 2 * kMlpBands + k] = (__bf16)0.0f;
+            const int k0 = (fpart & 1) * (kMlpBands / 2);
+            const float x = fr < nrows ? norm_coord(fp, flo, fhi) : 0.0f;
+            if (k0 == 0)
+                row[fc] = (__bf16)x;
+            for (int k = k0; k < k0 + kMlpBands / 2; ++k) {
+                float sn, cs;
+                sincospi_fast(band_freq(k) * x, sn, cs);
+                const bf16x2 v = {(__bf16)sn, (__bf16)(fr < nrows ? cs : 0.0f)};
+                *reinterpret_cast<bf16x2 *>(row + 6 + fc * 2 * kMlpBands + 2 * k) = v;
+            }
         }
     }
     __syncthreads();
-    copy_cols(X, a.X0, a.ld, t0, kMlpIn, tid);
+    // the features out, 16 bytes per lane, four lanes per column
+    for (int i = tid; i < kMlpIn * (kTRows / 8); i += kTThreads) {
+        const int col = (i & 15) + 16 * (i >> 6), g = (i >> 4) & 3;
+        bf16x8 v;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            v[j] = X[(8 * g + j) * kPPitch + col];
+        *reinterpret_cast<bf16x8 *>(a.X0 + tile_block(col, g, tile, a.tiles)) = v;
+    }
     // forward: each layer's output over its input in X once every wave has read it
-    f32x4 acc[kTRowTiles][kPColTiles];
-    bf16x8 pf[kTAhead][kPColTiles];  // the next layer's first k steps, loaded ahead
+    f32x4 acc[kTRowTiles][kTColTiles];
+    uint64_t relu = 0;  // where H_l > 0 in this lane's outputs, layer l in bits [16 l, 16 l + 16)
     auto wlayer = [&](int l) -> const __bf16 * {  // forward l = 0..3, then backward l = 3..1 as 4..6
         if (l == 0)
             return a.Wb;
@@ -625,58 +551,56 @@ __global__ __launch_bounds__(256) void k_train_tile(TrainArgs a) {
             return a.Wb + (int64_t)kMlpOut * kMlpIn + (int64_t)(l - 1) * kMlpHidden * kMlpHidden;
         return a.WbT + (int64_t)(6 - l) * kMlpHidden * kMlpHidden;
     };
-    prefetch_layer<kMlpIn, kTAhead>(a.Wb, wave, lane, pf);
-#pragma unroll 1
-    for (int l = 0; l < 4; ++l) {
-        const float *bl = a.bias + l * kMlpHidden;
-        float bvs[kPColTiles];  // this layer's biases, loaded while it multiplies
+    float bvs[4][kTColTiles];
 #pragma unroll
-        for (int b = 0; b < kPColTiles; ++b)
-            bvs[b] = bl[16 * kPColTiles * wave + 16 * b + (lane & 15)];
-        if (l == 0)
-            layer_chain<kMlpIn, kMlpHidden, kTRowTiles, kTAhead>(X, wlayer(0), wlayer(1), wave, lane, acc, pf);
-        else
-            layer_chain<kMlpHidden, kMlpHidden, kTRowTiles, kTAhead>(X, wlayer(l), wlayer(l + 1), wave, lane, acc, pf);
+    for (int l = 0; l < 4; ++l)
+#pragma unroll
+        for (int b = 0; b < kTColTiles; ++b)
+            bvs[l][b] = a.bias[l * kMlpHidden + 16 * kTColTiles * wave + 16 * b + l16];
+    // a hidden layer's outputs into X and out
+    auto hidden = [&](int l, const float(&bv)[kTColTiles]) {
         __syncthreads();
+        __bf16 *out = a.H + tile_block(l * kMlpHidden + 16 * kTColTiles * wave + l16, g4 >> 1, tile, a.tiles) + 4 * (g4 & 1);
+        uint32_t on = 0;
 #pragma unroll
-        for (int b = 0; b < kPColTiles; ++b) {
-            const int col = 16 * kPColTiles * wave + 16 * b + (lane & 15);
-            const float bv = bvs[b];
+        for (int b = 0; b < kTColTiles; ++b)
 #pragma unroll
-            for (int t = 0; t < kTRowTiles; ++t)
+            for (int t = 0; t < kTRowTiles; ++t) {
+                bf16x4 hv;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int row = 16 * t + 4 * (lane >> 4) + i;
-                    const float v = acc[t][b][i] + bv;
-                    if (l < 3) {
-                        const __bf16 h = (__bf16)fmaxf(v, 0.0f);
-                        X[row * kPPitch + col] = h;
-                        // ReLU mask of the backward pass, kept in the layout its epilogue reads
-                        const uint64_t m = __ballot((float)h > 0.0f);
-                        if (lane == 0)
-                            Msk[l * kTMaskWords + ((t * kPColTiles + b) * 4 + i) * 4 + wave] = m;
-                    } else {
-                        L[row * kLPitch + col] = v;
-                    }
+                    hv[i] = (__bf16)fmaxf(acc[t][b][i] + bv[b], 0.0f);
+                    X[(16 * t + 4 * g4 + i) * kPPitch + 16 * kTColTiles * wave + 16 * b + l16] = hv[i];
+                    on |= (uint32_t)((float)hv[i] > 0.0f) << (4 * (t * kTColTiles + b) + i);
                 }
-        }
+                *reinterpret_cast<bf16x4 *>(out + (int64_t)b * a.tiles * 512 + 256 * t) = hv;
+            }
+        relu |= (uint64_t)on << (16 * l);
         __syncthreads();
-        if (l < 3)
-            copy_cols(X, a.H + (int64_t)l * kMlpHidden * a.ld, a.ld, t0, kMlpHidden, tid);
-        else if (a.logits)
-            for (int i = tid; i < nrows * kMlpOut; i += 256)
-                a.logits[(int64_t)t0 * kMlpOut + i] = L[(i / kMlpOut) * kLPitch + i % kMlpOut];
-    }
-    // softmax cross-entropy: four rows of a wave at a time, 16 lanes (one DPP
-    // row) per row, lane l16 holding columns l16 + 16 j
-    const int g4 = lane >> 4, l16 = lane & 15;
-    float cs[16];  // this lane's column sums of the bf16 gradient over its rows
+    };
+    layer_chain<kMlpIn, kMlpHidden, kTRowTiles, kTColTiles, kTAhead>(X, wlayer(0), wlayer(1), wave, lane, acc, pf);
+    hidden(0, bvs[0]);
+    layer_chain<kMlpHidden, kMlpHidden, kTRowTiles, kTColTiles, kTAhead>(X, wlayer(1), wlayer(2), wave, lane, acc, pf);
+    hidden(1, bvs[1]);
+    layer_chain<kMlpHidden, kMlpHidden, kTRowTiles, kTColTiles, kTAhead>(X, wlayer(2), wlayer(3), wave, lane, acc, pf);
+    hidden(2, bvs[2]);
+    layer_chain<kMlpHidden, kMlpHidden, kTRowTiles, kTColTiles, kTAhead>(X, wlayer(3), wlayer(4), wave, lane, acc, pf);
+    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 16; ++j)
-        cs[j] = 0.0f;
+    for (int b = 0; b < kTColTiles; ++b)
 #pragma unroll
-    for (int p = 0; p < kTRows / 16; ++p) {
-        const int row = (kTRows / 4) * wave + 4 * p + g4;
+        for (int t = 0; t < kTRowTiles; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                L[(16 * t + 4 * g4 + i) * kLPitch + 16 * kTColTiles * wave + 16 * b + l16] = acc[t][b][i] + bvs[3][b];
+    __syncthreads();
+    if (a.logits)
+        for (int i = tid; i < nrows * kMlpOut; i += kTThreads)
+            a.logits[(int64_t)t0 * kMlpOut + i] = L[(i / kMlpOut) * kLPitch + i % kMlpOut];
+    // softmax cross-entropy: a wave has four rows, 16 lanes (one DPP row)
+    // each, lane l16 holding columns l16 + 16 j
+    {
+        const int row = 4 * wave + g4;
         const float *z = L + row * kLPitch;
         float v[16];
         float mx = -INFINITY;
@@ -700,29 +624,35 @@ __global__ __launch_bounds__(256) void k_train_tile(TrainArgs a) {
         for (int j = 0; j < 16; ++j) {
             const int c = l16 + 16 * j;
             const float g = valid && c < a.nb ? (v[j] / sum - (c == label ? 1.0f : 0.0f)) * a.inv_rows : 0.0f;
-            const __bf16 gb = (__bf16)g;
-            D[row * kPPitch + c] = gb;
-            cs[j] += (float)gb;
+            D[row * kPPitch + c] = (__bf16)g;
         }
         if (l16 == 0)
             rl[row] = valid && label >= 0 && label < a.nb ? (logf(sum) + mx - z[label]) * a.loss_scale : 0.0f;
     }
-    // the wave's column sums: add the four lane groups
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        float x = cs[j];
-        x += __shfl_xor(x, 16);
-        x += __shfl_xor(x, 32);
-        cs[j] = x;
-    }
-    if (lane < 16)
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            csum[wave * kMlpOut + l16 + 16 * j] = cs[j];
     __syncthreads();
-    copy_cols(D, a.dZ + (int64_t)3 * kMlpOut * a.ld, a.ld, t0, kMlpOut, tid);
-    a.bias_part[((int64_t)tile * 4 + 3) * kMlpOut + tid] =
-        ((csum[tid] + csum[kMlpOut + tid]) + csum[2 * kMlpOut + tid]) + csum[3 * kMlpOut + tid];
+    // the logits' gradient out, and its column sums in a fixed order:
+    // two lanes per column, 16 rows each; of eight rows, r and r + 4 first,
+    // then neighbours, then pairs; the four eights one after the other
+    {
+        const int col = tid >> 1, half = tid & 1;
+        bf16x8 v[2];
+        float e8[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                v[q][j] = D[(16 * half + 8 * q + j) * kPPitch + col];
+            float c4[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                c4[j] = (0.0f + (float)v[q][j]) + (float)v[q][j + 4];
+            e8[q] = (c4[0] + c4[1]) + (c4[2] + c4[3]);
+            *reinterpret_cast<bf16x8 *>(a.dZ + tile_block(3 * kMlpOut + col, 2 * half + q, tile, a.tiles)) = v[q];
+        }
+        const float e2 = __shfl_xor(e8[0], 1), e3 = __shfl_xor(e8[1], 1);
+        if (half == 0)
+            a.bias_part[((int64_t)tile * 4 + 3) * kMlpOut + col] = ((e8[0] + e8[1]) + e2) + e3;
+    }
     if (wave == 0) {
         float v = lane < kTRows ? rl[lane] : 0.0f;
         for (int off = 32; off > 0; off >>= 1)
@@ -733,98 +663,241 @@ __global__ __launch_bounds__(256) void k_train_tile(TrainArgs a) {
     // backward: dZ(l - 1) = (dZ(l) W_l) where H_l > 0, in place in D; the
     // column sums (bias gradients) from the registers, over the lanes that
     // share a column
-#pragma unroll 1
-    for (int l = 3; l > 0; --l) {
-        layer_chain<kMlpHidden, kMlpHidden, kTRowTiles, kTAhead>(D, wlayer(7 - l), l > 1 ? wlayer(8 - l) : nullptr,
-                                                                 wave, lane, acc, pf);
+    auto back = [&](int l) {  // dZ(l) from acc
         __syncthreads();
-        const uint64_t *mk = Msk + (l - 1) * kTMaskWords;
+        __bf16 *out = a.dZ + tile_block(l * kMlpOut + 16 * kTColTiles * wave + l16, g4 >> 1, tile, a.tiles) + 4 * (g4 & 1);
+        const uint32_t on = (uint32_t)(relu >> (16 * l));
 #pragma unroll
-        for (int b = 0; b < kPColTiles; ++b) {
-            const int col = 16 * kPColTiles * wave + 16 * b + (lane & 15);
+        for (int b = 0; b < kTColTiles; ++b) {
+            const int col = 16 * kTColTiles * wave + 16 * b + l16;
             float colsum = 0.0f;
 #pragma unroll
-            for (int t = 0; t < kTRowTiles; ++t)
+            for (int t = 0; t < kTRowTiles; ++t) {
+                bf16x4 gv;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int row = 16 * t + 4 * (lane >> 4) + i;
-                    const bool on = (mk[((t * kPColTiles + b) * 4 + i) * 4 + wave] >> lane) & 1ull;
-                    const __bf16 gb = (__bf16)(on ? acc[t][b][i] : 0.0f);
-                    D[row * kPPitch + col] = gb;
-                    colsum += (float)gb;
+                    gv[i] = (__bf16)((on >> (4 * (t * kTColTiles + b) + i)) & 1u ? acc[t][b][i] : 0.0f);
+                    if (l > 0)
+                        D[(16 * t + 4 * g4 + i) * kPPitch + col] = gv[i];
+                    colsum += (float)gv[i];
                 }
+                *reinterpret_cast<bf16x4 *>(out + (int64_t)b * a.tiles * 512 + 256 * t) = gv;
+            }
             colsum += __shfl_xor(colsum, 16);
             colsum += __shfl_xor(colsum, 32);
             if (lane < 16)
-                a.bias_part[((int64_t)tile * 4 + (l - 1)) * kMlpOut + col] = colsum;
+                a.bias_part[((int64_t)tile * 4 + l) * kMlpOut + col] = colsum;
         }
-        __syncthreads();
-        copy_cols(D, a.dZ + (int64_t)(l - 1) * kMlpOut * a.ld, a.ld, t0, kMlpOut, tid);
-    }
+    };
+    layer_chain<kMlpHidden, kMlpHidden, kTRowTiles, kTColTiles, kTAhead>(D, wlayer(4), wlayer(5), wave, lane, acc, pf);
+    back(2);
+    __syncthreads();
+    layer_chain<kMlpHidden, kMlpHidden, kTRowTiles, kTColTiles, kTAhead>(D, wlayer(5), wlayer(6), wave, lane, acc, pf);
+    back(1);
+    __syncthreads();
+    layer_chain<kMlpHidden, kMlpHidden, kTRowTiles, kTColTiles, kTAhead>(D, wlayer(6), nullptr, wave, lane, acc, pf);
+    back(0);
 }
 
-// The gradient of every parameter: a weight's split-K partial sums added in
-// chunk order (or the value already in G), a bias's tile sums added in tile
-// order; the loss parts added in tile order.  With adam set, the Adam step on
-// the fp32 master parameters and the bf16 copies follow.
-struct FinishArgs {
-    const float *split;  // [4][kSplitMax][256][256] partials, or NULL: the weight gradients are in G
-    int chunks;
-    const float *bias_part;
+// ------------------------------- weight gradients and the parameter step
+// dW_l[n][k] = sum_r dZ_l[r][n] H_l[r][k] for the four layers, the sums of the
+// bias and loss parts, and with `adam` the Adam step on the fp32 masters and
+// the bf16 copies, in one launch.  Both operands come in the blocks
+// of tile_block, one per MFMA operand: no staging.  A workgroup makes a 32 x 32 tile of
+// one layer (248 of them: about one per CU), wave c the sum over row chunk c
+// of k_chunk rows (in r order, one accumulator per 16 x 16); the chunks are
+// then added in chunk order from LDS and the step follows in the same lanes,
+// so no partial sum leaves the CU.  XCD x (workgroups are dealt round-robin)
+// gets tiles [31 x, 31 x + 31), half of one layer: 1.2 MB of operands in its
+// L2 at 3,168 rows instead of all 13 MB.
+// What bounds it is latency: two round trips to memory, the tile sum and the
+// Adam traffic (7 MB).  At 3,168 rows 9.7 us; 128 x 128 tiles over the same
+// chunks, their partial sums (13.6 MB) through memory and a second launch to
+// add them took 12.1 + 10.1 us.
+constexpr int kSplitMax = 16;    // row chunks at most: a wave each
+constexpr int kSplitRows = 256;  // rows per chunk, up to kSplitMax of them
+constexpr int kChunkUnit = 128;  // chunks are whole multiples of this many rows
+constexpr int kWT = 32;          // tile edge
+constexpr int kWAhead = 4;       // row tiles in flight per wave (2: the same, 6: 40.8 us a batch of 4,096 instead of 36.0)
+constexpr int kWTilesFirst = (kMlpOut / kWT) * (kMlpIn / kWT), kWTilesHidden = (kMlpOut / kWT) * (kMlpHidden / kWT);
+constexpr int kWTiles = kWTilesFirst + 3 * kWTilesHidden;
+static_assert(kMlpOut % kWT == 0 && kMlpIn % kWT == 0 && kMlpHidden % kWT == 0 && kWTiles % 8 == 0, "whole tiles, dealt to 8 XCDs");
+static_assert(kMlpOut <= 256, "the bias workgroups");
+constexpr int kStepThreads = kWT * kWT / 4;  // lanes that make the Adam step, four parameters each
+constexpr int kWPitch = kWT + 8;
+static_assert(kStepThreads == 256 && 2 * kWT * kWPitch * sizeof(__bf16) <= 2 * kWT * kWT * sizeof(float), "the step's lanes and LDS");
+constexpr size_t kWgradLds = (size_t)kSplitMax * kWT * kWT * sizeof(float);
+
+struct GradArgs {
+    const __bf16 *X0, *H, *dZ;  // as in TrainArgs; padding rows have zero gradients
     int tiles;
+    int chunk_tiles, chunks;    // tiles per row chunk
+    const float *bias_part;
     const float *loss_part;
     float *loss;
-    float *G;
+    float *G;                   // without the step: the gradient
     int adam;
     float *P, *m1, *m2;
     __bf16 *Wb, *WbT;
     float lr, b1, b2, eps, c1, c2;
 };
 
-__global__ __launch_bounds__(256) void k_grad_finish(FinishArgs f) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0 && f.loss) {
-        float sum = 0.0f;
-#pragma unroll 32
-        for (int t = 0; t < f.tiles; ++t)
-            sum += f.loss_part[t];
-        *f.loss += sum;
-    }
-    if (i >= kMlpParams)
-        return;
-    float g;
-    if (i < kMlpWeights) {
-        if (f.split) {
-            const int64_t first = (int64_t)kMlpOut * kMlpIn, hh = (int64_t)kMlpHidden * kMlpHidden;
-            const int l = i < first ? 0 : 1 + (int)((i - first) / hh);
-            const int64_t j = i < first ? i : (i - first) % hh;
-            const int64_t mn = l == 0 ? first : hh;
-            const float *pp = f.split + (int64_t)l * kSplitMax * kMlpOut * kMlpHidden + j;
-            g = 0.0f;
-#pragma unroll 4
-            for (int z = 0; z < f.chunks; ++z)
-                g += pp[z * mn];
-        } else {
-            g = f.G[i];
+// one parameter's step from its gradient; m, v and w in and out
+__device__ __forceinline__ void adam_step(const GradArgs &f, float g, float &m, float &v, float &w) {
+#pragma clang fp contract(off)
+    m = __builtin_fmaf(1.0f - f.b1, g, f.b1 * m);
+    v = __builtin_fmaf((1.0f - f.b2) * g, g, f.b2 * v);
+    w = w - f.lr * (m * f.c1) / (sqrtf(v * f.c2) + f.eps);
+}
+
+__global__ __launch_bounds__(64 * kSplitMax) void k_wgrad(GradArgs f) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    float *part = reinterpret_cast<float *>(lds_raw);  // [chunks][kWT][kWT]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nthr = blockDim.x;
+    if (blockIdx.x >= kWTiles) {  // the biases of a layer, or the loss: the tiles' parts in tile order
+        const int l = blockIdx.x - kWTiles;
+        if (l < 4) {
+            if (tid < kMlpOut) {
+                const int i = l * kMlpOut + tid;
+                float g = 0.0f, m = 0.0f, v = 0.0f, w = 0.0f;
+                if (f.adam) {
+                    m = f.m1[kMlpWeights + i];
+                    v = f.m2[kMlpWeights + i];
+                    w = f.P[kMlpWeights + i];
+                }
+                for (int t0 = 0; t0 < f.tiles; t0 += 32) {  // 32 loads in flight, also in the last round
+                    float x[32];
+#pragma unroll
+                    for (int t = 0; t < 32; ++t)
+                        x[t] = f.bias_part[(int64_t)min(t0 + t, f.tiles - 1) * 4 * kMlpOut + i];
+#pragma unroll
+                    for (int t = 0; t < 32; ++t)
+                        g += t0 + t < f.tiles ? x[t] : 0.0f;
+                }
+                const int64_t q = kMlpWeights + i;
+                if (f.adam) {
+                    adam_step(f, g, m, v, w);
+                    f.m1[q] = m;
+                    f.m2[q] = v;
+                    f.P[q] = w;
+                } else {
+                    f.G[q] = g;
+                }
+            }
+        } else if (f.loss) {
+            float sum = 0.0f;
+            for (int b0 = 0; b0 < f.tiles; b0 += nthr) {
+                const int m = min(nthr, f.tiles - b0);
+                if (tid < m)
+                    part[tid] = f.loss_part[b0 + tid];
+                __syncthreads();
+                if (tid == 0)
+                    for (int t = 0; t < m; ++t)
+                        sum += part[t];
+                __syncthreads();
+            }
+            if (tid == 0)
+                *f.loss += sum;
         }
-    } else {
-        const int b = (int)(i - kMlpWeights), l = b / kMlpHidden, n = b % kMlpHidden;
-        g = 0.0f;
-#pragma unroll 32
-        for (int t = 0; t < f.tiles; ++t)
-            g += f.bias_part[((int64_t)t * 4 + l) * kMlpOut + n];
+        return;
     }
-    f.G[i] = g;
+    const int t = (blockIdx.x & 7) * (kWTiles / 8) + (blockIdx.x >> 3);
+    const int layer = t < kWTilesFirst ? 0 : 1 + (t - kWTilesFirst) / kWTilesHidden;
+    const int K = layer == 0 ? kMlpIn : kMlpHidden;
+    const int tl = layer == 0 ? t : (t - kWTilesFirst) % kWTilesHidden;
+    const int n0 = tl / (K / kWT) * kWT, k0 = tl % (K / kWT) * kWT;
+    const int64_t woff = layer == 0 ? 0 : (int64_t)kMlpOut * kMlpIn + (int64_t)(layer - 1) * kMlpHidden * kMlpHidden;
+    // the first kStepThreads lanes make the step for four parameters each:
+    // their state loads while the products run
+    const int n = n0 + tid / (kWT / 4), k = k0 + 4 * (tid % (kWT / 4));
+    const int64_t at = woff + (int64_t)n * K + k;
+    f32x4 m = {0, 0, 0, 0}, v2 = m, w = m;
+    if (tid < kStepThreads && f.adam) {
+        m = *reinterpret_cast<const f32x4 *>(f.m1 + at);
+        v2 = *reinterpret_cast<const f32x4 *>(f.m2 + at);
+        w = *reinterpret_cast<const f32x4 *>(f.P + at);
+    }
+    if (wave < f.chunks) {
+        const int64_t col_tile = (int64_t)f.tiles * 512;  // elements of a column tile
+        const __bf16 *A = f.dZ + (layer * (kMlpOut / 16) + (n0 >> 4)) * col_tile + 8 * lane;
+        const __bf16 *B = (layer == 0 ? f.X0 : f.H + (layer - 1) * (kMlpHidden / 16) * col_tile) +
+                          (k0 >> 4) * col_tile + 8 * lane;
+        const int tb = wave * f.chunk_tiles, te = min(f.tiles, tb + f.chunk_tiles);
+        f32x4 acc[2][2] = {{{0, 0, 0, 0}, {0, 0, 0, 0}}, {{0, 0, 0, 0}, {0, 0, 0, 0}}};
+        bf16x8 v[kWAhead][4];  // [tile ahead][A low, A high, B low, B high]
+        auto load = [&](int t, bf16x8(&d)[4]) {
+            const int64_t o = (int64_t)t * 512;
+            d[0] = *reinterpret_cast<const bf16x8 *>(A + o);
+            d[1] = *reinterpret_cast<const bf16x8 *>(A + col_tile + o);
+            d[2] = *reinterpret_cast<const bf16x8 *>(B + o);
+            d[3] = *reinterpret_cast<const bf16x8 *>(B + col_tile + o);
+        };
+#pragma unroll
+        for (int q = 0; q < kWAhead; ++q)
+            if (tb + q < te)
+                load(tb + q, v[q]);
+        for (int t = tb; t < te; t += kWAhead) {
+#pragma unroll
+            for (int q = 0; q < kWAhead; ++q) {
+                if (t + q >= te)
+                    break;
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[a][b] = mfma16(v[q][a], v[q][2 + b], acc[a][b]);
+                if (t + q + kWAhead < te)
+                    load(t + q + kWAhead, v[q]);
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    part[(wave * kWT + 16 * a + 4 * (lane >> 4) + i) * kWT + 16 * b + (lane & 15)] = acc[a][b][i];
+    }
+    __syncthreads();
+    f32x4 g = {0, 0, 0, 0};
+    if (tid < kStepThreads) {
+        for (int c = 0; c < f.chunks; ++c)
+            g += *reinterpret_cast<const f32x4 *>(part + c * kWT * kWT + 4 * tid);
+        if (!f.adam)
+            *reinterpret_cast<f32x4 *>(f.G + at) = g;
+    }
     if (!f.adam)
         return;
-    const float m = f.b1 * f.m1[i] + (1.0f - f.b1) * g;
-    const float v = f.b2 * f.m2[i] + (1.0f - f.b2) * g * g;
-    f.m1[i] = m;
-    f.m2[i] = v;
-    const float w = f.P[i] - f.lr * (m * f.c1) / (sqrtf(v * f.c2) + f.eps);
-    f.P[i] = w;
-    if (i < kMlpWeights)
-        store_weight(f.Wb, f.WbT, i, w);
+    __syncthreads();  // the partial sums have been read
+    // the new weights, n-major and k-major in bf16, for the two fragment orders
+    __bf16 *tn = reinterpret_cast<__bf16 *>(lds_raw), *tk = tn + kWT * kWPitch;
+    if (tid < kStepThreads) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float mq = m[q], vq = v2[q], wq = w[q];
+            adam_step(f, g[q], mq, vq, wq);
+            m[q] = mq;
+            v2[q] = vq;
+            w[q] = wq;
+            const __bf16 h = (__bf16)wq;
+            tn[(n - n0) * kWPitch + k - k0 + q] = h;
+            tk[(k - k0 + q) * kWPitch + n - n0] = h;
+        }
+        *reinterpret_cast<f32x4 *>(f.m1 + at) = m;
+        *reinterpret_cast<f32x4 *>(f.m2 + at) = v2;
+        *reinterpret_cast<f32x4 *>(f.P + at) = w;
+    }
+    __syncthreads();
+    if (tid < kStepThreads) {  // 16 bytes each: 128 lanes for Wb, 128 for WbT
+        const int o = (tid & 127) >> 2, c = 8 * (tid & 3);
+        if (tid < 128)
+            *reinterpret_cast<bf16x8 *>(f.Wb + woff + frag_index(n0 + o, k0 + c, K)) =
+                *reinterpret_cast<const bf16x8 *>(tn + o * kWPitch + c);
+        else if (layer > 0)
+            *reinterpret_cast<bf16x8 *>(f.WbT + (int64_t)(layer - 1) * kMlpHidden * kMlpHidden +
+                                        frag_index(k0 + o, n0 + c, kMlpOut)) =
+                *reinterpret_cast<const bf16x8 *>(tk + o * kWPitch + c);
+    }
 }
 
 // ------------------------------------------------ frontier and labels
@@ -1033,22 +1106,21 @@ hipError_t proposal_predict(const MeshDev &m, const Proposal &pr, const float *f
 }
 
 // Forward + backward of one batch (rows segments listed in seg[r0..r0+rows),
-// labels lab[r0..]) in three launches: k_train_tile (features, forward,
-// softmax cross-entropy, input gradients and bias / loss parts per tile of
-// kTRows rows), k_gemm4 (every layer's weight gradient, split over the rows)
-// and k_grad_finish (the sums in fixed order into pr.G, the loss, and with
-// `adam` the Adam step).  ws must hold proposal_batch_scratch(rows) bytes.
+// labels lab[r0..]) in two launches: k_train_tile (features, forward, softmax
+// cross-entropy, input gradients and bias / loss parts per tile of kTRows
+// rows) and k_wgrad (every layer's weight gradient and the sums in fixed
+// order; into pr.G without `adam`, else the Adam step).  ws must hold
+// proposal_batch_scratch(rows) bytes.
 hipError_t proposal_batch_grad(const MeshDev &m, Proposal &pr, const float *from, const float *to,
                                const int32_t *seg, const int32_t *lab, int64_t r0, int rows, int nb, float *loss,
                                float loss_scale, char *ws, hipStream_t s, float *logits_out, const AdamStep *adam) {
     const int tiles = cdiv(rows, kTRows);
     const int64_t ld = (int64_t)tiles * kTRows;
-    __bf16 *X0 = reinterpret_cast<__bf16 *>(ws);           // [224][ld]
-    __bf16 *H = X0 + ld * kMlpIn;                          // [3][256][ld]
-    __bf16 *dZ0 = H + 3 * ld * kMlpHidden;                 // [4][256][ld]
-    float *split = reinterpret_cast<float *>(dZ0 + 4 * ld * kMlpOut);  // [4][kSplitMax][256][256]
-    float *bias_part = split + 4 * (int64_t)kSplitMax * kMlpOut * kMlpHidden;       // [tiles][4][256]
-    float *loss_part = bias_part + (int64_t)tiles * 4 * kMlpOut;                   // [tiles]
+    __bf16 *X0 = reinterpret_cast<__bf16 *>(ws);  // 224 columns of ld rows
+    __bf16 *H = X0 + ld * kMlpIn;                 // 3 x 256 columns
+    __bf16 *dZ0 = H + 3 * ld * kMlpHidden;        // 4 x 256 columns
+    float *bias_part = reinterpret_cast<float *>(dZ0 + 4 * ld * kMlpOut);  // [tiles][4][256]
+    float *loss_part = bias_part + (int64_t)tiles * 4 * kMlpOut;           // [tiles]
     TrainArgs a{};
     a.from = from;
     a.to = to;
@@ -1061,7 +1133,7 @@ hipError_t proposal_batch_grad(const MeshDev &m, Proposal &pr, const float *from
     a.Wb = pr.Wb;
     a.WbT = pr.WbT;
     a.bias = pr.P + kMlpWeights;
-    a.ld = ld;
+    a.tiles = tiles;
     a.X0 = X0;
     a.H = H;
     a.dZ = dZ0;
@@ -1070,44 +1142,19 @@ hipError_t proposal_batch_grad(const MeshDev &m, Proposal &pr, const float *from
     a.loss_part = loss_part;
     a.inv_rows = 1.0f / rows;
     a.loss_scale = loss_scale > 0.0f ? loss_scale : 1.0f / rows;
-    // above the default 64 KB of dynamic LDS: set per call (cheap on the
-    // host, right for whichever device is current)
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_train_tile),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTrainLds);
-    if (e != hipSuccess)
-        return e;
-    k_train_tile<<<tiles, 256, kTrainLds, s>>>(a);
-    // every layer's weight gradient in one launch, split over the rows (a
-    // batch of at most kSplitRows rows is not split: its sums go straight to
-    // the gradient); padding rows add exact zeros, their gradients being zero
-    float *G = pr.G;
-    DwArgs dw{};
-    dw.ld = ld;
-    dw.chunks = ld > kSplitRows ? cdiv(ld, kSplitRows) : 1;
-    if (dw.chunks > kSplitMax)
-        dw.chunks = kSplitMax;
-    dw.k_chunk = cdiv(cdiv(ld, dw.chunks), kDStage) * kDStage;
-    dw.chunks = cdiv(ld, dw.k_chunk);
-    const bool split_k = dw.chunks > 1;
-    for (int l = 0; l < 4; ++l) {
-        const int64_t woff = l == 0 ? 0 : (int64_t)kMlpOut * kMlpIn + (int64_t)(l - 1) * kMlpHidden * kMlpHidden;
-        dw.A[l] = dZ0 + (int64_t)l * kMlpOut * ld;
-        dw.B[l] = l == 0 ? X0 : H + (int64_t)(l - 1) * kMlpHidden * ld;
-        dw.out[l] = split_k ? split + (int64_t)l * kSplitMax * kMlpOut * kMlpHidden : G + woff;
-    }
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_dw), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kDwLds);
-    if (e != hipSuccess)
-        return e;
-    k_dw<<<dim3(cdiv(kMlpHidden, kDT), cdiv(kMlpOut, kDT), 4 * dw.chunks), 256, kDwLds, s>>>(dw);
-    FinishArgs f{};
-    f.split = split_k ? split : nullptr;
-    f.chunks = dw.chunks;
+    static_assert(kTrainLds <= 64 * 1024 && kWgradLds <= 64 * 1024, "both fit the default dynamic LDS");
+    k_train_tile<<<tiles, kTThreads, kTrainLds, s>>>(a);
+    GradArgs f{};
+    f.X0 = X0;
+    f.H = H;
+    f.dZ = dZ0;
+    const int chunks = ld > kSplitRows ? (cdiv(ld, kSplitRows) < kSplitMax ? cdiv(ld, kSplitRows) : kSplitMax) : 1;
+    f.chunk_tiles = cdiv(cdiv(ld, chunks), kChunkUnit) * (kChunkUnit / kTRows);
+    f.chunks = cdiv(tiles, f.chunk_tiles);
     f.bias_part = bias_part;
     f.tiles = tiles;
     f.loss_part = loss_part;
     f.loss = loss;
-    f.G = G;
     if (adam) {
         f.adam = 1;
         f.P = pr.P;
@@ -1121,8 +1168,12 @@ hipError_t proposal_batch_grad(const MeshDev &m, Proposal &pr, const float *from
         f.eps = 1e-8f;
         f.c1 = 1.0f / (1.0f - powf(f.b1, (float)adam->step));
         f.c2 = 1.0f / (1.0f - powf(f.b2, (float)adam->step));
+    } else {
+        f.G = pr.G;
     }
-    k_grad_finish<<<cdiv(kMlpParams, 256), 256, 0, s>>>(f);
+    // at least four waves, to share the tile's sums and steps
+    const int parts = f.chunks > 4 ? f.chunks : 4;
+    k_wgrad<<<kWTiles + 5, 64 * parts, (size_t)parts * kWT * kWT * sizeof(float), s>>>(f);
     return hipGetLastError();
 }
 
@@ -1141,8 +1192,7 @@ hipError_t proposal_set_params(Proposal &pr, hipStream_t s) {
 
 size_t proposal_batch_scratch(int rows) {
     const size_t tiles = (size_t)cdiv(rows, kTRows);
-    return tiles * kTRows * (kMlpIn + 3 * kMlpHidden + 4 * kMlpOut) * 2 +
-           4 * (size_t)kSplitMax * kMlpOut * kMlpHidden * 4 + tiles * 4 * kMlpOut * 4 + tiles * 4 + 256;
+    return tiles * kTRows * (kMlpIn + 3 * kMlpHidden + 4 * kMlpOut) * 2 + tiles * 4 * kMlpOut * 4 + tiles * 4 + 256;
 }
 
 hipError_t proposal_features(const MeshDev &m, const float *from, const float *to, int64_t n, __bf16 *X,
