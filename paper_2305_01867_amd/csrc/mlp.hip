@@ -901,89 +901,6 @@ __global__ __launch_bounds__(64 * kSplitMax) void k_wgrad(GradArgs f) {
 }
 
 // ------------------------------------------------ frontier and labels
-// Left-to-right frontier of the tree at depth 8: internal nodes at depth 8
-// and leaves shallower than that.  One lane walks it level by level (at most
-// 511 nodes); then each bucket's first sorted leaf is found by descending left.
-__global__ void k_frontier(const Node *__restrict__ nodes, const int32_t *__restrict__ parent, int root, int nt,
-                           int32_t *__restrict__ bucket_ref, int32_t *__restrict__ bucket_first,
-                           int32_t *__restrict__ n_buckets, uint8_t *__restrict__ leaf_bucket) {
-    __shared__ int cur[kMlpOut], nxt[kMlpOut];
-    __shared__ int count;
-    if (threadIdx.x == 0) {
-        int nc = 1;
-        cur[0] = root;
-        for (int d = 0; d < kFrontierDepth; ++d) {
-            int nn = 0;
-            for (int j = 0; j < nc; ++j) {
-                const int r = cur[j];
-                if (r >= 0) {
-                    nxt[nn++] = nodes[r].refs.x;
-                    nxt[nn++] = nodes[r].refs.y;
-                } else {
-                    nxt[nn++] = r;
-                }
-            }
-            for (int j = 0; j < nn; ++j)
-                cur[j] = nxt[j];
-            nc = nn;
-        }
-        count = nc;
-        *n_buckets = nc;
-    }
-    __syncthreads();
-    const int b = threadIdx.x;
-    if (b < count) {
-        int r = cur[b];
-        bucket_ref[b] = r;
-        int x = r;
-        for (int guard = 0; x >= 0 && guard < nt; ++guard)  // a path has fewer than nt internal nodes
-            x = nodes[x].refs.x;
-        bucket_first[b] = ~x;
-        // mark every leaf of the bucket's subtree: a walk without a stack (down
-        // the left children, then up until a left child with an unvisited right
-        // sibling), bounded by the subtree's 2 N_t node steps
-        auto up = [&](int c) { return c >= 0 ? parent[c] : parent[(nt - 1) + ~c]; };
-        x = r;
-        for (int64_t step = 0; step < 4 * (int64_t)nt + 8; ++step) {
-            while (x >= 0 && step++ < 4 * (int64_t)nt + 8)
-                x = nodes[x].refs.x;
-            if (x < 0 && ~x < nt)
-                leaf_bucket[~x] = (uint8_t)b;
-            // climb until x is a left child whose parent's right child is unvisited
-            int c = x;
-            bool next = false;
-            while (c != r && step++ < 4 * (int64_t)nt + 8) {
-                const int q = up(c);
-                if (q < 0 || q >= nt - 1)
-                    break;
-                if (nodes[q].refs.x == c) {
-                    x = nodes[q].refs.y;
-                    next = true;
-                    break;
-                }
-                c = q;
-            }
-            if (!next)
-                break;
-        }
-    }
-}
-
-// rank[ids[k]] = k: sorted position of each input triangle.
-__global__ void k_rank(const int32_t *__restrict__ ids, int nt, int32_t *__restrict__ rank) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < nt)
-        rank[ids[k]] = k;
-}
-
-// The training list: for every segment with a first hit, in segment order,
-// the segment and its bucket (the frontier subtree that holds the hit leaf).
-// A stable compaction -- per-workgroup counts, one scan of them, then each
-// workgroup writes at its offset in order -- so the list, and the training
-// that walks it batch by batch, do not depend on scheduling.
-constexpr int kLabSeg = 16;                   // segments per lane
-constexpr int kLabPerBlock = 256 * kLabSeg;   // per workgroup of 256
-
 // Exclusive prefix sum of v over a 256-lane workgroup; total = the sum.
 __device__ __forceinline__ int block_excl_scan(int v, int &total) {
     __shared__ int wsum[4];
@@ -1007,6 +924,107 @@ __device__ __forceinline__ int block_excl_scan(int v, int &total) {
     __syncthreads();  // wsum is reused by the next call
     return off + incl - v;
 }
+
+// Left-to-right frontier of the tree at depth 8: internal nodes at depth 8
+// and leaves shallower than that, in order.  One workgroup opens it level by
+// level: lane j has node j of the level, a prefix sum of the children's numbers
+// gives their places.  Then each bucket's first leaf is found by descending left.
+__global__ __launch_bounds__(kMlpOut) void k_frontier(const Node *__restrict__ nodes, int root, int nt,
+                                                      int32_t *__restrict__ bucket_ref,
+                                                      int32_t *__restrict__ bucket_first,
+                                                      int32_t *__restrict__ n_buckets) {
+    __shared__ int cur[kMlpOut];
+    const int b = threadIdx.x;
+    int count = 1;
+    if (b == 0)
+        cur[0] = root;
+    for (int d = 0; d < kFrontierDepth; ++d) {  // at most 2^d nodes at depth d: they fit
+        __syncthreads();
+        const int r = b < count ? cur[b] : -1;
+        int2 kids = {r, r};
+        if (r >= 0) {
+            kids.x = nodes[r].refs.x;
+            kids.y = nodes[r].refs.y;
+        }
+        int total;
+        const int at = block_excl_scan(b < count ? (r >= 0 ? 2 : 1) : 0, total);  // its barriers: every lane has read cur
+        if (b < count) {
+            cur[at] = kids.x;
+            if (r >= 0)
+                cur[at + 1] = kids.y;
+        }
+        count = total;
+    }
+    __syncthreads();
+    if (b == 0)
+        *n_buckets = count;
+    if (b < count) {
+        int x = cur[b];
+        bucket_ref[b] = x;
+        for (int guard = 0; x >= 0 && guard < nt; ++guard)  // a path has fewer than nt internal nodes
+            x = nodes[x].refs.x;
+        bucket_first[b] = ~x;
+    }
+}
+
+// leaf_bucket[k] = the bucket whose subtree holds leaf k: each leaf climbs to
+// the first ancestor (or itself) among the frontier's references, looked up in
+// a hash table in LDS (512 places for at most 256 references; an empty place
+// ends a search).  Bound by the latency of the climb, one parent at a time,
+// with every leaf of the mesh in flight: 36 us at 522,242 triangles
+// and 25 at 32,258; one lane walking each bucket's subtree took 26.8 and 1.6 ms.
+constexpr int kFrontHash = 512;
+__device__ __forceinline__ uint32_t front_hash(int ref) { return ((uint32_t)ref * 2654435769u) >> 23; }
+
+__global__ __launch_bounds__(256) void k_leaf_buckets(const int32_t *__restrict__ parent, int nt,
+                                                      const int32_t *__restrict__ bucket_ref,
+                                                      const int32_t *__restrict__ n_buckets,
+                                                      uint8_t *__restrict__ leaf_bucket) {
+    static_assert(kFrontHash >= 2 * kMlpOut && kFrontHash == 1 << 9, "at most half full; front_hash has 9 bits");
+    constexpr int kEmpty = 0x7fffffff;  // no reference: nodes and leaves are below 2^30
+    __shared__ int key[kFrontHash], val[kFrontHash];
+    for (int i = threadIdx.x; i < kFrontHash; i += blockDim.x)
+        key[i] = kEmpty;
+    __syncthreads();
+    if (threadIdx.x < (unsigned)*n_buckets) {
+        const int ref = bucket_ref[threadIdx.x];
+        for (uint32_t h = front_hash(ref);; h = (h + 1) & (kFrontHash - 1))  // ends: half of the places stay empty
+            if (atomicCAS(&key[h], kEmpty, ref) == kEmpty) {
+                val[h] = threadIdx.x;
+                break;
+            }
+    }
+    __syncthreads();
+    const int leaf = blockIdx.x * blockDim.x + threadIdx.x;
+    if (leaf >= nt)
+        return;
+    int x = ~leaf;
+    for (int guard = 0; guard <= nt; ++guard) {  // a path has at most nt nodes
+        for (uint32_t h = front_hash(x); key[h] != kEmpty; h = (h + 1) & (kFrontHash - 1))
+            if (key[h] == x) {
+                leaf_bucket[leaf] = (uint8_t)val[h];
+                return;
+            }
+        x = x >= 0 ? parent[x] : parent[(nt - 1) + ~x];
+        if (x < 0 || x >= nt - 1)
+            return;  // above the root: not reached, every path meets the frontier
+    }
+}
+
+// rank[ids[k]] = k: sorted position of each input triangle.
+__global__ void k_rank(const int32_t *__restrict__ ids, int nt, int32_t *__restrict__ rank) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < nt)
+        rank[ids[k]] = k;
+}
+
+// The training list: for every segment with a first hit, in segment order,
+// the segment and its bucket (the frontier subtree that holds the hit leaf).
+// A stable compaction -- per-workgroup counts, one scan of them, then each
+// workgroup writes at its offset in order -- so the list, and the training
+// that walks it batch by batch, do not depend on scheduling.
+constexpr int kLabSeg = 16;                   // segments per lane
+constexpr int kLabPerBlock = 256 * kLabSeg;   // per workgroup of 256
 
 __device__ __forceinline__ int lane_hits(const int32_t *__restrict__ tri_id, int64_t n, int64_t base) {
     int c = 0;
@@ -1068,8 +1086,9 @@ hipError_t proposal_frontier(const MeshDev &m, Proposal &pr, hipStream_t s) {
     if (m.nt < 1)
         return hipErrorInvalidValue;
     k_rank<<<cdiv(m.nt, 256), 256, 0, s>>>(m.ids, (int)m.nt, pr.rank);
-    k_frontier<<<1, kMlpOut, 0, s>>>(m.nodes, m.parent, m.root, (int)m.nt, pr.bucket_ref, pr.bucket_first,
-                                     pr.dev_n_buckets, pr.leaf_bucket);
+    k_frontier<<<1, kMlpOut, 0, s>>>(m.nodes, m.root, (int)m.nt, pr.bucket_ref, pr.bucket_first, pr.dev_n_buckets);
+    k_leaf_buckets<<<cdiv(m.nt, 256), 256, 0, s>>>(m.parent, (int)m.nt, pr.bucket_ref, pr.dev_n_buckets,
+                                                   pr.leaf_bucket);
     return hipGetLastError();
 }
 
