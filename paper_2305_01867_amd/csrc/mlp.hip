@@ -150,25 +150,78 @@ __global__ __launch_bounds__(256) void k_init_params(float *__restrict__ P, __bf
 }
 
 // ------------------------------------------------ fused inference kernel
-// 96 segments per tile; four waves, wave w producing output columns
-// [64 w, 64 w + 64) of every layer for all 96 rows (24 MFMA per k step, so
-// each weight fragment fetched from L2 feeds 6 row tiles).  Activations stay
-// in LDS in one bf16 buffer that each layer overwrites once every wave has
-// read it (54 KB with the argmax scratch: two workgroups per CU, 246 VGPRs
-// and two waves per SIMD; 112 or 128 rows spill).  Weight fragments load two
-// k steps ahead of the multiplies that use them (measured at the paper's
-// scale: 64 rows with two buffers and a one-step register copy 11.0 ms per
-// 1e7 segments, this layout 7.6 ms; eight waves of 32 columns each, at four
-// waves per SIMD, are no faster).  The accumulation order over k is
-// the one k_gemm uses, so the logits are bit-identical to the training
-// forward pass.
+// kPRows segments per tile; four waves, wave w producing output columns
+// [64 w, 64 w + 64) of every layer for all rows (24 MFMA per k step, so each
+// weight fragment fetched from L2 feeds 6 row tiles).  Activations stay in LDS
+// in one bf16 buffer that each layer overwrites once every wave has read it
+// (two workgroups per CU, two waves per SIMD).  Weight fragments load two
+// k steps ahead of the multiplies that use them, activations one.
+// The weights are the MFMA's row operand and the segments its columns, so a
+// lane ends with four neighbouring outputs of one segment: the epilogue packs
+// them into one 8-byte LDS write, and the argmax needs two exchanges between
+// lanes per row tile.  2e6 segments take 957 us (1,060 TFLOP/s;
+// 1,279 with segments as rows, 24 row exchanges of four steps and 2-byte LDS
+// writes).  Measured: 80 rows 1,004, 112 rows 979 (they spill), weights three
+// steps ahead 970, activations read in their own step 1,001.
+// The accumulation order over k is the training pass's, so the logits are
+// bit-identical to its forward pass.
 constexpr int kPRows = 96;
 constexpr int kPPitch = kMlpHidden + 8;
 constexpr int kPRowTiles = kPRows / 16;
 constexpr int kPWaves = 4;                          // waves per workgroup, each owning a column slice
 constexpr int kPThreads = 64 * kPWaves;
 constexpr int kPColTiles = kMlpHidden / 16 / kPWaves;  // 16-column tiles per wave
-constexpr int kPAhead = 2;                          // k steps the weight loads run ahead (1: 8.0 ms, 2: 7.6, 3: 7.6, 4: 7.7)
+constexpr int kPAhead = 2;  // k steps the weight loads run ahead
+constexpr int kPRead = 1;   // and the activations' reads
+
+// One layer of the inference tile: acc[a][b] = outputs 64 wave + 16 b .. + 15
+// (rows) of segments 16 a .. + 15 (columns).  K (224 or 256) is known at compile
+// time and the k loop fully unrolled, so every step's fragments are registers
+// of their own and its loads stay in flight across the steps before it.
+template <int K>
+__device__ __forceinline__ void layer_tile(const __bf16 *__restrict__ Xin, const __bf16 *__restrict__ Wt, int wave,
+                                           int lane, f32x4 (&acc)[kPRowTiles][kPColTiles]) {
+    static_assert(K % 32 == 0, "K must be a multiple of 32");
+    constexpr int kSteps = K / 32;
+#pragma unroll
+    for (int a = 0; a < kPRowTiles; ++a)
+#pragma unroll
+        for (int b = 0; b < kPColTiles; ++b)
+            acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // the wave's first column tile, this lane's 16 bytes of each block
+    const __bf16 *wfrag = Wt + (int64_t)kPColTiles * wave * kSteps * 512 + 8 * lane;
+    const __bf16 *xrow = Xin + (lane & 15) * kPPitch + 8 * (lane >> 4);
+    bf16x8 f[kSteps][kPColTiles], x[kSteps][kPRowTiles];
+    auto weights = [&](int st) {
+#pragma unroll
+        for (int b = 0; b < kPColTiles; ++b)
+            f[st][b] = *reinterpret_cast<const bf16x8 *>(wfrag + (int64_t)(b * kSteps + st) * 512);
+    };
+    auto rows = [&](int st) {
+#pragma unroll
+        for (int a = 0; a < kPRowTiles; ++a)
+            x[st][a] = *reinterpret_cast<const bf16x8 *>(xrow + 16 * a * kPPitch + 32 * st);
+    };
+#pragma unroll
+    for (int st = 0; st < kPAhead; ++st)
+        weights(st);
+#pragma unroll
+    for (int st = 0; st < kPRead; ++st)
+        rows(st);
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+        if (st + kPAhead < kSteps)
+            weights(st + kPAhead);
+        if (st + kPRead < kSteps)
+            rows(st + kPRead);
+#pragma unroll
+        for (int a = 0; a < kPRowTiles; ++a)
+#pragma unroll
+            for (int b = 0; b < kPColTiles; ++b)
+                acc[a][b] = mfma16(f[st][b], x[st][a], acc[a][b]);
+        __builtin_amdgcn_sched_barrier(0);  // keep each step's loads in its step: no hoisting past the register budget
+    }
+}
 
 template <int RT, int CT>
 __device__ __forceinline__ void tile_step(const __bf16 *__restrict__ xrow, int k0, const bf16x8 (&fb)[CT],
@@ -182,44 +235,7 @@ __device__ __forceinline__ void tile_step(const __bf16 *__restrict__ xrow, int k
     }
 }
 
-// K (224 or 256) is known at compile time and the k loop fully unrolled, so
-// every step's weight fragments are registers of their own: step st + kPAhead's
-// loads are issued before step st multiplies and stay in flight across it,
-// with no register copy that would wait for them.
-// RT row tiles of 16 (activations in LDS at pitch kPPitch), the wave's
-// kPColTiles column tiles, weight loads AHEAD k steps early.
-template <int K, int RT = kPRowTiles, int AHEAD = kPAhead>
-__device__ __forceinline__ void layer_tile(const __bf16 *__restrict__ Xin, const __bf16 *__restrict__ Wt, int wave,
-                                           int lane, f32x4 (&acc)[RT][kPColTiles]) {
-    static_assert(K % 32 == 0, "K must be a multiple of 32");
-    constexpr int kSteps = K / 32;
-#pragma unroll
-    for (int a = 0; a < RT; ++a)
-#pragma unroll
-        for (int b = 0; b < kPColTiles; ++b)
-            acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const int kq = 8 * (lane >> 4);
-    // the wave's first column tile, this lane's 16 bytes of each block
-    const __bf16 *wfrag = Wt + (int64_t)kPColTiles * wave * kSteps * 512 + 8 * lane;
-    const __bf16 *xrow = Xin + (lane & 15) * kPPitch + kq;
-    bf16x8 f[kSteps][kPColTiles];
-#pragma unroll
-    for (int st = 0; st < AHEAD && st < kSteps; ++st)
-#pragma unroll
-        for (int b = 0; b < kPColTiles; ++b)
-            f[st][b] = *reinterpret_cast<const bf16x8 *>(wfrag + (int64_t)(b * kSteps + st) * 512);
-#pragma unroll
-    for (int st = 0; st < kSteps; ++st) {
-        if (st + AHEAD < kSteps)
-#pragma unroll
-            for (int b = 0; b < kPColTiles; ++b)
-                f[st + AHEAD][b] = *reinterpret_cast<const bf16x8 *>(wfrag + (int64_t)(b * kSteps + st + AHEAD) * 512);
-        tile_step(xrow, 32 * st, f[st], acc);
-        __builtin_amdgcn_sched_barrier(0);  // keep each step's loads in its step: no hoisting past the register budget
-    }
-}
-
-// layer_tile for a chain of layers: the first AHEAD k steps' fragments come
+// A layer of the training tile (segments as rows), in a chain: the first AHEAD k steps' fragments come
 // in pf, and the last AHEAD steps load the next layer's first AHEAD steps
 // (from Wn, with KN inputs; none when Wn is NULL) into pf, so a layer starts
 // without waiting on memory and the epilogue between two layers hides the
@@ -274,33 +290,57 @@ __device__ __forceinline__ void layer_chain(const __bf16 *__restrict__ Xin, cons
     }
 }
 
-__global__ __launch_bounds__(kPThreads) __attribute__((amdgpu_waves_per_eu(kPWaves / 2))) void k_mlp_propose(const float *__restrict__ from, const float *__restrict__ to,
-                                                     int64_t n, const float *__restrict__ bounds,
-                                                     const __bf16 *__restrict__ Wb, const float *__restrict__ P,
-                                                     int nb, uint8_t *__restrict__ bucket) {
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Half of the features that depend on coordinate c of value x (bands 8 h ..
+// 8 h + 7, and with h = 0 the value) into row[].
+__device__ __forceinline__ void half_features(float x, int c, int h, __bf16 *row) {
+#pragma clang fp contract(off)
+    if (h == 0)
+        row[c] = (__bf16)x;
+    const float f0 = h ? 16.0f : 1.0f;  // 2^(8 h / 2)
+    __bf16 *out = row + 6 + c * 2 * kMlpBands + h * kMlpBands;
+#pragma unroll
+    for (int k = 0; k < kMlpBands / 2; ++k) {
+        float sn, cs;
+        sincospi_fast(f0 * band_freq(k) * x, sn, cs);
+        *reinterpret_cast<bf16x2 *>(out + 2 * k) = bf16x2{(__bf16)sn, (__bf16)cs};
+    }
+}
+
+__global__ __launch_bounds__(kPThreads) __attribute__((amdgpu_waves_per_eu(kPWaves / 2))) void k_mlp_propose(
+    const float *__restrict__ from, const float *__restrict__ to, int64_t n, const float *__restrict__ bounds,
+    const __bf16 *__restrict__ Wb, const float *__restrict__ P, int nb, uint8_t *__restrict__ bucket) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __bf16 *X = reinterpret_cast<__bf16 *>(lds_raw);  // activations, overwritten layer by layer
     float *best_v = reinterpret_cast<float *>(X + kPRows * kPPitch);  // [kPWaves][kPRows]
     int *best_i = reinterpret_cast<int *>(best_v + kPWaves * kPRows);  // [kPWaves][kPRows]
+    float *bias = reinterpret_cast<float *>(best_i + kPWaves * kPRows);  // [4][kMlpOut]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float *bias = P + kMlpWeights;
+    const int l16 = lane & 15, g4 = lane >> 4;
+    for (int i = tid; i < 4 * kMlpOut; i += kPThreads)
+        bias[i] = P[kMlpWeights + i];
+    // this lane's outputs: columns col0 + 16 b + i of segment l16 of each row tile
+    const int col0 = 16 * kPColTiles * wave + 4 * g4;
     const int64_t tiles = (n + kPRows - 1) / kPRows;
 #pragma unroll 1
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const int64_t r0 = tile * kPRows;
-        // features -> X (pitch kPPitch)
+        // features -> X: 12 halves of a coordinate per segment, then the padding
 #pragma unroll 1
-        for (int q = tid; q < kPRows * 7; q += kPThreads) {
-            const int r = q / 7, part = q % 7;
+        for (int q = tid; q < kPRows * 13; q += kPThreads) {
+            const int r = q / 13, part = q % 13;
             __bf16 *row = X + r * kPPitch;
-            if (part == 6) {
-                for (int j = kMlpFeat; j < kMlpIn; ++j)
-                    row[j] = (__bf16)0.0f;
+            if (part == 12) {
+#pragma unroll
+                for (int j = kMlpFeat; j < kMlpIn; j += 2)
+                    *reinterpret_cast<bf16x2 *>(row + j) = bf16x2{(__bf16)0.0f, (__bf16)0.0f};
                 continue;
             }
             const int64_t seg = r0 + r < n ? r0 + r : n - 1;
-            const float x = norm_coord(seg_coord(from, to, seg, part), bounds[part % 3], bounds[3 + part % 3]);
-            coord_features(x, part, row);
+            const int c = part >> 1;
+            half_features(norm_coord(seg_coord(from, to, seg, c), bounds[c % 3], bounds[3 + c % 3]), c, part & 1, row);
         }
         __syncthreads();
         // the four layers through one call site, so the accumulators keep one
@@ -309,67 +349,60 @@ __global__ __launch_bounds__(kPThreads) __attribute__((amdgpu_waves_per_eu(kPWav
         f32x4 acc[kPRowTiles][kPColTiles];
 #pragma unroll 1
         for (int l = 0; l < 4; ++l) {
-            const __bf16 *in = X;
-            __bf16 *out = X;
             const int64_t woff = l == 0 ? 0 : (int64_t)kMlpOut * kMlpIn + (int64_t)(l - 1) * kMlpHidden * kMlpHidden;
             if (l == 0)
-                layer_tile<kMlpIn>(in, Wb + woff, wave, lane, acc);
+                layer_tile<kMlpIn>(X, Wb + woff, wave, lane, acc);
             else
-                layer_tile<kMlpHidden>(in, Wb + woff, wave, lane, acc);
+                layer_tile<kMlpHidden>(X, Wb + woff, wave, lane, acc);
             if (l == 3)
                 break;
-            const float *bl = bias + l * kMlpHidden;
-            __syncthreads();  // every wave has read `in` before it is overwritten
+            __syncthreads();  // every wave has read X before it is overwritten
 #pragma unroll
             for (int b = 0; b < kPColTiles; ++b) {
-                const int col = 16 * kPColTiles * wave + 16 * b + (lane & 15);
-                const float bv = bl[col];
+                const f32x4 bv = *reinterpret_cast<const f32x4 *>(bias + l * kMlpHidden + col0 + 16 * b);
 #pragma unroll
-                for (int a = 0; a < kPRowTiles; ++a)
+                for (int a = 0; a < kPRowTiles; ++a) {
+                    bf16x4 h;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int row = 16 * a + 4 * (lane >> 4) + i;
-                        out[row * kPPitch + col] = (__bf16)fmaxf(acc[a][b][i] + bv, 0.0f);
-                    }
+                    for (int i = 0; i < 4; ++i)
+                        h[i] = (__bf16)fmaxf(acc[a][b][i] + bv[i], 0.0f);
+                    *reinterpret_cast<bf16x4 *>(X + (16 * a + l16) * kPPitch + col0 + 16 * b) = h;
+                }
             }
             __syncthreads();
         }
-        const float *b4 = bias + 3 * kMlpHidden;
-        float b4v[kPColTiles];
+        // argmax over valid buckets (smallest index on ties): the lane's
+        // columns ascend, then the four lanes of a segment, then the waves
 #pragma unroll
-        for (int b = 0; b < kPColTiles; ++b)
-            b4v[b] = b4[16 * kPColTiles * wave + 16 * b + (lane & 15)];
-        // argmax over valid buckets (smallest index on ties)
+        for (int a = 0; a < kPRowTiles; ++a) {
+            float bv = -INFINITY;
+            int bi = INT32_MAX;
 #pragma unroll
-        for (int a = 0; a < kPRowTiles; ++a)
+            for (int b = 0; b < kPColTiles; ++b) {
+                const f32x4 b4 = *reinterpret_cast<const f32x4 *>(bias + 3 * kMlpHidden + col0 + 16 * b);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float bv = -INFINITY;
-                int bi = INT32_MAX;
-#pragma unroll
-                for (int b = 0; b < kPColTiles; ++b) {
-                    const int col = 16 * kPColTiles * wave + 16 * b + (lane & 15);
-                    const float v = acc[a][b][i] + b4v[b];
-                    if (col < nb && (v > bv || (v == bv && col < bi))) {
+                for (int i = 0; i < 4; ++i) {
+                    const float v = acc[a][b][i] + b4[i];
+                    if (col0 + 16 * b + i < nb && (v > bv || (v == bv && bi == INT32_MAX))) {
                         bv = v;
-                        bi = col;
+                        bi = col0 + 16 * b + i;
                     }
-                }
-#pragma unroll
-                for (int off = 1; off < 16; off <<= 1) {
-                    const float ov = __shfl_xor(bv, off);
-                    const int oi = __shfl_xor(bi, off);
-                    if (ov > bv || (ov == bv && oi < bi)) {
-                        bv = ov;
-                        bi = oi;
-                    }
-                }
-                if ((lane & 15) == 0) {
-                    const int row = 16 * a + 4 * (lane >> 4) + i;
-                    best_v[wave * kPRows + row] = bv;
-                    best_i[wave * kPRows + row] = bi;
                 }
             }
+#pragma unroll
+            for (int off = 16; off < 64; off <<= 1) {
+                const float ov = __shfl_xor(bv, off);
+                const int oi = __shfl_xor(bi, off);
+                if (ov > bv || (ov == bv && oi < bi)) {
+                    bv = ov;
+                    bi = oi;
+                }
+            }
+            if (g4 == 0) {
+                best_v[wave * kPRows + 16 * a + l16] = bv;
+                best_i[wave * kPRows + 16 * a + l16] = bi;
+            }
+        }
         __syncthreads();
         if (tid < kPRows && r0 + tid < n) {
             float bv = best_v[tid];
@@ -384,11 +417,13 @@ __global__ __launch_bounds__(kPThreads) __attribute__((amdgpu_waves_per_eu(kPWav
             }
             bucket[r0 + tid] = (uint8_t)(bi >= 0 && bi < nb ? bi : 0);
         }
-        __syncthreads();
+        // no barrier: the next write of best_v / best_i and of X by a faster
+        // wave comes after barriers that this wave has yet to reach
     }
 }
 
-constexpr size_t kProposeLds = (size_t)kPRows * kPPitch * sizeof(__bf16) + 2 * kPWaves * (size_t)kPRows * 4;
+constexpr size_t kProposeLds = (size_t)kPRows * kPPitch * sizeof(__bf16) + 2 * kPWaves * (size_t)kPRows * 4 +
+                               4 * (size_t)kMlpOut * sizeof(float);
 
 // ------------------------------------------------ fused training pass
 // One workgroup per kTRows rows of a batch: the features, the four layers
@@ -461,9 +496,6 @@ constexpr int kLPitch = kMlpOut + 16;  // logits row pitch (floats): four rows o
 constexpr size_t kTLogitBytes = (size_t)kTRows * kLPitch * sizeof(float);
 static_assert(kTLogitBytes >= kTActBytes, "the logits take the activations' place");
 constexpr size_t kTrainLds = kTLogitBytes + kTActBytes + (size_t)kTRows * sizeof(float);
-
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Max / sum over the 16 lanes of a DPP row, every lane ending with the same
 // value: rotations by 8, 4, 2 and 1 within the row, each step adding two
