@@ -81,41 +81,74 @@ constexpr int kStageWin = 256;
 constexpr int kStageWords = 2 * kStageWin / 32 + 1;  // value bits, done bits, count
 constexpr int kStageWaveWords = 2 * kStageWords + 2;  // two windows, padded to 16 bytes
 
+typedef __attribute__((address_space(3))) int *LdsInt;
+__device__ __forceinline__ float4 node_row(const char *p) { return *reinterpret_cast<const float4 *>(p); }
+
+// A child's sort key: its entry t (>= 0; +inf if the segment misses it) as the
+// high word of a double, its reference as the low word.  Doubles of one sign
+// order as their bits do and an infinite float makes a finite double, so two
+// instructions exchange keys and references together where comparing the floats
+// took a compare, a minimum, a maximum and two selects; equal t order by the
+// references.  (Instructions, not fmin / fmax: those would first quiet
+// signalling NaNs, which no key is.)
+__device__ __forceinline__ double sort_key(bool h, float t, int c) {
+    return __hiloint2double(h ? __float_as_int(t) : 0x7f800000, c);
+}
+__device__ __forceinline__ int key_child(double k) { return __double2loint(k); }
+__device__ __forceinline__ void order2(double &a, double &b) {
+    double lo, hi;
+    asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(a), "v"(b));
+    asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(a), "v"(b));
+    a = lo;
+    b = hi;
+}
+
 // PROP: proposal-first order.  Phase 0 traverses the predicted frontier
 // subtree; phase 1 the whole tree with that subtree left out.  Together they
 // visit exactly what the plain order visits, so results do not change.
 template <int MODE, bool CERT, bool STATS, bool PROP, bool WIDE>
 __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     const int lane = threadIdx.x & 63;
-    // each wave's stacks are a block of LDS of their own, an entry of all 64
-    // lanes after the other
+    // LDS: the top of the 4-wide tree (read-only once filled) from address 0,
+    // so that a node's byte offset is its address there too; one spare row of
+    // 64 entries; the waves' stacks, each a block of its own, an entry of all 64
+    // lanes after the other; the staging windows.  Stack positions are LDS byte
+    // addresses of the top entry (one row below the block: empty), so a step
+    // needs no address arithmetic: reads and pushes are at fixed offsets.
     constexpr int stride = 64;
+    constexpr int kRow = stride * (int)sizeof(int);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(LdsInt)lds_stack;
+    const int top_n = WIDE && lds0 == 0 ? p.top_lds : 0;  // (no static LDS: lds0 is 0)
+    const bool top_group = WIDE && p.top_group && lds0 == 0;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wave_stack = (p.stack_depth + (WIDE ? 3 : 1)) * stride;
-    int *stk = lds_stack + (threadIdx.x >> 6) * wave_stack + lane;
+    int *stk = lds_stack + 32 * p.top_lds + stride + wave * wave_stack;  // the wave's block
+    const int sp_base = (int)lds0 + 4 * (32 * p.top_lds + stride + wave * wave_stack);
+    const int sp_empty = sp_base - kRow + 4 * lane;  // stack positions at or above sp_base hold something
+    const int sp_lim = sp_base + p.stack_depth * kRow;  // at or above: more than stack_depth entries
     const uint64_t lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
     const float scale = p.bounds[6];
     const int n_internal = (int)p.nt - 1;
     const int max_steps = 2 * (int)p.nt + 8;  // N_t < 2^30
-    const int depth_lim = p.stack_depth * stride;  // stack offsets are kept in units of lanes
-    // 4-wide: the top of the tree in LDS, after the stacks (read-only once filled)
+    const bool far = ((int64_t)p.nt + kTopSlots) * (int64_t)sizeof(Node4) > INT64_C(0xffffffff);
     const int ref_lim = WIDE ? n_internal + kTopSlots : n_internal;
-    float4 *top_cache = reinterpret_cast<float4 *>(lds_stack + (p.stack_depth + 3) * blockDim.x);
+    float4 *top_cache = reinterpret_cast<float4 *>(lds_stack);
     const int group = p.n_groups > 0 ? (int)(blockIdx.x % p.n_groups) : 0;
     if (WIDE) {
-        const Node4 *top = p.top_group ? p.top4g + (int64_t)group * kTopSlots : p.top4;
+        const Node4 *top = top_group ? p.top4g + (int64_t)group * kTopSlots : p.top4;
         const float4 *src = reinterpret_cast<const float4 *>(top);
-        for (int i = threadIdx.x; i < 8 * p.top_lds; i += blockDim.x)
+        for (int i = threadIdx.x; i < 8 * top_n; i += blockDim.x)
             top_cache[i] = src[i];
         __syncthreads();
     }
-    const int32_t *roots4 = p.top_group ? p.roots4g + (int64_t)group * 64 : p.mesh_root4;
+    const int32_t *roots4 = top_group ? p.roots4g + (int64_t)group * 64 : p.mesh_root4;
 
     // One mesh: each wave owns a contiguous range of segments and its lanes
     // draw from it.  Batched form: waves take (mesh, segment range) items from
     // a shared queue, one atomic per item.  Wave-uniform state.
     const bool batch = p.items != nullptr;
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    const int64_t wave_id = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int64_t wave_id = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
     // boolean results staged in LDS (one mesh, input order, 4-byte aligned output)
     const bool stage = MODE == MODE_BOOL && !STATS && !batch && p.order == nullptr && p.stage_ok;
     // One mesh: the first segments are split evenly over the waves; the rest
@@ -134,10 +167,10 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     int win_old = 0;              // which of the two holds the older window
     if (stage) {
         // after the stacks (stack_depth + 3 entries per lane with 4-wide nodes,
-        // + 1 with binary ones) and the top nodes
-        stage_w = reinterpret_cast<uint32_t *>(lds_stack + (p.stack_depth + (WIDE ? 3 : 1)) * blockDim.x +
-                                               32 * p.top_lds) +
-                  (threadIdx.x >> 6) * kStageWaveWords;
+        // + 1 with binary ones)
+        stage_w = reinterpret_cast<uint32_t *>(lds_stack + 32 * p.top_lds + stride +
+                                               (p.stack_depth + (WIDE ? 3 : 1)) * blockDim.x) +
+                  wave * kStageWaveWords;
         if (lane < kStageWaveWords)
             stage_w[lane] = 0u;
     }
@@ -194,7 +227,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     // and the matching slab offsets, fixed per segment by the direction signs
     int offx = 0, offy = 32, offz = 64;
     float3 nn = make_float3(0.0f, 0.0f, 0.0f), nf = nn;
-    int ref = kDone, sp = 0;  // sp: offset of the next free slot (a multiple of stride)
+    int ref = kDone, sp = sp_empty;  // idle lanes have ref == kDone
     int held[kPend<MODE>];    // leaves held aside (-1: free), tested in this order
 #pragma unroll
     for (int k = 0; k < kPend<MODE>; ++k)
@@ -233,7 +266,16 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     int nk = 0;
     bool list_full = false;
 
-    auto pop = [&]() -> int { return sp > 0 ? stk[sp -= stride] : kDone; };
+    // (popping an empty stack reads the row below it and leaves sp below
+    // sp_empty: the segment, or its proposed subtree, is done then)
+    auto entry = [](int at) -> int { return *(LdsInt)(uint32_t)at; };
+    auto put_entry = [](int at, int x) { *(LdsInt)(uint32_t)at = x; };
+    auto pop = [&]() -> int {
+        const int x = entry(sp);
+        const int r = sp >= sp_base ? x : kDone;
+        sp -= kRow;
+        return r;
+    };
 
     // the lane's segment is decided: its result goes out
     auto finish = [&]() {
@@ -363,7 +405,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                     lane_toff = cur_toff;
                     ref = lane_root;
                     drop_held();
-                    sp = 0;
+                    sp = sp_empty;
                     tlimit = 1.0f;
                     best_id = -1;
                     best_t = best_lo = best_hi = INFINITY;
@@ -395,6 +437,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                             write_out(p.out, ray, MODE, -1, 0.0f, 0.0f, 0.0f);
                         }
                         ray = -1;
+                        ref = kDone;
                     } else if (WIDE) {
                         const bool sx = r.inv.x < 0.0f, sy = r.inv.y < 0.0f, sz = r.inv.z < 0.0f;
                         offx = sx ? 16 : 0;
@@ -418,12 +461,13 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
             break;
 
         // ---- node phase
-        // Push and pop are branch-free: every lane has one spare LDS slot past
-        // its stack_depth entries, so the push slot is written unconditionally
-        // (a slot at or above sp holds nothing live), and the top of stack is
-        // read ahead of the node fetch and used only if the node yields nothing.
-        for (;;) {
-            if (ray >= 0 && ref < 0 && ref != kDone) {  // a leaf: hold it aside if a slot is free
+        // Push and pop are branch-free: every lane has spare LDS slots past its
+        // stack_depth entries, so the push slots are written unconditionally (a
+        // slot above sp holds nothing live), and the top of stack is read ahead
+        // of the node fetch and used only if the node yields nothing.  The step
+        // count is checked after the phase, which is bounded itself.
+        for (int turn = 0; turn <= max_steps; ++turn) {
+            if ((uint32_t)ref > (uint32_t)kDone) {  // a leaf: hold it aside if a slot is free
                 bool put = false;
 #pragma unroll
                 for (int k = 0; k < kPend<MODE>; ++k)
@@ -434,20 +478,21 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                 if (put)
                     ref = pop();
             }
-            const bool want = ray >= 0 && ref >= 0;
-            const uint64_t w = __ballot(want);
+            const bool want = ref >= 0;
+            const uint64_t w = __builtin_amdgcn_ballot_w64(want);
             if (!w)
                 break;
             const uint64_t waiting = active & ~w;
             if (kLeafShare<MODE> * __popcll(waiting) > __popcll(active))
                 break;
             if (want) {
-                if (++steps > max_steps || ref >= ref_lim) {
+                ++steps;
+                if (ref >= ref_lim) {
                     overflow = true;  // cannot happen for a well-formed tree
                     ref = kDone;
                     drop_held();
                 } else {
-                    const int top = stk[sp > 0 ? sp - stride : 0];
+                    const int top = entry(sp);  // an empty stack: the row below, not used
                     if (STATS)
                         ++n_nodes;
                     if (WIDE) {
@@ -458,28 +503,31 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                         // near and far faces chosen by the segment's signs
                         float4 nx, fx, ny, fy, nz, fz;
                         int4 ch;
-                        if (ref < p.top_lds) {  // the top of the tree, from LDS (ds_read)
-                            const LdsBytes c = (LdsBytes)(top_cache + 8 * ref);  // generic -> LDS
-                            nx = lds_f4(c + offx);
-                            fx = lds_f4(c + (offx ^ 16));
-                            ny = lds_f4(c + offy);
-                            fy = lds_f4(c + (offy ^ 16));
-                            nz = lds_f4(c + offz);
-                            fz = lds_f4(c + (offz ^ 16));
-                            const float4 cf = lds_f4(c + 96);
+                        const uint32_t at = (uint32_t)ref << 7;
+                        auto fetch = [&](auto row) {
+                            nx = row(at + offx);
+                            fx = row(at + (offx ^ 16));
+                            ny = row(at + offy);
+                            fy = row(at + (offy ^ 16));
+                            nz = row(at + offz);
+                            fz = row(at + (offz ^ 16));
+                            const float4 cf = row(at + 96u);
                             ch = make_int4(__float_as_int(cf.x), __float_as_int(cf.y), __float_as_int(cf.z),
                                            __float_as_int(cf.w));
-                        } else {
-                            // nodes4 follows top4: one address for both kinds of reference
-                            const char *c = reinterpret_cast<const char *>(p.top4 + ref);
-                            nx = *reinterpret_cast<const float4 *>(c + offx);
-                            fx = *reinterpret_cast<const float4 *>(c + (offx ^ 16));
-                            ny = *reinterpret_cast<const float4 *>(c + offy);
-                            fy = *reinterpret_cast<const float4 *>(c + (offy ^ 16));
-                            nz = *reinterpret_cast<const float4 *>(c + offz);
-                            fz = *reinterpret_cast<const float4 *>(c + (offz ^ 16));
-                            ch = *reinterpret_cast<const int4 *>(c + 96);
-                        }
+                        };
+                        // nodes4 follows top4: one address for both kinds of
+                        // reference, 32-bit offsets from it below 4 GB of nodes
+                        if (ref < top_n)
+                            fetch([](uint32_t o) { return lds_f4((LdsBytes)o); });
+                        else if (!far)
+                            fetch([&](uint32_t o) { return node_row(reinterpret_cast<const char *>(p.top4) + o); });
+                        else  // (o - at: the row's offset in the node)
+                            fetch([&](uint32_t o) {
+                                return node_row(reinterpret_cast<const char *>(p.top4 + ref) + (o - at));
+                            });
+                        // (the references are moved into their keys here, not in the
+                        // branches, which would wait for the loads there)
+                        asm("" : "+v"(ch.x), "+v"(ch.y), "+v"(ch.z), "+v"(ch.w));
                         float k0, k1, k2, k3;
                         bool h0 = slab_nf(nx.x, fx.x, ny.x, fy.x, nz.x, fz.x, r.inv, nn, nf, tlimit, k0);
                         bool h1 = slab_nf(nx.y, fx.y, ny.y, fy.y, nz.y, fz.y, r.inv, nn, nf, tlimit, k1);
@@ -497,34 +545,36 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                             // nearest first: a boolean segment meets a hit
                             // sooner, the nearest-hit modes' shrinking t limit
                             // prunes the rest
-                            k0 = h0 ? k0 : INFINITY;
-                            k1 = h1 ? k1 : INFINITY;
-                            k2 = h2 ? k2 : INFINITY;
-                            k3 = h3 ? k3 : INFINITY;
-                            order2(k0, c0, k1, c1);
-                            order2(k2, c2, k3, c3);
-                            order2(k0, c0, k2, c2);
-                            order2(k1, c1, k3, c3);
-                            order2(k1, c1, k2, c2);
-                            stk[sp] = nh == 4 ? c3 : (nh == 3 ? c2 : c1);
-                            stk[sp + stride] = nh == 4 ? c2 : c1;
-                            stk[sp + 2 * stride] = c1;
+                            double s0 = sort_key(h0, k0, c0), s1 = sort_key(h1, k1, c1);
+                            double s2 = sort_key(h2, k2, c2), s3 = sort_key(h3, k3, c3);
+                            order2(s0, s1);
+                            order2(s2, s3);
+                            order2(s0, s2);
+                            order2(s1, s3);
+                            order2(s1, s2);
+                            c0 = key_child(s0);
+                            c1 = key_child(s1);
+                            c2 = key_child(s2);
+                            c3 = key_child(s3);
+                            put_entry(sp + kRow, nh == 4 ? c3 : (nh == 3 ? c2 : c1));
+                            put_entry(sp + 2 * kRow, nh == 4 ? c2 : c1);
+                            put_entry(sp + 3 * kRow, c1);
                         } else {
                             // count mode visits every candidate whatever the
                             // order: the first hit child is next, the others go
                             // on the stack in child order
                             const int p1 = h0, p2 = p1 + h1, p3 = p2 + h2;
                             if (h1 && p1)
-                                stk[sp] = c1;
+                                put_entry(sp + kRow, c1);
                             if (h2 && p2)
-                                stk[sp + (p2 - 1) * stride] = c2;
+                                put_entry(sp + p2 * kRow, c2);
                             if (h3 && p3)
-                                stk[sp + (p3 - 1) * stride] = c3;
+                                put_entry(sp + p3 * kRow, c3);
                             c0 = h0 ? c0 : (h1 ? c1 : (h2 ? c2 : c3));
                         }
-                        ref = nh ? c0 : (sp > 0 ? top : kDone);
-                        sp += nh > 1 ? (nh - 1) * stride : (nh == 0 && sp > 0 ? -stride : 0);
-                        if (sp > depth_lim) {
+                        ref = nh ? c0 : (sp >= sp_base ? top : kDone);
+                        sp += (nh - 1) * kRow;
+                        if (sp >= sp_lim) {
                             overflow = true;  // the segment goes to the deep-stack pass
                             ref = kDone;
                             drop_held();
@@ -542,18 +592,24 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                         }
                         const bool both = hl && hr, any = hl || hr;
                         const bool left_first = both ? tl <= tr : hl;
-                        stk[sp] = left_first ? refs.y : refs.x;
+                        put_entry(sp + kRow, left_first ? refs.y : refs.x);
                         const int next = left_first ? refs.x : refs.y;
-                        overflow = overflow || (both && sp >= depth_lim);
-                        ref = any ? next : (sp > 0 ? top : kDone);
-                        sp += both ? stride : (!any && sp > 0 ? -stride : 0);
-                        if (both && sp > depth_lim) {
-                            ref = kDone;  // overflow: the segment goes to the deep-stack pass
+                        ref = any ? next : (sp >= sp_base ? top : kDone);
+                        sp += both ? kRow : (any ? 0 : -kRow);
+                        if (sp >= sp_lim) {
+                            overflow = true;  // the segment goes to the deep-stack pass
+                            ref = kDone;
                             drop_held();
                         }
                     }
                 }
             }
+        }
+
+        if (ray >= 0 && steps > max_steps) {  // cannot happen for a well-formed tree
+            overflow = true;
+            ref = kDone;
+            drop_held();
         }
 
         // ---- leaf phase: the leaves held aside, in the order they were met;
@@ -730,6 +786,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
         if (PROP && ray >= 0 && ref == kDone && none_held() && phase == 0 && !found && !flagged && !overflow) {
             phase = 1;
             ref = lane_root == skip ? kDone : lane_root;
+            sp = sp_empty;
         }
 
         // ---- finish lanes whose segment is decided; one whose path outgrew the
@@ -773,9 +830,9 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
         // from the beginning (the second pass takes 12 to 20 us for a queue of
         // one segment).
         Pool<MODE, CERT, PROP> pool;
-        pool.init(p, reinterpret_cast<uint32_t *>(stk - lane), 64, wave_stack - kPoolLeafCap - 64);
+        pool.init(p, reinterpret_cast<uint32_t *>(stk), 64, wave_stack - kPoolLeafCap - 64);
         pool.top_cache = top_cache;
-        pool.top_lds = p.top_lds;
+        pool.top_lds = top_n;
         PoolSegment<MODE, CERT> s;
         s.reset();
         s.ray = (int)ray;
@@ -1435,12 +1492,13 @@ void launch_pass1(const TravParams &p, int block, hipStream_t s) {
         (void)hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     // a workgroup whose stacks do not fit in LDS runs with fewer threads
     const size_t lane_bytes = (size_t)(p.stack_depth + (WIDE ? 3 : 1)) * sizeof(int);
-    // the boolean staging windows (per wave), after the stacks and the top nodes
+    // the boolean staging windows (per wave), after the top nodes and the stacks
     const bool staged = MODE == MODE_BOOL && !STATS && p.stage_ok && p.items == nullptr && p.order == nullptr;
     const size_t wave_stage = staged ? kStageWaveWords * sizeof(uint32_t) : 0;
-    while (block > 64 && lane_bytes * block + wave_stage * (block / 64) > (size_t)lds_block)
+    const size_t spare = 64 * sizeof(int);  // the row below the first stack
+    while (block > 64 && spare + lane_bytes * block + wave_stage * (block / 64) > (size_t)lds_block)
         block /= 2;
-    const size_t stack_bytes = lane_bytes * block;
+    const size_t stack_bytes = spare + lane_bytes * block;
     const size_t stage_bytes = wave_stage * (size_t)(block / 64);
     TravParams q = p;
     q.top_lds = 0;
