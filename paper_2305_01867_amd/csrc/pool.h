@@ -151,8 +151,9 @@ struct Pool {
     int slots, cap;         // cap: entries of `node`
     int ns, ls;             // entries in use (wave-uniform)
     uint64_t lost;          // slots with an entry that found no room (wave-uniform)
-    const float4 *top_cache;  // the tree's first top_lds nodes in LDS
-    int top_lds, ref_last;
+    int top_lds;            // the tree's first top_lds nodes are in LDS, from address 0
+    int ref_last;
+    bool far;
 
     __device__ __forceinline__ void init(const TravParams &p, uint32_t *words, int n_slots, int node_cap) {
         node = words;
@@ -162,8 +163,8 @@ struct Pool {
         cap = node_cap;
         ns = ls = 0;
         lost = 0;
-        top_cache = nullptr;
         top_lds = 0;
+        far = far_nodes(p.nt);
         ref_last = (int)p.nt - 2 + kTopSlots;
     }
     __device__ __forceinline__ float *list(int slot) {
@@ -210,36 +211,15 @@ struct Pool {
         int c0 = 0, c1 = 0, c2 = 0, c3 = 0;
         if (on && (MODE != MODE_BOOL || tlimit >= 0.0f)) {
             const int offx = inv.x < 0.0f ? 16 : 0, offy = inv.y < 0.0f ? 48 : 32, offz = inv.z < 0.0f ? 80 : 64;
-            float4 nx, fx, ny, fy, nz, fz;
-            int4 ch;
-            if (ref < top_lds) {
-                const LdsBytes c = (LdsBytes)(top_cache + 8 * ref);
-                nx = lds_f4(c + offx);
-                fx = lds_f4(c + (offx ^ 16));
-                ny = lds_f4(c + offy);
-                fy = lds_f4(c + (offy ^ 16));
-                nz = lds_f4(c + offz);
-                fz = lds_f4(c + (offz ^ 16));
-                const float4 cf = lds_f4(c + 96);
-                ch = make_int4(__float_as_int(cf.x), __float_as_int(cf.y), __float_as_int(cf.z), __float_as_int(cf.w));
-            } else {
-                const char *c = reinterpret_cast<const char *>(p.top4 + ref);
-                nx = *reinterpret_cast<const float4 *>(c + offx);
-                fx = *reinterpret_cast<const float4 *>(c + (offx ^ 16));
-                ny = *reinterpret_cast<const float4 *>(c + offy);
-                fy = *reinterpret_cast<const float4 *>(c + (offy ^ 16));
-                nz = *reinterpret_cast<const float4 *>(c + offz);
-                fz = *reinterpret_cast<const float4 *>(c + (offz ^ 16));
-                ch = *reinterpret_cast<const int4 *>(c + 96);
-            }
-            h0 = slab_nf(nx.x, fx.x, ny.x, fy.x, nz.x, fz.x, inv, nn, nf, tlimit, k0);
-            h1 = slab_nf(nx.y, fx.y, ny.y, fy.y, nz.y, fz.y, inv, nn, nf, tlimit, k1);
-            h2 = slab_nf(nx.z, fx.z, ny.z, fy.z, nz.z, fz.z, inv, nn, nf, tlimit, k2);
-            h3 = slab_nf(nx.w, fx.w, ny.w, fy.w, nz.w, fz.w, inv, nn, nf, tlimit, k3);
-            c0 = ch.x;
-            c1 = ch.y;
-            c2 = ch.z;
-            c3 = ch.w;
+            const NodeRows c = fetch_node(p.top4, ref, top_lds, far, offx, offy, offz);
+            h0 = slab_nf(c.nx.x, c.fx.x, c.ny.x, c.fy.x, c.nz.x, c.fz.x, inv, nn, nf, tlimit, k0);
+            h1 = slab_nf(c.nx.y, c.fx.y, c.ny.y, c.fy.y, c.nz.y, c.fz.y, inv, nn, nf, tlimit, k1);
+            h2 = slab_nf(c.nx.z, c.fx.z, c.ny.z, c.fy.z, c.nz.z, c.fz.z, inv, nn, nf, tlimit, k2);
+            h3 = slab_nf(c.nx.w, c.fx.w, c.ny.w, c.fy.w, c.nz.w, c.fz.w, inv, nn, nf, tlimit, k3);
+            c0 = c.ch.x;
+            c1 = c.ch.y;
+            c2 = c.ch.z;
+            c3 = c.ch.w;
         }
         if (PROP) {
             const int skip = from_lane(from, s.skip);
@@ -251,15 +231,17 @@ struct Pool {
         if (MODE != MODE_COUNT) {
             // the nearest children of all lanes on top
             const int nh = (int)h0 + (int)h1 + (int)h2 + (int)h3;
-            k0 = h0 ? k0 : INFINITY;
-            k1 = h1 ? k1 : INFINITY;
-            k2 = h2 ? k2 : INFINITY;
-            k3 = h3 ? k3 : INFINITY;
-            order2(k0, c0, k1, c1);
-            order2(k2, c2, k3, c3);
-            order2(k0, c0, k2, c2);
-            order2(k1, c1, k3, c3);
-            order2(k1, c1, k2, c2);
+            double s0 = sort_key(h0, k0, c0), s1 = sort_key(h1, k1, c1);
+            double s2 = sort_key(h2, k2, c2), s3 = sort_key(h3, k3, c3);
+            order2(s0, s1);
+            order2(s2, s3);
+            order2(s0, s2);
+            order2(s1, s3);
+            order2(s1, s2);
+            c0 = key_child(s0);
+            c1 = key_child(s1);
+            c2 = key_child(s2);
+            c3 = key_child(s3);
             h0 = nh > 0;
             h1 = nh > 1;
             h2 = nh > 2;

@@ -10,12 +10,25 @@ namespace {
 struct PoolShape {
     int slots, cap, leaves;
 };
-constexpr int kPoolBlock = 256;
-constexpr int kPoolNodes = 1024;  // node entries per wave (64 segments in flight keep a few hundred)
-// Resident waves per CU: 16, what the registers allow; count mode 12, what
-// the lists of hits leave in LDS (11.3 KB a wave).
+// Node entries per wave (64 segments in flight keep a few hundred).  Count
+// mode, whose lists of hits take 5.9 KB a wave: 384, so that 16 waves and part
+// of the tree's top fit (4e6 segments at the paper's scale: 12 waves of 1024
+// entries 1,990 us, 16 of 512 1,890; with the top 12 / 512 1,935, 16 / 512
+// 1,765, 16 / 384 1,741, 16 / 256, which run out of entries, 2,145).
 template <int MODE>
-constexpr int kPoolWavesPerCU = MODE == MODE_COUNT ? 12 : 16;
+constexpr int kPoolNodes = MODE == MODE_COUNT ? 384 : 1024;
+// Resident waves per CU, what the registers allow.
+constexpr int kPoolWavesPerCU = 16;
+// From this many segments per CU on the tree's top is kept in LDS: at least
+// twelve for each wave, whose steps then spend less on fetches than the copy of
+// 20 to 64 KB costs (522,242 triangles, nearest hit: 1e5 segments 136 -> 112 us,
+// 3.9e5 357 -> 277; 7,938 triangles: 5e4 56 -> 53, 3.9e5 186 -> 171, but 1e4 39 -> 41).
+constexpr int kPoolTopMin = 192;
+
+// Threads of a workgroup.  With the tree's top in LDS (TOP) one workgroup has
+// all of a CU's waves, so there is one copy of it.
+template <bool TOP>
+constexpr int kPoolBlock = TOP ? 64 * kPoolWavesPerCU : 256;
 
 // Each wave owns a contiguous range of segments; with more segments than are
 // in flight at once the last 1/kPoolTailDiv of them is a pool of
@@ -42,15 +55,30 @@ __device__ __forceinline__ void mesh_of(const TravParams &p, int64_t ray, int &r
     }
 }
 
-template <int MODE, bool CERT>
-__global__ __launch_bounds__(kPoolBlock, kPoolWavesPerCU<MODE> / 4) void k_pool(TravParams p, PoolShape sh) {
-    constexpr int kWords = pool_words<MODE, CERT>(64, kPoolNodes);
-    __shared__ uint32_t words[kWords * (kPoolBlock / 64)];
+template <int MODE, bool CERT, bool TOP>
+__global__ __launch_bounds__(kPoolBlock<TOP>, kPoolWavesPerCU / 4) void k_pool(TravParams p, PoolShape sh) {
+    constexpr int kWords = pool_words<MODE, CERT>(64, kPoolNodes<MODE>);
+    constexpr int kBlock = kPoolBlock<TOP>;
+    uint32_t *words;
+    int top_n = 0;
+    if constexpr (TOP) {
+        extern __shared__ float4 lds_dyn[];  // the tree's top, then the waves' words
+        if ((uint32_t)(uintptr_t)(LdsInt)(int *)lds_dyn == 0)  // (no static LDS: so it is)
+            top_n = p.top_lds;
+        const float4 *src = reinterpret_cast<const float4 *>(p.top4);
+        for (int i = threadIdx.x; i < 8 * top_n; i += kBlock)
+            lds_dyn[i] = src[i];
+        __syncthreads();
+        words = reinterpret_cast<uint32_t *>(lds_dyn + 8 * p.top_lds);
+    } else {
+        __shared__ uint32_t fixed[kWords * (kBlock / 64)];
+        words = fixed;
+    }
     const int lane = threadIdx.x & 63;
     const float scale = p.bounds[6];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t waves = (int64_t)gridDim.x * (kPoolBlock / 64);
-    const int64_t wave_id = (int64_t)blockIdx.x * (kPoolBlock / 64) + wave;
+    const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
+    const int64_t wave_id = (int64_t)blockIdx.x * (kBlock / 64) + wave;
     const int64_t n_static = p.n <= waves * sh.slots ? p.n : p.n - p.n / kPoolTailDiv;
     int64_t cursor = n_static * wave_id / waves;
     int64_t range_end = n_static * (wave_id + 1) / waves;
@@ -58,6 +86,7 @@ __global__ __launch_bounds__(kPoolBlock, kPoolWavesPerCU<MODE> / 4) void k_pool(
 
     Pool<MODE, CERT, false> pool;
     pool.init(p, words + wave * kWords, sh.slots, sh.cap);
+    pool.top_lds = top_n;
     PoolSegment<MODE, CERT> s;
     s.ray = -1;
     s.toff = 0;
@@ -190,16 +219,25 @@ __global__ __launch_bounds__(kPoolBlock, kPoolWavesPerCU<MODE> / 4) void k_pool(
     }
 }
 
-template <int MODE, bool CERT>
-void launch(const TravParams &p, hipStream_t s) {
-    int dev = 0, cus = 256;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+template <int MODE, bool CERT, bool TOP>
+void launch_shape(const TravParams &p, int cus, hipStream_t s) {
+    constexpr int kBlock = kPoolBlock<TOP>, kWaves = kBlock / 64;
+    constexpr size_t kBytes = TOP ? (size_t)pool_words<MODE, CERT>(64, kPoolNodes<MODE>) * 4 * kWaves : 0;
+    TravParams q = p;
+    q.top_lds = 0;
+    size_t lds = 0;
+    if constexpr (TOP) {
+        static_assert(kBytes + sizeof(Node4) < 160 * 1024, "the waves' words leave room for nodes");
+        constexpr int kRoom = (int)((160 * 1024 - kBytes) / sizeof(Node4));
+        q.top_lds = kRoom < kTopSlots ? kRoom : kTopSlots;
+        lds = kBytes + (size_t)q.top_lds * sizeof(Node4);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_pool<MODE, CERT, TOP>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    }
     int per_cu = 0;
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, reinterpret_cast<const void *>(&k_pool<MODE, CERT>), kPoolBlock, 0);
-    constexpr int kWaves = kPoolBlock / 64;
-    per_cu = per_cu < kPoolWavesPerCU<MODE> / kWaves ? per_cu : kPoolWavesPerCU<MODE> / kWaves;
+        &per_cu, reinterpret_cast<const void *>(&k_pool<MODE, CERT, TOP>), kBlock, lds);
+    per_cu = per_cu < kPoolWavesPerCU / kWaves ? per_cu : kPoolWavesPerCU / kWaves;
     per_cu = per_cu < 1 ? 1 : per_cu;
     const int64_t resident = (int64_t)cus * per_cu;
     // few segments: as few per wave as fill the resident waves (so the lanes
@@ -207,11 +245,22 @@ void launch(const TravParams &p, hipStream_t s) {
     const int64_t share = (p.n + resident * kWaves - 1) / (resident * kWaves);
     PoolShape sh;
     sh.slots = (int)(share < 64 ? share : 64);
-    sh.cap = p.pool_cap < kPoolNodes ? p.pool_cap : kPoolNodes;
+    sh.cap = p.pool_cap < kPoolNodes<MODE> ? p.pool_cap : kPoolNodes<MODE>;
     sh.leaves = sh.slots <= 32 ? 32 : 64;
     const int64_t per_block = (int64_t)sh.slots * kWaves;
     const int64_t want = (p.n + per_block - 1) / per_block;
-    k_pool<MODE, CERT><<<(int)(want < resident ? want : resident), kPoolBlock, 0, s>>>(p, sh);
+    k_pool<MODE, CERT, TOP><<<(int)(want < resident ? want : resident), kBlock, lds, s>>>(q, sh);
+}
+
+template <int MODE, bool CERT>
+void launch(const TravParams &p, hipStream_t s) {
+    int dev = 0, cus = 256;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (p.n >= (int64_t)cus * kPoolTopMin)
+        launch_shape<MODE, CERT, true>(p, cus, s);
+    else
+        launch_shape<MODE, CERT, false>(p, cus, s);
 }
 
 }  // namespace

@@ -313,15 +313,66 @@ __device__ __forceinline__ float4 lds_f4(LdsBytes p) {
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// Compare-exchange of (entry t, child) pairs: the nearer first.
-__device__ __forceinline__ void order2(float &ka, int &ca, float &kb, int &cb) {
-    const bool sw = kb < ka;
-    const float lo = fminf(ka, kb), hi = fmaxf(ka, kb);
-    const int cl = sw ? cb : ca, ch = sw ? ca : cb;
-    ka = lo;
-    kb = hi;
-    ca = cl;
-    cb = ch;
+typedef __attribute__((address_space(3))) int *LdsInt;
+
+// A 4-wide node as a segment sees it: each row a face of all four children,
+// near and far faces chosen by the segment's signs (offx, offy, offz: byte
+// offsets of the near rows, the far row being the other of each pair).  The
+// first top_n nodes come from LDS, where the tree's top lies from address 0, so
+// that a node's byte offset is its address there too; the others are at 32-bit
+// offsets from the tree's first node (nodes4 follows top4: one address for both
+// kinds of reference), or, from 4 GB of nodes on (far), at 64-bit addresses.
+struct NodeRows {
+    float4 nx, fx, ny, fy, nz, fz;
+    int4 ch;
+};
+__device__ __forceinline__ float4 node_row(const char *p) { return *reinterpret_cast<const float4 *>(p); }
+__device__ __forceinline__ bool far_nodes(int64_t nt) {
+    return (nt + kTopSlots) * (int64_t)sizeof(Node4) > INT64_C(0xffffffff);
+}
+__device__ __forceinline__ NodeRows fetch_node(const Node4 *__restrict__ top4, int ref, int top_n, bool far, int offx,
+                                               int offy, int offz) {
+    NodeRows r;
+    const uint32_t at = (uint32_t)ref << 7;
+    auto fetch = [&](auto row) {
+        r.nx = row(at + offx);
+        r.fx = row(at + (offx ^ 16));
+        r.ny = row(at + offy);
+        r.fy = row(at + (offy ^ 16));
+        r.nz = row(at + offz);
+        r.fz = row(at + (offz ^ 16));
+        const float4 cf = row(at + 96u);
+        r.ch = make_int4(__float_as_int(cf.x), __float_as_int(cf.y), __float_as_int(cf.z), __float_as_int(cf.w));
+    };
+    if (ref < top_n)
+        fetch([](uint32_t o) { return lds_f4((LdsBytes)o); });
+    else if (!far)
+        fetch([&](uint32_t o) { return node_row(reinterpret_cast<const char *>(top4) + o); });
+    else  // (o - at: the row's offset in the node)
+        fetch([&](uint32_t o) { return node_row(reinterpret_cast<const char *>(top4 + ref) + (o - at)); });
+    // (the references are moved into their keys here, not in the branches,
+    // which would wait for the loads there)
+    asm("" : "+v"(r.ch.x), "+v"(r.ch.y), "+v"(r.ch.z), "+v"(r.ch.w));
+    return r;
+}
+
+// A child's sort key: its entry t (>= 0; +inf if the segment misses it) as the
+// high word of a double, its reference as the low word.  Doubles of one sign
+// order as their bits do and an infinite float makes a finite double, so two
+// instructions exchange keys and references together where comparing the floats
+// took a compare, a minimum, a maximum and two selects; equal t order by the
+// references.  (Instructions, not fmin / fmax: those would first quiet
+// signalling NaNs, which no key is.)
+__device__ __forceinline__ double sort_key(bool h, float t, int c) {
+    return __hiloint2double(h ? __float_as_int(t) : 0x7f800000, c);
+}
+__device__ __forceinline__ int key_child(double k) { return __double2loint(k); }
+__device__ __forceinline__ void order2(double &a, double &b) {
+    double lo, hi;
+    asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(a), "v"(b));
+    asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(a), "v"(b));
+    a = lo;
+    b = hi;
 }
 
 }  // namespace

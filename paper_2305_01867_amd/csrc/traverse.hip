@@ -81,28 +81,6 @@ constexpr int kStageWin = 256;
 constexpr int kStageWords = 2 * kStageWin / 32 + 1;  // value bits, done bits, count
 constexpr int kStageWaveWords = 2 * kStageWords + 2;  // two windows, padded to 16 bytes
 
-typedef __attribute__((address_space(3))) int *LdsInt;
-__device__ __forceinline__ float4 node_row(const char *p) { return *reinterpret_cast<const float4 *>(p); }
-
-// A child's sort key: its entry t (>= 0; +inf if the segment misses it) as the
-// high word of a double, its reference as the low word.  Doubles of one sign
-// order as their bits do and an infinite float makes a finite double, so two
-// instructions exchange keys and references together where comparing the floats
-// took a compare, a minimum, a maximum and two selects; equal t order by the
-// references.  (Instructions, not fmin / fmax: those would first quiet
-// signalling NaNs, which no key is.)
-__device__ __forceinline__ double sort_key(bool h, float t, int c) {
-    return __hiloint2double(h ? __float_as_int(t) : 0x7f800000, c);
-}
-__device__ __forceinline__ int key_child(double k) { return __double2loint(k); }
-__device__ __forceinline__ void order2(double &a, double &b) {
-    double lo, hi;
-    asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(a), "v"(b));
-    asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(a), "v"(b));
-    a = lo;
-    b = hi;
-}
-
 // PROP: proposal-first order.  Phase 0 traverses the predicted frontier
 // subtree; phase 1 the whole tree with that subtree left out.  Together they
 // visit exactly what the plain order visits, so results do not change.
@@ -130,7 +108,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     const float scale = p.bounds[6];
     const int n_internal = (int)p.nt - 1;
     const int max_steps = 2 * (int)p.nt + 8;  // N_t < 2^30
-    const bool far = ((int64_t)p.nt + kTopSlots) * (int64_t)sizeof(Node4) > INT64_C(0xffffffff);
+    const bool far = far_nodes(p.nt);
     const int ref_lim = WIDE ? n_internal + kTopSlots : n_internal;
     float4 *top_cache = reinterpret_cast<float4 *>(lds_stack);
     const int group = p.n_groups > 0 ? (int)(blockIdx.x % p.n_groups) : 0;
@@ -499,41 +477,13 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                         // four children per fetch; the hits after the next one
                         // go on the stack, at most three slots past sp (the
                         // lane has three spare slots past stack_depth)
-                        // each load fetches a face row of all four children:
-                        // near and far faces chosen by the segment's signs
-                        float4 nx, fx, ny, fy, nz, fz;
-                        int4 ch;
-                        const uint32_t at = (uint32_t)ref << 7;
-                        auto fetch = [&](auto row) {
-                            nx = row(at + offx);
-                            fx = row(at + (offx ^ 16));
-                            ny = row(at + offy);
-                            fy = row(at + (offy ^ 16));
-                            nz = row(at + offz);
-                            fz = row(at + (offz ^ 16));
-                            const float4 cf = row(at + 96u);
-                            ch = make_int4(__float_as_int(cf.x), __float_as_int(cf.y), __float_as_int(cf.z),
-                                           __float_as_int(cf.w));
-                        };
-                        // nodes4 follows top4: one address for both kinds of
-                        // reference, 32-bit offsets from it below 4 GB of nodes
-                        if (ref < top_n)
-                            fetch([](uint32_t o) { return lds_f4((LdsBytes)o); });
-                        else if (!far)
-                            fetch([&](uint32_t o) { return node_row(reinterpret_cast<const char *>(p.top4) + o); });
-                        else  // (o - at: the row's offset in the node)
-                            fetch([&](uint32_t o) {
-                                return node_row(reinterpret_cast<const char *>(p.top4 + ref) + (o - at));
-                            });
-                        // (the references are moved into their keys here, not in the
-                        // branches, which would wait for the loads there)
-                        asm("" : "+v"(ch.x), "+v"(ch.y), "+v"(ch.z), "+v"(ch.w));
+                        const NodeRows c = fetch_node(p.top4, ref, top_n, far, offx, offy, offz);
                         float k0, k1, k2, k3;
-                        bool h0 = slab_nf(nx.x, fx.x, ny.x, fy.x, nz.x, fz.x, r.inv, nn, nf, tlimit, k0);
-                        bool h1 = slab_nf(nx.y, fx.y, ny.y, fy.y, nz.y, fz.y, r.inv, nn, nf, tlimit, k1);
-                        bool h2 = slab_nf(nx.z, fx.z, ny.z, fy.z, nz.z, fz.z, r.inv, nn, nf, tlimit, k2);
-                        bool h3 = slab_nf(nx.w, fx.w, ny.w, fy.w, nz.w, fz.w, r.inv, nn, nf, tlimit, k3);
-                        int c0 = ch.x, c1 = ch.y, c2 = ch.z, c3 = ch.w;
+                        bool h0 = slab_nf(c.nx.x, c.fx.x, c.ny.x, c.fy.x, c.nz.x, c.fz.x, r.inv, nn, nf, tlimit, k0);
+                        bool h1 = slab_nf(c.nx.y, c.fx.y, c.ny.y, c.fy.y, c.nz.y, c.fz.y, r.inv, nn, nf, tlimit, k1);
+                        bool h2 = slab_nf(c.nx.z, c.fx.z, c.ny.z, c.fy.z, c.nz.z, c.fz.z, r.inv, nn, nf, tlimit, k2);
+                        bool h3 = slab_nf(c.nx.w, c.fx.w, c.ny.w, c.fy.w, c.nz.w, c.fz.w, r.inv, nn, nf, tlimit, k3);
+                        int c0 = c.ch.x, c1 = c.ch.y, c2 = c.ch.z, c3 = c.ch.w;
                         if (PROP) {  // in phase 1 the proposed subtree is done already
                             h0 = h0 && c0 != skip;
                             h1 = h1 && c1 != skip;
@@ -831,7 +781,6 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
         // one segment).
         Pool<MODE, CERT, PROP> pool;
         pool.init(p, reinterpret_cast<uint32_t *>(stk), 64, wave_stack - kPoolLeafCap - 64);
-        pool.top_cache = top_cache;
         pool.top_lds = top_n;
         PoolSegment<MODE, CERT> s;
         s.reset();
@@ -1647,7 +1596,7 @@ TravParams make_params(const MeshDev &m, const TraverseArgs &a) {
 
 // Does the first pass run in pool form (pool.hip)?  In count mode always: it
 // visits every candidate in any order, and the pool keeps the lanes busy
-// (1e7 segments of the paper's scale 6.30 -> 4.83 ms, 1e6 0.93 -> 0.57).  In
+// (4e6 segments at the paper's scale 2.50 -> 1.74 ms).  In
 // the other modes up to one and a half times the lanes that are resident at
 // once (393,216): below that the launch is its slowest segments (1e4 segments
 // 156 -> 35 us, 1e5 against 526k triangles 293 -> 114, 2.5e5 at the paper's
