@@ -1597,12 +1597,15 @@ TravParams make_params(const MeshDev &m, const TraverseArgs &a) {
 // Does the first pass run in pool form (pool.hip)?  In count mode always: it
 // visits every candidate in any order, and the pool keeps the lanes busy
 // (4e6 segments at the paper's scale 2.50 -> 1.74 ms).  In
-// the other modes up to one and a half times the lanes that are resident at
-// once (393,216): below that the launch is its slowest segments (1e4 segments
-// 156 -> 35 us, 1e5 against 526k triangles 293 -> 114, 2.5e5 at the paper's
-// scale 175 -> 120); above it a lane's nearest-first walk with its last
-// segments shared does less work (5e5: 198 against 224 us, 1e6: 292 / 388).
-// A launch shape the caller chose is the lane form's.
+// the other modes up to the lanes that are resident at once (262,144): below
+// that a launch of the lane form is its slowest segments (1e4 segments 156 -> 35
+// us, 1e5 against 522,242 triangles 150 -> 88, 2e5 at the paper's scale 134 ->
+// 78); up to twice as many on meshes of at most kPoolSmallMesh triangles, whose
+// nodes stay in an XCD's L2.  Above that a lane's nearest-first walk does less
+// work (boolean, pool / lane form: 32,258 triangles 5e5 154 / 166 us, 6e5 187 /
+// 178; 130,050 3e5 167 / 174, 3.9e5 200 / 186; 522,242 2.6e5 163 / 180, 3e5
+// 190 / 178).  A launch shape the caller chose is the lane form's.
+constexpr int64_t kPoolSmallMesh = 65536;
 bool use_pool(const TravParams &p, const TraverseArgs &a) {
     if (!a.default_shape || p.nodes4 == nullptr || a.bucket != nullptr || p.nt > kMaxPoolTris)
         return false;
@@ -1611,7 +1614,7 @@ bool use_pool(const TravParams &p, const TraverseArgs &a) {
     int dev = 0, cus = 256;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    return a.n <= (int64_t)cus * kDefaultWavesPerCU * 64 * 3 / 2;
+    return a.n <= (int64_t)cus * kDefaultWavesPerCU * 64 * (p.nt <= kPoolSmallMesh ? 2 : 1);
 }
 
 // Keys and a stable sort of the segment indices; p.order then lists them.

@@ -35,3 +35,18 @@ def test_pool_with_the_top_in_lds(grid, over):
             plain = host(rsi.rsi_intersect(mesh, dO, dE, mode=mode, precision="plain")[names[0]])
             same = plain2 == host(want[names[0]])
             assert same.mean() > 0.999 and np.array_equal(plain[same], plain2[same]), mode
+
+
+@pytest.mark.parametrize("per_cu,over", [(1024, 1), (1536, 0), (2048, 0), (2048, 1)])
+def test_pool_past_one_round(per_cu, over):
+    """More segments than are in flight at once, up to twice as many (no chunks
+    at the end) and one past that, against the binary tree's lane form."""
+    V, F = workloads.heightfield(33, 5)
+    n = torch.cuda.get_device_properties(0).multi_processor_count * per_cu + over
+    O, E = workloads.rays_in_box(n, 9, V.min(0), V.max(0))
+    dO, dE = dev(O), dev(E)
+    with rsi.rsi_build(dev(V), dev(F)) as mesh:
+        for mode, name in (("boolean", "hit"), ("first_hit", "tri_id"), ("intercept_count", "count")):
+            want = rsi.rsi_intersect(mesh, dO, dE, mode=mode, precision="certified", node_width=2)
+            got = rsi.rsi_intersect(mesh, dO, dE, mode=mode, precision="certified")
+            assert np.array_equal(host(got[name]), host(want[name])), mode
