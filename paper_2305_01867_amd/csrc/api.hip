@@ -730,10 +730,10 @@ rsi_status rsi_mesh_export(rsi_mesh mesh, int32_t what, void *dst, int64_t dst_b
 
 // ------------------------------------------------------------------ batch
 constexpr uint32_t kBatchMagic = 0x52534942u;  // "RSIB"
-// Segments per work item of the batched form: a wave spends about 0.35 ms on
-// 512 of them, so the last items end close together (2048-segment items left
-// the launch waiting on a few waves: 3.59 against 2.95 ms for 1.44e7
-// segments; 256-segment items cost more in item changes than they balance).
+// Segments per work item of the batched form: a wave spends about 0.3 ms on
+// 512 of them, so the last items end close together (1.4e7 segments: 1,024 a
+// item 2,710 us, 512 2,525, 256 2,492, 128 2,556; 2e6: 693, 508, 552, 508; sizes
+// that follow the number of segments or shrink towards a group's end: no better).
 constexpr int64_t kBatchChunk = 512;
 
 static bool valid_batch(rsi_batch b) { return b != nullptr && b->magic == kBatchMagic; }
@@ -778,32 +778,49 @@ rsi_status rsi_batch_create(int32_t n_meshes, const int64_t *vertex_offsets, con
     d.root = d.nt >= 2 ? 0 : (d.nt == 1 ? ~0 : INT32_MIN);
     b.M = M;
     b.n_rays = ray_offsets[M];
-    // work items of at most kBatchChunk segments, grouped per XCD: meshes go
-    // to the group with the least estimated cost so far (largest first; cost
-    // ~ segments x log2 triangles), each group's items mesh by mesh
-    std::vector<int> order(M), group_of(M);
-    std::vector<double> cost(M), load(rsi::kItemGroups, 0.0);
+    // work items of at most kBatchChunk segments, mesh by mesh (costliest first),
+    // cut into groups of equal cost (~ segments x log2 triangles); part k of
+    // them is a group on XCD k / (groups per XCD).  A mesh with little in a group
+    // takes no place in its top.
+    std::vector<int> order(M);
+    std::vector<double> unit(M), cost(M);
+    double total_cost = 0.0;
     for (int m = 0; m < M; ++m) {
         order[m] = m;
-        cost[m] = (double)(ray_offsets[m + 1] - ray_offsets[m]) *
-                  std::log2((double)(triangle_offsets[m + 1] - triangle_offsets[m]) + 2.0);
+        unit[m] = std::log2((double)(triangle_offsets[m + 1] - triangle_offsets[m]) + 2.0);
+        cost[m] = (double)(ray_offsets[m + 1] - ray_offsets[m]) * unit[m];
+        total_cost += cost[m];
     }
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost[x] > cost[y]; });
-    for (int m : order) {
-        int g = 0;
-        for (int h = 1; h < rsi::kItemGroups; ++h)
-            g = load[h] < load[g] ? h : g;
-        group_of[m] = g;
-        load[g] += cost[m];
-    }
+    constexpr int kPerXcd = rsi::kItemGroups / rsi::kXcds;
+    std::vector<std::vector<int4>> grouped(rsi::kItemGroups);
+    std::vector<std::vector<double>> part(rsi::kItemGroups, std::vector<double>(M, 0.0));
+    double at = 0.0;
+    for (int m : order)
+        for (int64_t from = ray_offsets[m]; from < ray_offsets[m + 1]; from += kBatchChunk) {
+            const int64_t to = std::min(from + kBatchChunk, ray_offsets[m + 1]);
+            const double c = (double)(to - from) * unit[m];
+            const int k = std::min(rsi::kItemGroups - 1, (int)((at + 0.5 * c) / total_cost * rsi::kItemGroups));
+            const int g = k / kPerXcd + k % kPerXcd * rsi::kXcds;
+            grouped[g].push_back(make_int4(m, (int)from, (int)to, 0));
+            part[g][m] += c;
+            at += c;
+        }
     std::vector<int4> items;
     std::vector<int32_t> group_start(rsi::kItemGroups + 1, 0);
+    std::vector<uint64_t> group_meshes(rsi::kItemGroups, 0);
     for (int g = 0; g < rsi::kItemGroups; ++g) {
         group_start[g] = (int32_t)items.size();
+        items.insert(items.end(), grouped[g].begin(), grouped[g].end());
+        double sum = 0.0;
+        int meshes = 0;
+        for (double c : part[g]) {
+            sum += c;
+            meshes += c > 0.0 ? 1 : 0;
+        }
         for (int m = 0; m < M; ++m)
-            if (group_of[m] == g)
-                for (int64_t a = ray_offsets[m]; a < ray_offsets[m + 1]; a += kBatchChunk)
-                    items.push_back(make_int4(m, (int)a, (int)std::min(a + kBatchChunk, ray_offsets[m + 1]), 0));
+            if (part[g][m] > 0.0 && 4.0 * part[g][m] * meshes >= sum)
+                group_meshes[g] |= 1ull << m;
     }
     group_start[rsi::kItemGroups] = (int32_t)items.size();
     b.n_items = (int)items.size();
@@ -814,9 +831,9 @@ rsi_status rsi_batch_create(int32_t n_meshes, const int64_t *vertex_offsets, con
     // the 4-wide tree (top slots, then one slot per binary internal node)
     const size_t sz_nodes4 = nt > 1 ? round_up(128 * (size_t)(nt - 1 + rsi::kTopSlots)) : 0;
     const size_t sz_roots4 = round_up(4 * (size_t)M) + round_up(4 * (size_t)rsi::kTopSlots);
-    // each XCD group's top and roots, and the mesh -> group map
+    // each group's top, roots and meshes
     const size_t sz_groups = nt > 1 ? round_up(sizeof(rsi::Node4) * rsi::kItemGroups * rsi::kTopSlots) +
-                                          round_up(4 * 64 * rsi::kItemGroups) + round_up(4 * (size_t)M)
+                                          round_up(4 * 64 * rsi::kItemGroups) + round_up(8 * rsi::kItemGroups)
                                     : 0;
     const size_t sz_par = round_up(4 * (size_t)(nt > 0 ? 2 * nt - 1 : 1)), sz_cnt = round_up(4 * (size_t)(nt > 1 ? nt - 1 : 1));
     const size_t sz_tris = round_up(48 * (size_t)nt + 48), sz_small = 256;
@@ -853,7 +870,7 @@ rsi_status rsi_batch_create(int32_t n_meshes, const int64_t *vertex_offsets, con
     if (sz_groups) {
         b.top4g = reinterpret_cast<rsi::Node4 *>(take(round_up(sizeof(rsi::Node4) * rsi::kItemGroups * rsi::kTopSlots)));
         b.roots4g = reinterpret_cast<int32_t *>(take(round_up(4 * 64 * rsi::kItemGroups)));
-        b.mesh_group = reinterpret_cast<int32_t *>(take(round_up(4 * (size_t)M)));
+        b.group_meshes = reinterpret_cast<uint64_t *>(take(round_up(8 * rsi::kItemGroups)));
     }
     d.parent = reinterpret_cast<int32_t *>(take(sz_par));
     d.counters = reinterpret_cast<int32_t *>(take(sz_cnt));
@@ -895,8 +912,8 @@ rsi_status rsi_batch_create(int32_t n_meshes, const int64_t *vertex_offsets, con
     if (e == hipSuccess)
         e = hipMemcpyAsync(b.group_start, group_start.data(), 4 * (size_t)(rsi::kItemGroups + 1),
                            hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && b.mesh_group)
-        e = hipMemcpyAsync(b.mesh_group, group_of.data(), 4 * (size_t)M, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && b.group_meshes)
+        e = hipMemcpyAsync(b.group_meshes, group_meshes.data(), 8 * (size_t)rsi::kItemGroups, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);  // the host vectors go out of scope
     if (e != hipSuccess) {

@@ -118,10 +118,17 @@ struct MeshDev {
     Proposal prop;
 };
 
-// Batched form (batch.hip): many meshes in one BVH.  Its work items are
-// grouped, one group per XCD of the MI355X: the meshes are spread over the
-// groups by estimated cost, so each XCD's L2 holds the trees of a few meshes.
-constexpr int kItemGroups = 8;
+// Batched form (batch.hip): many meshes in one BVH.  Its work items, mesh by
+// mesh, are cut into kItemGroups groups of equal estimated cost.  A group is
+// worked on by the workgroups blockIdx.x mod kItemGroups, all on one XCD, whose
+// LDS holds the top of the few meshes (or the one) that it has a part of;
+// neighbouring groups are on the same XCD, so its L2 holds few trees too.
+// The pass is bound by the L1, which every node fetch past the LDS copy goes
+// through seven times: 64 meshes, 1.4e7 segments 2,746 us with 8 groups, whole
+// meshes each; 2,740 / 2,658 / 2,525 with 8 / 16 / 32 groups of equal cost; five
+// meshes, 2e6 segments 916 and 583 / 568 / 503.
+constexpr int kXcds = 8, kItemGroups = 32;
+static_assert(kItemGroups % kXcds == 0 && kItemGroups <= 48, "as many groups on each XCD; their counters fit before the queue");
 // Batched keys: the mesh id (6 bits, at most 64 meshes) above a 30-bit Morton
 // code over the mesh's own box, kept in 64-bit words.
 constexpr int kBatchMortonBits = 30;
@@ -137,7 +144,7 @@ struct BatchDev {
     int32_t *roots = nullptr;                    // device [M] subtree root (INT32_MIN: empty)
     int32_t *roots4 = nullptr;                   // device [M] the same as 4-wide references
     int32_t *slot_bin = nullptr;                 // device [kTopSlots] binary node of each top slot
-    int32_t *mesh_group = nullptr;               // device [M] item group (XCD) of each mesh
+    uint64_t *group_meshes = nullptr;            // device [kItemGroups] the meshes of each group's top, a bit each
     Node4 *top4g = nullptr;                      // device [kItemGroups][kTopSlots] each group's meshes' top
     int32_t *roots4g = nullptr;                  // device [kItemGroups][64] mesh roots as references in it
     int32_t *tri_mesh = nullptr;                 // device [nt]
@@ -268,7 +275,7 @@ struct TraverseArgs {
     // batched form (NULL items: one mesh)
     const int4 *items = nullptr;          // (mesh, first segment, end segment, 0)
     int n_items = 0;
-    const int32_t *group_start = nullptr; // [n_groups + 1] items grouped per XCD (NULL: one queue)
+    const int32_t *group_start = nullptr; // [n_groups + 1] first item of each group (NULL: one queue)
     int n_groups = 0;
     int n_meshes = 0;
     const int32_t *mesh_root = nullptr;   // subtree root per mesh (INT32_MIN: empty)

@@ -49,7 +49,7 @@ struct TravParams {
     const int32_t *mesh_root;
     const int32_t *mesh_root4;  // the mesh roots as 4-wide references (first pass over 4-wide nodes)
     // batched form, 4-wide, every top slot in LDS: each workgroup keeps the
-    // top of its XCD group's meshes (group blockIdx.x mod n_groups) instead
+    // top of its item group's meshes (group blockIdx.x mod n_groups) instead
     // of the combined tree's, with the mesh roots as references in it
     const Node4 *top4g;
     const int32_t *roots4g;

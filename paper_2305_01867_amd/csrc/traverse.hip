@@ -189,7 +189,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
         }
     };
     bool items_left = batch || n_static < p.n;  // batch items, or the pool's chunks
-    uint32_t groups_done = 0;  // item groups found empty (wave-uniform)
+    bool own_done = false;  // nothing left in this workgroup's item group (wave-uniform)
     int cur_root = p.root, cur_toff = 0;
     int lane_root = p.root, lane_toff = 0;  // of the lane's current segment
 
@@ -333,24 +333,39 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
         if (batch && items_left && cursor >= range_end && idle) {
             int item = -1;
             if (p.group_start) {
-                // items are grouped by XCD (workgroups are spread over the
-                // eight XCDs in turn): this workgroup's group first, so each
-                // XCD's L2 serves a few meshes; then the others, so no XCD
-                // idles while work is left
-#pragma unroll 1
-                for (int t = 0; t < p.n_groups && item < 0; ++t) {
-                    const int g = (group + t) % p.n_groups;
-                    if (groups_done & (1u << g))
-                        continue;
+                // workgroups are spread over the eight XCDs in turn: this
+                // workgroup's group first, whose meshes' tops are in its LDS,
+                // then those on the same XCD, whose trees are in its L2, then
+                // the others, so no XCD idles while work is left.  Where work
+                // is left is read, a lane per group in that order, before an
+                // item is asked for: at the end thousands of waves would queue
+                // up at each counter in turn.
+                const int per = p.n_groups / kXcds;
+                const int mine = (group + lane / per) % kXcds + (group / kXcds + lane % per) % per * kXcds;
+                for (bool own = true;; own = false) {
+                    uint64_t left = own && !own_done ? 1ull : 0ull;
+                    if (!left) {
+                        bool some = false;
+                        if (lane < p.n_groups) {
+                            const uint32_t next = __hip_atomic_load(p.queue_len + kGroupNext + mine, __ATOMIC_RELAXED,
+                                                                    __HIP_MEMORY_SCOPE_AGENT);
+                            some = next < (uint32_t)(p.group_start[mine + 1] - p.group_start[mine]);
+                        }
+                        left = __ballot(some);
+                        if (!left)
+                            break;
+                    }
+                    const int g = __builtin_amdgcn_readlane(mine, __builtin_ctzll(left));
                     uint32_t k = 0;
                     if (lane == 0)
                         k = atomicAdd(p.queue_len + kGroupNext + g, 1u);
                     k = __shfl(k, 0);
                     const int first = p.group_start[g], count = p.group_start[g + 1] - first;
-                    if (k < (uint32_t)count)
+                    if (k < (uint32_t)count) {
                         item = first + (int)k;
-                    else
-                        groups_done |= 1u << g;
+                        break;
+                    }
+                    own_done = own_done || g == group;  // (a group found empty stays so: the loop ends)
                 }
             } else {
                 uint32_t k = 0;

@@ -254,14 +254,14 @@ __global__ __launch_bounds__(kTopSlots) void k_bucket_ref4(const int32_t *__rest
     bucket_refs(bucket_ref, *n_buckets, slot_bin, ref4);
 }
 
-// Batched form: the top of each XCD group's meshes, breadth-first from their
+// Batched form: the top of each item group's meshes, breadth-first from their
 // roots (group g = blockIdx.x), and each mesh's root as a reference in it (a
 // slot for the group's own meshes, the node index + kTopSlots or a leaf
 // reference for the others).  The last workgroup does the same for the combined
 // tree.
 __global__ __launch_bounds__(kTopSlots) void k_top_cache_group(const Node4 *__restrict__ nodes4,
                                                                const int32_t *__restrict__ roots,
-                                                               const int32_t *__restrict__ mesh_group, int M,
+                                                               const uint64_t *__restrict__ group_meshes, int M,
                                                                Node4 *__restrict__ top4g,
                                                                int32_t *__restrict__ roots4g,
                                                                Node4 *__restrict__ combined, int32_t *slot_bin,
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kTopSlots) void k_top_cache_group(const Node4 *__re
     }
     // the group's internal roots in mesh order take the first slots
     if (tid < 64) {
-        const bool mine = tid < M && mesh_group[tid] == g && roots[tid] >= 0;
+        const bool mine = tid < M && (group_meshes[g] >> tid & 1u) && roots[tid] >= 0;
         const uint64_t all = __ballot(mine);  // the whole wave votes: not inside a lane branch
         const int k = __popcll(all & (lane ? (~0ull >> (64 - lane)) : 0ull));
         root_slot[tid] = mine ? k : -1;
@@ -347,7 +347,7 @@ hipError_t launch_collapse_batch(MeshDev &m, BatchDev &b, hipStream_t s) {
         return hipSuccess;
     }
     collapse(m, m.nodes4, build_lists(m).flag, kMeshRootFlag, s);
-    k_top_cache_group<<<kItemGroups + 1, kTopSlots, 0, s>>>(m.nodes4, b.roots, b.mesh_group, b.M, b.top4g, b.roots4g,
+    k_top_cache_group<<<kItemGroups + 1, kTopSlots, 0, s>>>(m.nodes4, b.roots, b.group_meshes, b.M, b.top4g, b.roots4g,
                                                             m.top4, b.slot_bin, b.roots4);
     const hipError_t e = hipGetLastError();
     m.node_width = e == hipSuccess ? 4 : 2;
