@@ -212,10 +212,10 @@ struct Pool {
         if (on && (MODE != MODE_BOOL || tlimit >= 0.0f)) {
             const int offx = inv.x < 0.0f ? 16 : 0, offy = inv.y < 0.0f ? 48 : 32, offz = inv.z < 0.0f ? 80 : 64;
             const NodeRows c = fetch_node(p.top4, ref, top_lds, far, offx, offy, offz);
-            h0 = slab_nf(c.nx.x, c.fx.x, c.ny.x, c.fy.x, c.nz.x, c.fz.x, inv, nn, nf, tlimit, k0);
-            h1 = slab_nf(c.nx.y, c.fx.y, c.ny.y, c.fy.y, c.nz.y, c.fz.y, inv, nn, nf, tlimit, k1);
-            h2 = slab_nf(c.nx.z, c.fx.z, c.ny.z, c.fy.z, c.nz.z, c.fz.z, inv, nn, nf, tlimit, k2);
-            h3 = slab_nf(c.nx.w, c.fx.w, c.ny.w, c.fy.w, c.nz.w, c.fz.w, inv, nn, nf, tlimit, k3);
+            h0 = slab_nf<MODE == MODE_BOOL>(c.nx.x, c.fx.x, c.ny.x, c.fy.x, c.nz.x, c.fz.x, inv, nn, nf, tlimit, k0);
+            h1 = slab_nf<MODE == MODE_BOOL>(c.nx.y, c.fx.y, c.ny.y, c.fy.y, c.nz.y, c.fz.y, inv, nn, nf, tlimit, k1);
+            h2 = slab_nf<MODE == MODE_BOOL>(c.nx.z, c.fx.z, c.ny.z, c.fy.z, c.nz.z, c.fz.z, inv, nn, nf, tlimit, k2);
+            h3 = slab_nf<MODE == MODE_BOOL>(c.nx.w, c.fx.w, c.ny.w, c.fy.w, c.nz.w, c.fz.w, inv, nn, nf, tlimit, k3);
             c0 = c.ch.x;
             c1 = c.ch.y;
             c2 = c.ch.z;
@@ -229,7 +229,7 @@ struct Pool {
             h3 = h3 && c3 != skip;
         }
         if (MODE != MODE_COUNT) {
-            // the nearest children of all lanes on top
+            // each lane's first child (slab_nf) on top
             const int nh = (int)h0 + (int)h1 + (int)h2 + (int)h3;
             double s0 = sort_key(h0, k0, c0), s1 = sort_key(h1, k1, c1);
             double s2 = sort_key(h2, k2, c2), s3 = sort_key(h3, k3, c3);

@@ -133,15 +133,22 @@ __device__ __forceinline__ bool slab(float xlo, float xhi, float ylo, float yhi,
 // lo <= hi the sign picks exactly the operands min / max pick in slab(), so
 // the decisions are the same bit for bit; a box that is +inf on every face
 // still misses.
+// `order` is what the children a segment meets are visited by, the smallest
+// first.  Nearest hits: the entry t, since a hit found early shrinks the limit.
+// Boolean: minus the length of the segment's way through the box, since the
+// longer it is the likelier a hit, and the first hit ends the search (by the entry
+// t: 1e7 segments at the paper's scale 1,701 us, by this 1,629; 64 meshes 3,167 and
+// 2,990; ways relative to the box, or weighted towards the near: no better).
+template <bool ANY>
 __device__ __forceinline__ bool slab_nf(float nx, float fx, float ny, float fy, float nz, float fz,
                                         const float3 &inv, const float3 &nn, const float3 &nf, float tlimit,
-                                        float &tenter) {
+                                        float &order) {
     const float tnx = fmaf(nx, inv.x, nn.x), tfx = fmaf(fx, inv.x, nf.x);
     const float tny = fmaf(ny, inv.y, nn.y), tfy = fmaf(fy, inv.y, nf.y);
     const float tnz = fmaf(nz, inv.z, nn.z), tfz = fmaf(fz, inv.z, nf.z);
     const float tmin = fmaxf(fmaxf(tnx, tny), fmaxf(tnz, 0.0f));
     const float tmax = fminf(fminf(tfx, tfy), fminf(tfz, tlimit));
-    tenter = tmin;
+    order = ANY ? tmin - tmax : tmin;
     return tmin <= tmax;
 }
 
@@ -356,9 +363,9 @@ __device__ __forceinline__ NodeRows fetch_node(const Node4 *__restrict__ top4, i
     return r;
 }
 
-// A child's sort key: its entry t (>= 0; +inf if the segment misses it) as the
-// high word of a double, its reference as the low word.  Doubles of one sign
-// order as their bits do and an infinite float makes a finite double, so two
+// A child's sort key: its order (slab_nf; +inf if the segment misses it) as the
+// high word of a double, its reference as the low word.  Doubles order as their
+// high words do as floats, and an infinite float makes a finite double, so two
 // instructions exchange keys and references together where comparing the floats
 // took a compare, a minimum, a maximum and two selects; equal t order by the
 // references.  (Instructions, not fmin / fmax: those would first quiet

@@ -494,10 +494,10 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                         // lane has three spare slots past stack_depth)
                         const NodeRows c = fetch_node(p.top4, ref, top_n, far, offx, offy, offz);
                         float k0, k1, k2, k3;
-                        bool h0 = slab_nf(c.nx.x, c.fx.x, c.ny.x, c.fy.x, c.nz.x, c.fz.x, r.inv, nn, nf, tlimit, k0);
-                        bool h1 = slab_nf(c.nx.y, c.fx.y, c.ny.y, c.fy.y, c.nz.y, c.fz.y, r.inv, nn, nf, tlimit, k1);
-                        bool h2 = slab_nf(c.nx.z, c.fx.z, c.ny.z, c.fy.z, c.nz.z, c.fz.z, r.inv, nn, nf, tlimit, k2);
-                        bool h3 = slab_nf(c.nx.w, c.fx.w, c.ny.w, c.fy.w, c.nz.w, c.fz.w, r.inv, nn, nf, tlimit, k3);
+                        bool h0 = slab_nf<MODE == MODE_BOOL>(c.nx.x, c.fx.x, c.ny.x, c.fy.x, c.nz.x, c.fz.x, r.inv, nn, nf, tlimit, k0);
+                        bool h1 = slab_nf<MODE == MODE_BOOL>(c.nx.y, c.fx.y, c.ny.y, c.fy.y, c.nz.y, c.fz.y, r.inv, nn, nf, tlimit, k1);
+                        bool h2 = slab_nf<MODE == MODE_BOOL>(c.nx.z, c.fx.z, c.ny.z, c.fy.z, c.nz.z, c.fz.z, r.inv, nn, nf, tlimit, k2);
+                        bool h3 = slab_nf<MODE == MODE_BOOL>(c.nx.w, c.fx.w, c.ny.w, c.fy.w, c.nz.w, c.fz.w, r.inv, nn, nf, tlimit, k3);
                         int c0 = c.ch.x, c1 = c.ch.y, c2 = c.ch.z, c3 = c.ch.w;
                         if (PROP) {  // in phase 1 the proposed subtree is done already
                             h0 = h0 && c0 != skip;
@@ -507,9 +507,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                         }
                         const int nh = (int)h0 + (int)h1 + (int)h2 + (int)h3;
                         if (MODE != MODE_COUNT) {
-                            // nearest first: a boolean segment meets a hit
-                            // sooner, the nearest-hit modes' shrinking t limit
-                            // prunes the rest
+                            // in the mode's order (slab_nf)
                             double s0 = sort_key(h0, k0, c0), s1 = sort_key(h1, k1, c1);
                             double s2 = sort_key(h2, k2, c2), s3 = sort_key(h3, k3, c3);
                             order2(s0, s1);
