@@ -125,8 +125,8 @@ typedef struct rsi_build_opts {
 
 /* Intersection options; pass NULL for defaults.  With block, stack_depth and
  * waves_per_cu all 0 the first pass over 4-wide nodes takes the form that suits
- * the call: up to 1.5 x 64 x 16 segments per compute unit, and in the
- * intercept-count mode always, the segments of a wave share its lanes through
+ * the call: up to 64 x 16 segments per compute unit (twice that on meshes of at
+ * most 65,536 triangles), and in the intercept-count mode always, the segments of a wave share its lanes through
  * a pool of pending nodes and leaves; otherwise each lane has a segment of its
  * own.  A value other than 0 in any of the three asks for the latter with that
  * shape. */
