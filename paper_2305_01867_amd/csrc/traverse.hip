@@ -45,11 +45,14 @@ namespace {
 // leaf code runs for many lanes at once.
 constexpr int kRefillMin = 8;     // refill when at least this many lanes idle
 // The node phase hands over to the leaf phase once more than 1/kLeafShare of
-// the active lanes wait on a leaf: early for the modes that test few leaves
-// per segment (node steps keep more lanes busy), at half for the count mode,
-// which tests every leaf it reaches (measured on the paper-scale workload).
-template <int MODE>
-constexpr int kLeafShare = MODE == MODE_COUNT ? 2 : 3;
+// the active lanes wait on a leaf: at a third where a leaf test is cheap or ends
+// the search (node steps keep more lanes busy), at half where it costs as much as
+// a node step or more and more lanes should share it: certified nearest hits
+// (3e6 segments of the precision form 1,022 us at a third, 957 at half, 967 at
+// two thirds; the paper's scale 787 / 777 / 820; plain 619 / 620 / 651, boolean
+// 1e7 1,625 / 1,637) and the count mode, which tests every leaf it reaches.
+template <int MODE, bool CERT>
+constexpr int kLeafShare = MODE == MODE_COUNT || (CERT && MODE != MODE_BOOL) ? 2 : 3;
 // Leaves a lane may hold aside while it goes on with internal nodes: two
 // keep more lanes in the node phase (boolean -2%, intercept count -5% at the
 // paper's scale against one; three gain nothing more).
@@ -476,7 +479,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
             if (!w)
                 break;
             const uint64_t waiting = active & ~w;
-            if (kLeafShare<MODE> * __popcll(waiting) > __popcll(active))
+            if (kLeafShare<MODE, CERT> * __popcll(waiting) > __popcll(active))
                 break;
             if (want) {
                 ++steps;
