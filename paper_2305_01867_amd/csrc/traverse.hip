@@ -773,7 +773,6 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                 if (lane == l) {
                     if (MODE == MODE_BOOL)
                         put_hit(ray, 0u);  // written again then
-                    atomicAdd(p.counters + 1, 1ull);
                     ray = -1;
                 }
             }
@@ -796,7 +795,8 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
         // from the beginning (the second pass takes 12 to 20 us for a queue of
         // one segment).
         Pool<MODE, CERT, PROP> pool;
-        pool.init(p, reinterpret_cast<uint32_t *>(stk), 64, wave_stack - kPoolLeafCap - 64);
+        const int room = wave_stack - kPoolLeafCap - 64;
+        pool.init(p, reinterpret_cast<uint32_t *>(stk), 64, room < p.pool_cap ? room : p.pool_cap);
         pool.top_lds = top_n;
         PoolSegment<MODE, CERT> s;
         s.reset();
@@ -852,6 +852,14 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
             pool.push(rest, lane_root, tag);
             wave_lds_fence();
             pool.run(p, s, 0, 64);
+            if (turn == 1) {
+                // they outgrew their stack: those that the second pass now gets
+                // are counted as it gets them (finish), the others here
+                const bool queued = ((pool.lost >> lane) & 1ull) && !(MODE == MODE_BOOL && s.best_id >= 0);
+                const int settled = __popcll(__ballot(ray >= 0 && !queued));
+                if (lane == 0 && settled)
+                    atomicAdd(p.counters + 1, (unsigned long long)settled);
+            }
             if (ray >= 0) {
                 best_late = s.best_late;
                 found = MODE == MODE_BOOL && s.best_id >= 0;
@@ -1601,8 +1609,8 @@ TravParams make_params(const MeshDev &m, const TraverseArgs &a) {
             p.wave_cap = k;
         }
     }
-    // RSI_DEBUG_POOL_NODES=k (1..) shrinks the pool form's node stack, so
-    // tests reach its overflow into the second pass
+    // RSI_DEBUG_POOL_NODES=k (1..) shrinks the node stack of the pool form and
+    // of a wave's last segments, so tests reach their overflow into the second pass
     p.pool_cap = INT32_MAX;
     if (const char *env = getenv("RSI_DEBUG_POOL_NODES"))
         if (atoi(env) >= 1)
