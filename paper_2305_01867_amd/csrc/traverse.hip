@@ -773,6 +773,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                 if (lane == l) {
                     if (MODE == MODE_BOOL)
                         put_hit(ray, 0u);  // written again then
+                    atomicAdd(p.counters + 1, 1ull);
                     ray = -1;
                 }
             }
@@ -852,14 +853,6 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
             pool.push(rest, lane_root, tag);
             wave_lds_fence();
             pool.run(p, s, 0, 64);
-            if (turn == 1) {
-                // they outgrew their stack: those that the second pass now gets
-                // are counted as it gets them (finish), the others here
-                const bool queued = ((pool.lost >> lane) & 1ull) && !(MODE == MODE_BOOL && s.best_id >= 0);
-                const int settled = __popcll(__ballot(ray >= 0 && !queued));
-                if (lane == 0 && settled)
-                    atomicAdd(p.counters + 1, (unsigned long long)settled);
-            }
             if (ray >= 0) {
                 best_late = s.best_late;
                 found = MODE == MODE_BOOL && s.best_id >= 0;
@@ -870,6 +863,8 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                 best_u = s.best_u;
                 best_v = s.best_v;
                 n_redecided += s.redecided;
+                if (turn == 1 && overflow && !found)
+                    atomicAdd(p.counters + 1, ~0ull);  // counted when put off, and again as it is queued now
                 finish();
             }
             pool.lost = 0;
