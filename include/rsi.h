@@ -176,13 +176,13 @@ typedef struct rsi_outputs {
     uint64_t *counters; /* optional [4]: [0] segments re-decided in binary64, [1] segments
                            that outgrew the LDS stack, [2] hitting segments whose answer
                            was not in the proposed bucket (proposal misses), [3] count-mode
-                           segments with more hits than the first pass lists for them
-                           (11 in CERTIFIED precision, 12 in PLAIN), finished by the second
-                           pass.  Zeroed by the call before it counts.  [0] and [1] depend
-                           on the order in which a wave's lanes reach their leaves, and the
-                           last segments of a launch go to whichever waves are free first,
-                           so these two may vary slightly from call to call; the results
-                           never do. */
+                           segments with more distinct hits than the first pass lists for
+                           them (11 in CERTIFIED precision, 12 in PLAIN), finished by the
+                           second pass.  Zeroed by the call before it counts.  [0], [1] and
+                           in CERTIFIED precision [3] depend on the order in which a wave's
+                           lanes reach their leaves, and the last segments of a launch go to
+                           whichever waves are free first, so these may vary slightly from
+                           call to call; the results never do. */
     int32_t *count;     /* [N_r] intercept-count mode: distinct intersections, 0 on a miss */
 } rsi_outputs;
 

@@ -161,8 +161,8 @@ __global__ __launch_bounds__(kPoolBlock<TOP>, kPoolWavesPerCU / 4) void k_pool(T
                 enqueue(p, s.ray, 1);
             } else if (MODE == MODE_COUNT) {
                 const int total = pool.mail[lane];
-                const int m = total & (kPoolMeet - 1);
-                const int kept = m < kCountSlots<CERT> ? m : kCountSlots<CERT>;
+                const bool full = total >= kPoolFull;
+                const int kept = full ? kCountSlots<CERT> : total;
                 const float *l = pool.list(lane);
                 // plain: distinct values; certified: disjoint intervals hold
                 // distinct values, intervals that meet are counted exactly by
@@ -178,9 +178,9 @@ __global__ __launch_bounds__(kPoolBlock<TOP>, kPoolWavesPerCU / 4) void k_pool(T
                     distinct += first ? 1 : 0;
                     meet = meet || !first;
                 }
-                if (CERT && meet && m <= kPoolMeetMost)
+                if (CERT && meet)
                     enqueue(p, s.ray, 0);
-                else if (m > kept)
+                else if (full)
                     enqueue(p, s.ray, 3);
                 else
                     write_count(p.out, s.ray, distinct);
