@@ -670,8 +670,8 @@ def main():
             key = autotune.size_class(args.mode, args.precision, 64, Fb.shape[0], nb)
             choice, timings = autotune.tune(run, key, None, space=space, reps=2)
             choice = {k: v for k, v in choice.items() if k != "ms"}
-            ms_default = min(t["ms"] for t in timings if t["block"] == 1024 and t["stack_depth"] == 20
-                             and t["waves_per_cu"] == 0 and t["ray_sort"] == 0 and t["node_width"] == 0)
+            ms_default = min(t["ms"] for t in timings if t["block"] == t["stack_depth"] == t["waves_per_cu"] == 0
+                             and t["ray_sort"] == 0 and t["node_width"] == 0)
             ms_binary = min(t["ms"] for t in timings if t["node_width"] == 2)
 
             def bstep():
