@@ -133,21 +133,33 @@ def achievable_hbm(reps: int = 5):
     return out
 
 
-def measured_traffic(mode, precision, build):
-    """(HBM bytes per traversal launch, the counter view beside them) from the
-    committed rocprofv3 counter summary, or (None, None) when the traversal
-    source or the tree build differs from the one it was taken with (counters
-    of another kernel say nothing about this one)."""
+# the sources that the traversal kernel is compiled from
+TRAVERSAL_SOURCES = ("traverse.hip", "segment.h", "pool.h", "rsi_internal.h")
+
+
+def traversal_hash():
+    """One sha256 over the traversal kernel's sources, each by name and content."""
     import hashlib
 
+    h = hashlib.sha256()
+    for name in TRAVERSAL_SOURCES:
+        with open(os.path.join(ROOT, "paper_2305_01867_amd", "csrc", name), "rb") as fh:
+            h.update(name.encode() + b"\0" + hashlib.sha256(fh.read()).digest())
+    return h.hexdigest()
+
+
+def measured_traffic(mode, precision, build):
+    """(HBM bytes per traversal launch, the counter view beside them) from the
+    committed rocprofv3 counter summary, or (None, None) when one of the
+    traversal's sources or the tree build differs from what it was taken with
+    (counters of another kernel say nothing about this one)."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None, None
     rec = json.load(open(path)).get(f"{mode}_{precision}")
     if not rec or rec.get("build") != build:
         return None, None
-    src = open(os.path.join(ROOT, "paper_2305_01867_amd", "csrc", "traverse.hip"), "rb").read()
-    if hashlib.sha256(src).hexdigest() != rec["traverse_hip_sha256"]:
+    if rec.get("sources_sha256") != traversal_hash():
         return None, None
     return rec["fetch_bytes_per_launch"] + rec["write_bytes_per_launch"], rec.get("counters")
 
