@@ -45,16 +45,9 @@ __device__ __forceinline__ void mesh_of(const TravParams &p, int64_t ray, int &r
     root = 0;
     toff = 0;
     if (p.items) {
-        int lo = 0, hi = p.n_meshes - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (p.ray_off[mid] <= ray)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        root = p.mesh_root4[lo];
-        toff = p.mesh_toff[lo];
+        const int m = mesh_of_segment(p.ray_off, p.n_meshes, ray);
+        root = p.mesh_root4[m];
+        toff = p.mesh_toff[m];
     }
 }
 

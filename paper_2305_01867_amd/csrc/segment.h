@@ -19,7 +19,7 @@ struct TravParams {
     const Node4 *__restrict__ nodes4;  // the 4-wide tree the first pass walks, or NULL
     const Node4 *__restrict__ top4;    // its first kTopSlots nodes, breadth-first
     int top_lds;                       // how many of them each workgroup keeps in LDS
-    int bary_after;                    // certified barycentric, one mesh: (u, v, t) by k_bary64
+    int bary_after;                    // pool form, certified barycentric: (u, v, t) by k_bary64
     const Tri *__restrict__ tris;
     const float *__restrict__ V;
     const int32_t *__restrict__ F;
@@ -280,6 +280,19 @@ __device__ __forceinline__ MT64 mt64(double ox, double oy, double oz, double ex,
 __device__ __forceinline__ bool valid_tri(const int32_t *__restrict__ F, int64_t nv, int t) {
     const int32_t i0 = F[3 * (int64_t)t], i1 = F[3 * (int64_t)t + 1], i2 = F[3 * (int64_t)t + 2];
     return i0 >= 0 && i1 >= 0 && i2 >= 0 && i0 < nv && i1 < nv && i2 < nv;
+}
+
+// Batched form: the mesh of segment i.
+__device__ __forceinline__ int mesh_of_segment(const int32_t *__restrict__ ray_off, int n_meshes, int64_t i) {
+    int lo = 0, hi = n_meshes - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (ray_off[mid] <= i)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
 }
 
 __device__ __forceinline__ void write_count(const Outs &o, int64_t i, int32_t c) {

@@ -107,7 +107,6 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     const int sp_base = (int)lds0 + 4 * (32 * p.top_lds + stride + wave * wave_stack);
     const int sp_empty = sp_base - kRow + 4 * lane;  // stack positions at or above sp_base hold something
     const int sp_lim = sp_base + p.stack_depth * kRow;  // at or above: more than stack_depth entries
-    const uint64_t lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
     const float scale = p.bounds[6];
     const int n_internal = (int)p.nt - 1;
     const int max_steps = 2 * (int)p.nt + 8;  // N_t < 2^30
@@ -196,7 +195,9 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
     int cur_root = p.root, cur_toff = 0;
     int lane_root = p.root, lane_toff = 0;  // of the lane's current segment
 
-    int64_t ray = -1;
+    // (fewer than 2^31 segments; the staging of flags counts in 64 bits)
+    using RayId = std::conditional_t<MODE == MODE_BOOL, int64_t, int>;
+    RayId ray = -1;
     // the last segments shared by the wave's lanes: where a pool of at least
     // 512 node entries fits in the wave's stacks
     constexpr bool kTail = WIDE && !STATS && MODE != MODE_COUNT;
@@ -289,17 +290,15 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
             } else if (CERT && flagged) {
                 enqueue(p, ray, 0);
             } else if (CERT && MODE == MODE_BARY && best_id >= 0) {
-                if (p.bary_after) {  // (u, v, t) after both passes, a lane per segment
-                    if (p.out.hit)
-                        p.out.hit[ray] = 1;
-                    p.out.id[ray] = best_id - lane_toff;
-                } else {
-                    const float *o = p.from + 3 * ray, *e = p.to + 3 * ray;
-                    const MT64 h = mt64(o[0], o[1], o[2], e[0], e[1], e[2], p.V, p.F, best_id);
-                    write_out(p.out, ray, MODE, best_id - lane_toff, (float)h.u, (float)h.v, (float)h.t);
-                }
+                // (u, v, t) after both passes, a lane per segment (k_bary64):
+                // with the binary64 test here these kernels spilled, or ran
+                // three waves a SIMD instead of four (129 registers)
+                if (p.out.hit)
+                    p.out.hit[ray] = 1;
+                p.out.id[ray] = best_id - lane_toff;
             } else {
-                write_out(p.out, ray, MODE, best_id >= 0 ? best_id - lane_toff : -1, best_u, best_v, best_t);
+                write_out(p.out, ray, MODE, best_id >= 0 ? best_id - lane_toff : -1, CERT ? 0.0f : best_u,
+                          CERT ? 0.0f : best_v, CERT ? 0.0f : best_t);
             }
         }
         ray = -1;
@@ -343,8 +342,11 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                 // is left is read, a lane per group in that order, before an
                 // item is asked for: at the end thousands of waves would queue
                 // up at each counter in turn.
+                int own_group = group;
+                if (MODE == MODE_COUNT)  // worked out here: outside the loop it holds registers that the list needs
+                    asm volatile("" : "+s"(own_group));
                 const int per = p.n_groups / kXcds;
-                const int mine = (group + lane / per) % kXcds + (group / kXcds + lane % per) % per * kXcds;
+                const int mine = (own_group + lane / per) % kXcds + (own_group / kXcds + lane % per) % per * kXcds;
                 for (bool own = true;; own = false) {
                     uint64_t left = own && !own_done ? 1ull : 0ull;
                     if (!left) {
@@ -394,9 +396,9 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
             const int64_t base = cursor;
             cursor = base + cnt < range_end ? base + cnt : range_end;
             if (ray < 0) {
-                const int64_t idx = base + __popcll(idle & lt_mask);
+                const int64_t idx = base + lane_rank(idle);
                 if (idx < range_end) {
-                    ray = p.order ? p.order[idx] : idx;
+                    ray = p.order ? p.order[idx] : (RayId)idx;
                     lane_root = cur_root;
                     lane_toff = cur_toff;
                     ref = lane_root;
@@ -619,8 +621,8 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                         const int c = classify(m, tri, r, lo, hi);
                         bool take = c == kHit;
                         if (c == kUnsure && valid_tri(p.F, p.nv, id)) {
-                            const float *o = p.from + 3 * ray, *e = p.to + 3 * ray;
-                            const MT64 h = mt64(o[0], o[1], o[2], e[0], e[1], e[2], p.V, p.F, id);
+                            const float *e = p.to + 3 * (int64_t)ray;
+                            const MT64 h = mt64(r.o.x, r.o.y, r.o.z, e[0], e[1], e[2], p.V, p.F, id);
                             take = h.hit;
                             lo = __double2float_rd(h.t);
                             hi = __double2float_ru(h.t);
@@ -679,7 +681,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                             // through everything its box overlaps
                             ++n_redecided;
                             if (valid_tri(p.F, p.nv, id)) {
-                                const float *o = p.from + 3 * ray, *e = p.to + 3 * ray;
+                                const float *o = p.from + 3 * (int64_t)ray, *e = p.to + 3 * (int64_t)ray;
                                 hit = mt64(o[0], o[1], o[2], e[0], e[1], e[2], p.V, p.F, id).hit;
                             }
                         }
@@ -694,7 +696,7 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                         // like a sure one, its interval holding the exact t
                         bool hit = c == kHit, exact = false;
                         double t64 = 0.0;
-                        const float *o = p.from + 3 * ray, *e = p.to + 3 * ray;
+                        const float *o = p.from + 3 * (int64_t)ray, *e = p.to + 3 * (int64_t)ray;
                         if (c == kUnsure) {
                             ++n_redecided;
                             hit = false;
@@ -826,8 +828,10 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                 s.ray = (int)ray;
                 n_redecided = 0;
                 if (ray >= 0) {
-                    lane_root = later_root;
-                    lane_toff = later_toff;
+                    if (!PROP) {
+                        lane_root = later_root;
+                        lane_toff = later_toff;
+                    }
                     (void)setup_ray(p.from, p.to, ray, scale, r);  // (finite: it was in flight before)
                     s.set(r);
                     if (PROP) {
@@ -859,9 +863,11 @@ __device__ __forceinline__ void traverse_pass1(TravParams p, int *lds_stack) {
                 flagged = false;
                 overflow = (pool.lost >> lane) & 1ull;
                 best_id = s.best_id;
-                best_t = s.best_t;
-                best_u = s.best_u;
-                best_v = s.best_v;
+                if (!CERT) {
+                    best_t = s.best_t;
+                    best_u = s.best_u;
+                    best_v = s.best_v;
+                }
                 n_redecided += s.redecided;
                 if (turn == 1 && overflow && !found)
                     atomicAdd(p.counters + 1, ~0ull);  // counted when put off, and again as it is queued now
@@ -1093,17 +1099,10 @@ struct Finish {
 __device__ __forceinline__ void segment_root(const TravParams &p, int64_t i, int &root, int &toff) {
     root = p.root;
     toff = 0;
-    if (p.items) {  // batched form: the mesh of segment i
-        int lo = 0, hi = p.n_meshes - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (p.ray_off[mid] <= i)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        root = p.mesh_root[lo];
-        toff = p.mesh_toff[lo];
+    if (p.items) {
+        const int m = mesh_of_segment(p.ray_off, p.n_meshes, i);
+        root = p.mesh_root[m];
+        toff = p.mesh_toff[m];
     }
 }
 
@@ -1364,18 +1363,7 @@ __global__ void k_ray_keys(const float *__restrict__ from, const float *__restri
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n)
         return;
-    int m = 0;
-    if (ray_off) {
-        int lo = 0, hi = n_meshes - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (ray_off[mid] <= i)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        m = lo;
-    }
+    const int m = ray_off ? mesh_of_segment(ray_off, n_meshes, i) : 0;
     const float *b = bounds + 8 * m;
     const float ox = from[3 * i], oy = from[3 * i + 1], oz = from[3 * i + 2];
     const float ex = to[3 * i], ey = to[3 * i + 1], ez = to[3 * i + 2];
@@ -1409,19 +1397,23 @@ __global__ void k_reset(uint32_t *queue_len, unsigned long long *counters, int n
         counters[threadIdx.x] = 0;
 }
 
-// Certified barycentric output of one mesh: the binary64 (u, v, t) of each
-// segment's nearest triangle, from the original corners in the oracle's
-// operation order.  Run after both passes with a lane per segment, so the
-// binary64 work is not spread over the traversal's divergent lanes.
+// Certified barycentric output: the binary64 (u, v, t) of each segment's
+// nearest triangle, from the original corners in the oracle's operation order.
+// Run after both passes with a lane per segment, so the binary64 work is not
+// spread over the traversal's divergent lanes.  Batched form: ray_off and toff
+// give the mesh's first triangle, from which tri_id counts.
 __global__ void k_bary64(const float *__restrict__ from, const float *__restrict__ to, const float *__restrict__ V,
                          const int32_t *__restrict__ F, const int32_t *__restrict__ tri_id, float *__restrict__ uvt,
-                         int64_t n) {
+                         int64_t n, const int32_t *__restrict__ ray_off, const int32_t *__restrict__ toff,
+                         int n_meshes) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n)
         return;
-    const int id = tri_id[i];
+    int id = tri_id[i];
     if (id < 0)
         return;  // a miss: written by the passes
+    if (ray_off)
+        id += toff[mesh_of_segment(ray_off, n_meshes, i)];
     const MT64 h = mt64(from[3 * i], from[3 * i + 1], from[3 * i + 2], to[3 * i], to[3 * i + 1], to[3 * i + 2], V, F,
                         id);
     uvt[3 * i] = (float)h.u;
@@ -1556,7 +1548,7 @@ TravParams make_params(const MeshDev &m, const TraverseArgs &a) {
         p.top4 = nullptr;
     }
     p.top_lds = 0;
-    p.bary_after = (a.mode == MODE_BARY && a.certified && a.items == nullptr && a.uvt != nullptr) ? 1 : 0;
+    p.bary_after = 0;
     p.tris = m.tris;
     p.V = m.V;
     p.F = m.F;
@@ -1669,7 +1661,12 @@ hipError_t launch_intersect(const MeshDev &m, const TraverseArgs &a, hipStream_t
     const hipError_t e = order_segments(a, p, s);
     if (e != hipSuccess)
         return e;
-    if (use_pool(p, a))
+    // Certified barycentric: (u, v, t) by a launch of its own, except for a
+    // batch in pool form, which writes them as it finishes a segment (5,000
+    // segments in 7 meshes: 35.5 us, 37.2 with that launch)
+    const bool pool = use_pool(p, a), bary_after = a.mode == MODE_BARY && a.certified && !(pool && a.items);
+    p.bary_after = bary_after ? 1 : 0;
+    if (pool)
         launch_pool(p, a.mode, a.certified != 0, s);
     else
         dispatch_pass1<false>(p, a.mode, a.certified != 0, a.block, s);
@@ -1686,8 +1683,9 @@ hipError_t launch_intersect(const MeshDev &m, const TraverseArgs &a, hipStream_t
         a.certified ? k_finish<MODE_BARY, true><<<grid2, kFinishThreads, 0, s>>>(p) : k_finish<MODE_BARY, false><<<grid2, kFinishThreads, 0, s>>>(p);
     else
         a.certified ? k_finish<MODE_COUNT, true><<<grid2, kFinishThreads, 0, s>>>(p) : k_finish<MODE_COUNT, false><<<grid2, kFinishThreads, 0, s>>>(p);
-    if (p.bary_after)
-        k_bary64<<<(int)((a.n + 255) / 256), 256, 0, s>>>(a.from, a.to, m.V, m.F, a.tri_id, a.uvt, a.n);
+    if (bary_after)
+        k_bary64<<<(int)((a.n + 255) / 256), 256, 0, s>>>(a.from, a.to, m.V, m.F, a.tri_id, a.uvt, a.n,
+                                                         a.items ? a.ray_off : nullptr, a.mesh_toff, a.n_meshes);
     return hipGetLastError();
 }
 
