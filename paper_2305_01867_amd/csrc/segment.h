@@ -157,23 +157,32 @@ struct MT32 {
     float3 s;
 };
 
-// Binary32 Moller-Trumbore quantities (contraction allowed: the bound below
-// holds for any grouping into fused operations).
+// Binary32 Moller-Trumbore quantities.  The grouping into fused operations is
+// written out, so that every kernel that has this in it gets the same values (the
+// bound below holds for any grouping).
+__device__ __forceinline__ float cross1(float a, float b, float c, float d) {  // a b - c d
+#pragma clang fp contract(off)
+    return __builtin_fmaf(a, b, -(c * d));
+}
+__device__ __forceinline__ float dot1(float ax, float bx, float ay, float by, float az, float bz) {
+#pragma clang fp contract(off)
+    return __builtin_fmaf(az, bz, __builtin_fmaf(ax, bx, ay * by));
+}
 __device__ __forceinline__ MT32 mt32(const Tri &tri, const Ray &r) {
     MT32 m;
     const float3 e1 = make_float3(tri.e1.x, tri.e1.y, tri.e1.z);
     const float3 e2 = make_float3(tri.e2.x, tri.e2.y, tri.e2.z);
     m.s = make_float3(r.o.x - tri.a.x, r.o.y - tri.a.y, r.o.z - tri.a.z);
-    const float px = r.d.y * e2.z - r.d.z * e2.y;
-    const float py = r.d.z * e2.x - r.d.x * e2.z;
-    const float pz = r.d.x * e2.y - r.d.y * e2.x;
-    const float qx = m.s.y * e1.z - m.s.z * e1.y;
-    const float qy = m.s.z * e1.x - m.s.x * e1.z;
-    const float qz = m.s.x * e1.y - m.s.y * e1.x;
-    m.det = e1.x * px + e1.y * py + e1.z * pz;
-    m.U = m.s.x * px + m.s.y * py + m.s.z * pz;
-    m.W = r.d.x * qx + r.d.y * qy + r.d.z * qz;
-    m.T = e2.x * qx + e2.y * qy + e2.z * qz;
+    const float px = cross1(r.d.y, e2.z, r.d.z, e2.y);
+    const float py = cross1(r.d.z, e2.x, r.d.x, e2.z);
+    const float pz = cross1(r.d.x, e2.y, r.d.y, e2.x);
+    const float qx = cross1(m.s.y, e1.z, m.s.z, e1.y);
+    const float qy = cross1(m.s.z, e1.x, m.s.x, e1.z);
+    const float qz = cross1(m.s.x, e1.y, m.s.y, e1.x);
+    m.det = dot1(e1.x, px, e1.y, py, e1.z, pz);
+    m.U = dot1(m.s.x, px, m.s.y, py, m.s.z, pz);
+    m.W = dot1(r.d.x, qx, r.d.y, qy, r.d.z, qz);
+    m.T = dot1(e2.x, qx, e2.y, qy, e2.z, qz);
     return m;
 }
 
