@@ -126,10 +126,10 @@ typedef struct rsi_build_opts {
 /* Intersection options; pass NULL for defaults.  With block, stack_depth and
  * waves_per_cu all 0 the first pass over 4-wide nodes takes the form that suits
  * the call: up to 64 x 16 segments per compute unit (twice that on meshes of at
- * most 65,536 triangles), and in the intercept-count mode always, the segments of a wave share its lanes through
- * a pool of pending nodes and leaves; otherwise each lane has a segment of its
- * own.  A value other than 0 in any of the three asks for the latter with that
- * shape. */
+ * most 65,536 triangles), and in the intercept-count mode always, the segments
+ * of a wave share its lanes through a pool of pending nodes and leaves;
+ * otherwise each lane has a segment of its own.  A value other than 0 in any of
+ * the three asks for the latter with that shape. */
 typedef struct rsi_intersect_opts {
     int32_t precision;    /* rsi_precision; default RSI_PRECISION_PLAIN */
     int32_t block;        /* threads per workgroup of the first pass: 64, 128, 256,
@@ -215,11 +215,12 @@ rsi_status rsi_build(const float *vertices, int64_t n_vertices,
  *   opts                NULL or intersection options
  *   out                 output buffers (see rsi_outputs)
  * Per segment (paper: Background -- tree search for candidates, then the
- * Moller-Trumbore test): traverse the tree from the root, nearer child first,
- * skipping children whose box (conservatively widened, so no binary64 hit is
- * ever culled) the segment misses; test each reached triangle.  Boolean mode
- * stops at the first hit; the other modes keep the nearest and skip boxes that
- * begin beyond it.  n_rays == 0 does nothing.  Limit: n_rays < 2^31.
+ * Moller-Trumbore test): traverse the tree from the root, skipping children
+ * whose box (conservatively widened, so no binary64 hit is ever culled) the
+ * segment misses; test each reached triangle.  Boolean mode takes the child with
+ * the longer way through its box first and stops at the first hit; the
+ * nearest-hit modes take the nearer child first and skip boxes that begin beyond
+ * the best hit; the intercept count visits every candidate in any order.  n_rays == 0 does nothing.  Limit: n_rays < 2^31.
  * Temporary device memory (4 n_rays + 64 bytes, plus what a proposal or a
  * segment order needs) is allocated and freed stream-ordered on `stream`.
  */

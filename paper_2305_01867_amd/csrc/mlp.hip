@@ -736,8 +736,8 @@ __global__ __launch_bounds__(kTThreads) void k_train_tile(TrainArgs a) {
 // bias and loss parts, and with `adam` the Adam step on the fp32 masters and
 // the bf16 copies, in one launch.  Both operands come in the blocks
 // of tile_block, one per MFMA operand: no staging.  A workgroup makes a 32 x 32 tile of
-// one layer (248 of them: about one per CU), wave c the sum over row chunk c
-// of k_chunk rows (in r order, one accumulator per 16 x 16); the chunks are
+// one layer (248 of them: about one per CU), wave c the sum over row chunk c of
+// chunk_tiles tiles (in r order, one accumulator per 16 x 16); the chunks are
 // then added in chunk order from LDS and the step follows in the same lanes,
 // so no partial sum leaves the CU.  XCD x (workgroups are dealt round-robin)
 // gets tiles [31 x, 31 x + 31), half of one layer: 1.2 MB of operands in its

@@ -73,10 +73,12 @@ constexpr float kBoundK = 12.0f * 0x1p-24f;  // >= 8 u32 (binary32) + 8 u64 (bin
 constexpr float kBoundTiny = 0x1p-140f;      // absorbs underflow in the products
 constexpr int kMiss = 0, kHit = 1, kUnsure = 2;
 enum { MODE_BOOL = 0, MODE_FIRST = 1, MODE_BARY = 2, MODE_COUNT = 3 };
-// distinct t a lane keeps in registers in count mode: binary32 values (plain),
-// or intervals of two floats each (certified: 11, which keeps the kernel
-// within its 128 VGPRs with few spills; the segments with more go to the
-// second pass -- 27k of 1e7 at the paper's scale, 6.38 -> 6.28 ms against 12)
+// Distinct t that the first pass lists per segment in count mode: binary32 values
+// (plain), or intervals of two floats each (certified).  The pool form's lists are
+// in LDS; the lane form's in registers, where 11 intervals keep the kernel within
+// its 128 VGPRs with few spills (1e7 segments at the paper's scale in that form:
+// 6.28 ms with 11, 6.38 with 12).  Segments with more go to the second pass, 27k
+// of those 1e7.
 template <bool CERT>
 constexpr int kCountSlots = CERT ? 11 : 12;
 

@@ -5,8 +5,10 @@
 // operating modes boolean / barycentric; Epilogue -- binary32 can misjudge
 // near-parallel rays, binary64 intermediates fix it.
 //
-// Pass 1 (k_traverse): one lane per segment, stack of pending subtrees in LDS
-// (stack_depth entries per lane), nearer child first, binary32 arithmetic.
+// Pass 1 (k_traverse; calls with few segments and the intercept count: k_pool in
+// pool.hip): one lane per segment, stack of pending subtrees in LDS (stack_depth
+// entries per lane), binary32 arithmetic.  Of a node's children the nearer first;
+// in boolean mode the one with the longer way through its box.
 //   PLAIN      the binary32 predicates decide.
 //   CERTIFIED  each predicate X comes with a proven bound B(X) on its distance
 //              from the exact value and from the binary64 value; |X| > B(X)
@@ -17,10 +19,12 @@
 //              division).  Nearest-hit choice uses proven intervals around
 //              the binary64 t, and the binary64 t themselves where two
 //              intervals overlap.
-// A segment whose path outgrows the LDS stack (or, in count mode, whose list
-// of distinct t overflows or holds nearly equal ones) is appended to a queue
-// and finished by pass 2 (k_finish): a deep private stack and, in CERTIFIED
-// precision, the binary64 test on every candidate.
+// A segment whose path outgrows the LDS stack waits for its wave's end, where the
+// wave's lanes share such segments (pool.h).  What finds no room there either, or
+// outgrows a stack too small for that pool or over binary nodes, and in count
+// mode a segment whose list of distinct t overflows or holds nearly equal ones,
+// is appended to a queue and finished by pass 2 (k_finish): a deep private stack
+// and, in CERTIFIED precision, the binary64 test on every candidate.
 //
 // Box test: the slab test on each child box widened by eta = 2^-20 max(|coord|)
 // of the segment and mesh.  That margin exceeds every rounding of the slab
@@ -912,7 +916,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, kMaxBlock<WIDE>))) void
     traverse_pass1<MODE, CERT, STATS, PROP, WIDE>(p, reinterpret_cast<int *>(lds_dyn));
 }
 
-// Count mode holds its list of distinct t in registers; the register budget
+// Count mode over binary nodes, or with a launch shape the caller chose (others
+// take k_pool), holds its list of distinct t in registers; the register budget
 // is fixed at four waves per SIMD (the default resident count) so the list
 // cannot lower occupancy.
 template <bool CERT, bool STATS, bool WIDE>
